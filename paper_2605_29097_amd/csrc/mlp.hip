@@ -29,6 +29,7 @@
 namespace rfvr {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
@@ -70,6 +71,48 @@ __device__ __forceinline__ void split_bf16x8(floatx4 lo, floatx4 hi, bf16x8& big
     }
 }
 
+// x = p[0] + p[1] + p[2], each BF16 (RNE): the first two remainders are exact in
+// FP32 and the third has at most 8 significant bits, so the three parts hold all
+// 24 bits of x (down to where the parts leave BF16's normal range, |x| ~ 1e-33)
+// (two values per conversion instruction: 11 VALU instructions a pair)
+__device__ __forceinline__ uint32_t pk_bf16(float x, float y) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x, y}, b2));
+}
+__device__ __forceinline__ void split3_bf16x8(floatx4 lo, floatx4 hi, bf16x8 p[3]) {
+    uintx4 w[3];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float x = e < 2 ? lo[2 * e] : hi[2 * e - 4], y = e < 2 ? lo[2 * e + 1] : hi[2 * e - 3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const uint32_t b = pk_bf16(x, y);
+            w[q][e] = b;
+            x -= __uint_as_float(b << 16);
+            y -= __uint_as_float(b & 0xffff0000u);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) p[q] = __builtin_bit_cast(bf16x8, w[q]);
+}
+
+// An FP32 product of one 16 x 16 tile over 32 k from operands split in three:
+// the six part products down to 2^-16 of the leading one (the three left out
+// are below 2^-25 of it), smallest first.  TM tiles share a point fragment, so
+// that consecutive MFMAs are independent.
+template <int TM>
+__device__ __forceinline__ void mfma_split3(const bf16x8 (&w)[TM][3], const bf16x8 (&a)[3], floatx4* acc,
+                                            bool points_first) {
+    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int b = 0; b < TM; ++b)
+            acc[b] = points_first ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[PA[q]], w[b][PB[q]], acc[b], 0, 0, 0)
+                                  : __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b][PB[q]], a[PA[q]], acc[b], 0, 0, 0);
+}
+
 // BF16 storage of the single-rounded BF16 backward's arrays (tangents Hdot and
 // adjoints Zbar): the BF16 products that read them round them to BF16 (RNE)
 // anyway, so they are stored rounded, as raw 16-bit words in buffers sized for
@@ -103,7 +146,8 @@ __device__ __forceinline__ void st_bf16(float* base, long i, float v) {
 // which operands of a GEMM are held in BF16 storage
 enum { ST_A = 1, ST_B = 2, ST_C2 = 4, ST_Y = 8 };
 
-// operand precision of a network GEMM: FP32 MFMA, BF16 MFMA, BF16 MFMA on split
+// operand precision of a network GEMM: FP32 (MM_FP32: operands split in three;
+// MM_MFMA32: the FP32 instruction, see gemm_first), BF16 MFMA, BF16 MFMA on split
 // operands (a b ~ a_big b_big + a_big b_small + a_small b_big), or FP16 MFMA
 // with the weights rounded once and the per-point operand split in two
 // (a b ~ a_big b + a_small b, two products).  The per-point operand's rounding
@@ -113,7 +157,7 @@ enum { ST_A = 1, ST_B = 2, ST_C2 = 4, ST_Y = 8 };
 // (its 5-bit exponent cannot hold the backward's adjoints, which scale with the
 // upstream gradients); in the dual forward GEMM, MM_F16 means this form for
 // the primal and BF16 for the tangent.
-enum { MM_FP32 = 0, MM_BF16 = 1, MM_F16 = 2, MM_BF16X3 = 3 };
+enum { MM_FP32 = 0, MM_BF16 = 1, MM_F16 = 2, MM_BF16X3 = 3, MM_MFMA32 = 4 };
 
 // operand prologues: identity, relu, or SEED: A[p][k] = H -> sp'(Z) colv[k] (the
 // normal sweep's seed from the top layer's activation, formed while the tile is
@@ -167,9 +211,13 @@ __device__ __forceinline__ float sp_d2(float z, float beta) {
 // current chunk's MFMAs.  The k index of a lane's MFMA operand is permuted so
 // each lane reads 4 consecutive k (one float4) per 16-wide k group.
 // ----------------------------------------------------------------------------
+// rows per block of a product's weight operand and of its split image
+__host__ __device__ constexpr int block_rows(int M) { return M <= 64 ? 64 : 128; }
+
 struct GemmArgs {
     const float* A; long lda;
     const float* B; long ldb;
+    const uint16_t* Bx;           // FP32: the split image of B (k_prep_split)
     const float* bias;            // EPI_BIAS*: [M] or null
     const float* C;               // EPI_RELUMASK / DSPMUL / TOPADJ: [P][ldc]
     const float* C2;              // EPI_TOPADJ, ADJ1: [P][ldc]
@@ -185,6 +233,160 @@ struct GemmArgs {
     long P; int M; int K;
     float beta;
 };
+
+// Epilogue of a block of BP x BM products, WP x (4 / WP) waves of TP x TM tiles
+// of 16 x 16; scr: (TP * 4) * (BM / WM) floats of LDS free for the column partials.
+template <int EPI, int BP, int BM, int WP, int ST, int TP, int TM>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx4 (&acc)[TP][TM], float* scr, long p0, int m0) {
+    constexpr int WM = 4 / WP;
+    const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+    const int wp = wv % WP, wm = wv / WP;
+    const int li = lane & 15, lg = lane >> 4;
+    // The weights are the MFMA's first operand, so a lane's four
+    // accumulator values acc[a][b][0..3] are four consecutive outputs
+    // m = m0 + wm (BM/WM) + 16 b + 4 lg + v of one point p = p0 + wp (BP/WP)
+    // + 16 a + li: one float4 of a row-major [P][ld] array.  Tiles wholly inside
+    // the output (with 16-byte aligned rows) load and store float4s without
+    // guards; the others clamp their loads into the arrays and guard each
+    // store.  A 16-point group's loads are all issued before the first is used.
+    constexpr int NC = (EPI == EPI_ADJ1) ? 3 : (EPI == EPI_TOPADJ) ? 2 : (EPI == EPI_DSPMUL || EPI == EPI_RELUMASK) ? 1 : 0;
+    auto epilogue = [&](auto guarded) {
+        constexpr bool GUARD = decltype(guarded)::value;
+        // per-output vector (bias, or the top adjoint's column vector): the same
+        // 16 values for every point group of the lane, loaded once
+        constexpr bool VEC = (EPI == EPI_BIAS || EPI == EPI_BIAS_SP || EPI == EPI_TOPADJ);
+        const float* vsrc = (EPI == EPI_TOPADJ) ? g.colv : g.bias;
+        floatx4 vv[VEC ? TM : 1];
+        if constexpr (VEC) {
+#pragma unroll
+            for (int b = 0; b < TM; ++b) {
+                const int mb = m0 + wm * (BM / WM) + b * 16 + lg * 4;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    vv[b][v] = vsrc ? vsrc[GUARD ? min(mb + v, g.M - 1) : mb + v] : 0.0f;
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < TP; ++a) {
+            const long p = p0 + wp * (BP / WP) + a * 16 + li;
+            const bool pin = !GUARD || p < g.P;
+            const long pr = pin ? p : g.P - 1;
+            floatx4 cl[NC ? NC : 1][TM];
+            const float* src[3] = {g.C, g.C2, g.C3};
+            if constexpr (NC > 0 && !GUARD) {
+#pragma unroll
+                for (int b = 0; b < TM; ++b) {
+                    const int mb = m0 + wm * (BM / WM) + b * 16 + lg * 4;
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) {
+                        if ((ST & ST_C2) != 0 && c == 1) {
+                            const float4 t = ld_bf16x4(src[c], pr * g.ldc + mb);
+                            cl[c][b] = floatx4{t.x, t.y, t.z, t.w};
+                        } else {
+                            cl[c][b] = *reinterpret_cast<const floatx4*>(src[c] + pr * g.ldc + mb);
+                        }
+                    }
+                }
+            }
+            float rv = 0.0f;
+            if constexpr (EPI == EPI_TOPADJ) rv = g.rowv ? g.scale * g.rowv[pr] : 0.0f;
+#pragma unroll
+            for (int b = 0; b < TM; ++b) {
+                const int mb = m0 + wm * (BM / WM) + b * 16 + lg * 4;
+                if constexpr (NC > 0 && GUARD) {
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const long ci = pr * g.ldc + min(mb + v, g.M - 1);
+                            cl[c][b][v] = ((ST & ST_C2) != 0 && c == 1) ? ld_bf16(src[c], ci) : src[c][ci];
+                        }
+                }
+                floatx4 y = acc[a][b], y2 = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_SP) y[v] += vv[b][v];
+                    if constexpr (EPI == EPI_BIAS_SP) y[v] = sp_f(y[v], g.beta);
+                    if constexpr (EPI == EPI_RELUMASK) y[v] = cl[0][b][v] > 0.0f ? y[v] : 0.0f;
+                    if constexpr (EPI == EPI_DSPMUL) y[v] *= sp_d1_h(cl[0][b][v], g.beta);
+                    if constexpr (EPI == EPI_TOPADJ) {
+                        const float cv = vv[b][v];
+                        const float hb = __builtin_fmaf(rv, cv, y[v]);
+                        const float hdb = g.scale * cv;
+                        const float em = fexp(-g.beta * cl[0][b][v]);   // 1 - sp'(Z)
+                        const float sg = 1.0f - em;
+                        y[v] = sg * hb + g.beta * em * cl[1][b][v] * hdb;
+                        y2[v] = sg * hdb;
+                    }
+                    if constexpr (EPI == EPI_ADJ1) {
+                        // the sweep kept S = sp'(Z) G, so sigma(-beta Z) G = exp(-beta Z) S,
+                        // with exp(-beta Z) = 1 / (e^(beta H) - 1)
+                        const float bh = g.beta * cl[0][b][v];
+                        const float ex = __builtin_amdgcn_rcpf(fexp(bh) - 1.0f);
+                        const float sg = 1.0f - fexp(-bh);
+                        y[v] = sg * y[v] + g.beta * fminf(ex, 1e30f) * cl[1][b][v] * (g.scale * cl[2][b][v]);
+                    }
+                }
+                constexpr bool TWO = (EPI == EPI_TOPADJ);
+                constexpr bool YB = (ST & ST_Y) != 0;
+                if constexpr (!GUARD) {
+                    if constexpr (YB) st_bf16x4(g.Y, p * g.ldy + mb, y);
+                    else *reinterpret_cast<floatx4*>(g.Y + p * g.ldy + mb) = y;
+                    if constexpr (TWO) *reinterpret_cast<floatx4*>(g.Y2 + p * g.ldy + mb) = y2;
+                } else if (pin) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        if (mb + v >= g.M) continue;
+                        if constexpr (YB) st_bf16(g.Y, p * g.ldy + mb + v, y[v]);
+                        else g.Y[p * g.ldy + mb + v] = y[v];
+                        if constexpr (TWO) g.Y2[p * g.ldy + mb + v] = y2[v];
+                    }
+                }
+                if constexpr (GUARD && NC >= 2) __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (EPI == EPI_TOPADJ) {
+                if (g.cpart) {
+                    // the group's share of the output layer's weight gradient,
+                    // sum_p (rowv[p] scale H + scale Hdot) per column: a fixed-order
+                    // sum over the 16 lanes of the same columns (lane bits 0-3:
+                    // the points), one row per (group, wave) into LDS
+#pragma unroll
+                    for (int b = 0; b < TM; ++b) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            float c = pin ? __builtin_fmaf(rv, cl[0][b][v], g.scale * cl[1][b][v]) : 0.0f;
+#pragma unroll
+                            for (int o = 1; o < 16; o <<= 1) c += __shfl_xor(c, o);
+                            if (li == 0) scr[(a * 4 + wv) * (BM / WM) + b * 16 + lg * 4 + v] = c;
+                        }
+                    }
+                }
+            }
+            // the next group's loads stay behind this group's stores
+            if constexpr (NC >= 2) __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    const bool aligned = (((g.ldy | g.ldc) & 3) == 0) &&
+                         (((uintptr_t)g.Y | (uintptr_t)g.Y2 | (uintptr_t)g.C | (uintptr_t)g.C2 | (uintptr_t)g.C3) & 15) == 0;
+    if (aligned && p0 + BP <= g.P && m0 + BM <= g.M) epilogue(std::false_type{});
+    else epilogue(std::true_type{});
+    if constexpr (EPI == EPI_TOPADJ) {
+        if (g.cpart) {
+            // the tile's column sums: one thread per column adds the rows of
+            // its waves along points and their groups in a fixed order (the LDS
+            // tiles were last read before the main loop's final barrier; the
+            // rows above were written after it); one partial row per tile
+            __syncthreads();
+            if (tid < BM) {
+                const int wmc = tid / (BM / WM), col = tid % (BM / WM);
+                float t = 0.0f;
+                for (int q = 0; q < WP; ++q)
+                    for (int a = 0; a < TP; ++a) t += scr[(a * 4 + (wmc * WP + q)) * (BM / WM) + col];
+                if (m0 + tid < g.M) g.cpart[(p0 / BP) * (long)g.M + m0 + tid] = t;
+            }
+        }
+    }
+}
 
 template <int PRO, int EPI, int BM, int MM, int ST = 0>
 __global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g) {
@@ -368,150 +570,128 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g) {
         compute();
         __syncthreads();
     }
-    // Epilogue.  The weights are the MFMA's first operand, so a lane's four
-    // accumulator values acc[a][b][0..3] are four consecutive outputs
-    // m = m0 + wm (BM/WM) + 16 b + 4 lg + v of one point p = p0 + wp (BP/WP)
-    // + 16 a + li: one float4 of a row-major [P][ld] array.  Tiles wholly inside
-    // the output (with 16-byte aligned rows) load and store float4s without
-    // guards; the others clamp their loads into the arrays and guard each
-    // store.  A 16-point group's loads are all issued before the first is used.
-    constexpr int NC = (EPI == EPI_ADJ1) ? 3 : (EPI == EPI_TOPADJ) ? 2 : (EPI == EPI_DSPMUL || EPI == EPI_RELUMASK) ? 1 : 0;
-    auto epilogue = [&](auto guarded) {
-        constexpr bool GUARD = decltype(guarded)::value;
-        // per-output vector (bias, or the top adjoint's column vector): the same
-        // 16 values for every point group of the lane, loaded once
-        constexpr bool VEC = (EPI == EPI_BIAS || EPI == EPI_BIAS_SP || EPI == EPI_TOPADJ);
-        const float* vsrc = (EPI == EPI_TOPADJ) ? g.colv : g.bias;
-        floatx4 vv[VEC ? TM : 1];
-        if constexpr (VEC) {
+    gemm_epilogue<EPI, BP, BM, WP, ST>(g, acc, sA, p0, m0);
+}
+
+// ----------------------------------------------------------------------------
+// The same product in FP32: every operand split in three BF16 parts
+// (mfma_split3), because six BF16 MFMAs over 32 k take 96 cycles of a SIMD's
+// matrix core where the FP32 instruction takes 256.  The per-point operand is split once, on
+// its way into LDS; the weights come split from k_prep_split.  Both lie in LDS in
+// fragment order: [part][16-row tile][slot][8 k], a lane's 16 bytes of a
+// fragment in one ds_read_b128 and a wave's in one linear kilobyte.  The store
+// side has four lanes on a row (32 bytes of k each, for coalesced global loads);
+// slot kg * 16 + (row ^ 2 kg) of (row, kg) keeps both sides free of bank conflicts.
+// 2^20 x 256 x 256, against the FP32 instruction in the same kernel shape:
+// softplus layer 1.17 -> 0.84 ms, sp'(Z) product 1.21 -> 0.95 ms, weight gradient
+// 1.45 -> 1.0 ms.  The main loop runs at 1.26 PFLOP/s of BF16 products, what a
+// large BF16 product reaches on this card (1.31); the epilogue's HBM traffic
+// (4.7 TB/s) is not hidden behind it.  Tried and slower: persistent work-groups
+// that fetch the next tile's first chunk and their epilogue's operands early
+// (training pair 45.4 -> 49.3 ms).
+// ----------------------------------------------------------------------------
+__device__ __forceinline__ int frag_slot(int row, int kg) { return kg * 16 + (row ^ (kg * 2)); }
+
+// T x T tiles; HB output tiles of a wave are multiplied at a time: with two,
+// three waves fit on a SIMD (all four, at two waves, read less LDS: better
+// where no third work-group would come to the CU anyway).
+template <int PRO, int EPI, int T, int HB>
+__global__ __launch_bounds__(256, T != 128 ? 4 : (HB == 4 || EPI == EPI_TOPADJ) ? 2 : 3) void k_gemm_nt32(GemmArgs g) {
+    constexpr int BP = T, BM = T, BK = 32, WP = 2, WM = 2;
+    constexpr int TP = BP / WP / 16, TM = BM / WM / 16;
+    constexpr int FT = 64 * 8;                   // 16-bit words of one tile of one part
+    constexpr int NA = BP / 64;                  // 8-k pieces of the point chunk per thread
+    constexpr int NBV = 3 * BM * BK / 8 / 256;   // 16-byte vectors of the weight chunk per thread
+    __shared__ __align__(16) uint16_t sA[3 * (BP / 16) * FT];
+    __shared__ __align__(16) uint16_t sB[3 * (BM / 16) * FT];
+    const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+    const int wp = wv % WP, wm = wv / WP;
+    const int li = lane & 15, lg = lane >> 4;
+    // XCD mapping as in k_gemm_nt
+    const int nmb = (g.M + BM - 1) / BM;
+    const long bid = blockIdx.x;
+    const long grp = bid / (8L * nmb);
+    const int within = (int)(bid % (8L * nmb));
+    const int mb = within / 8;
+    const long pt = grp * 8 + (within % 8);
+    const long p0 = pt * BP;
+    const int m0 = mb * BM;
+    if (p0 >= g.P) return;                       // padding work-groups of the last group
+    floatx4 acc[TP][TM];
 #pragma unroll
-            for (int b = 0; b < TM; ++b) {
-                const int mb = m0 + wm * (BM / WM) + b * 16 + lg * 4;
+    for (int a = 0; a < TP; ++a)
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    vv[b][v] = vsrc ? vsrc[GUARD ? min(mb + v, g.M - 1) : mb + v] : 0.0f;
-            }
+        for (int b = 0; b < TM; ++b) acc[a][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int nk = g.K / BK;
+    // the block's part of the image: BM of the bm rows of image block m0 / bm
+    const int bm = block_rows(g.M), pv = bm * 4;             // 16-byte vectors of one part of a chunk
+    const uintx4* img = reinterpret_cast<const uintx4*>(g.Bx) + (long)(m0 / bm) * nk * (3 * pv) + (m0 % bm) * 4;
+    floatx4 ra[NA][2];
+    uintx4 rb[NBV];
+    auto load = [&](int kc) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int u = tid + i * 256;
+            // rows beyond the last point repeat it: their products are not stored
+            const long p = min(p0 + (u >> 2), g.P - 1);
+            const floatx4* q = reinterpret_cast<const floatx4*>(g.A + p * g.lda + kc * BK + (u & 3) * 8);
+            ra[i][0] = q[0];
+            ra[i][1] = q[1];
         }
 #pragma unroll
-        for (int a = 0; a < TP; ++a) {
-            const long p = p0 + wp * (BP / WP) + a * 16 + li;
-            const bool pin = !GUARD || p < g.P;
-            const long pr = pin ? p : g.P - 1;
-            floatx4 cl[NC ? NC : 1][TM];
-            const float* src[3] = {g.C, g.C2, g.C3};
-            if constexpr (NC > 0 && !GUARD) {
-#pragma unroll
-                for (int b = 0; b < TM; ++b) {
-                    const int mb = m0 + wm * (BM / WM) + b * 16 + lg * 4;
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        if ((ST & ST_C2) != 0 && c == 1) {
-                            const float4 t = ld_bf16x4(src[c], pr * g.ldc + mb);
-                            cl[c][b] = floatx4{t.x, t.y, t.z, t.w};
-                        } else {
-                            cl[c][b] = *reinterpret_cast<const floatx4*>(src[c] + pr * g.ldc + mb);
-                        }
-                    }
-                }
-            }
-            float rv = 0.0f;
-            if constexpr (EPI == EPI_TOPADJ) rv = g.rowv ? g.scale * g.rowv[pr] : 0.0f;
-#pragma unroll
-            for (int b = 0; b < TM; ++b) {
-                const int mb = m0 + wm * (BM / WM) + b * 16 + lg * 4;
-                if constexpr (NC > 0 && GUARD) {
-#pragma unroll
-                    for (int c = 0; c < NC; ++c)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const long ci = pr * g.ldc + min(mb + v, g.M - 1);
-                            cl[c][b][v] = ((ST & ST_C2) != 0 && c == 1) ? ld_bf16(src[c], ci) : src[c][ci];
-                        }
-                }
-                floatx4 y = acc[a][b], y2 = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_SP) y[v] += vv[b][v];
-                    if constexpr (EPI == EPI_BIAS_SP) y[v] = sp_f(y[v], g.beta);
-                    if constexpr (EPI == EPI_RELUMASK) y[v] = cl[0][b][v] > 0.0f ? y[v] : 0.0f;
-                    if constexpr (EPI == EPI_DSPMUL) y[v] *= sp_d1_h(cl[0][b][v], g.beta);
-                    if constexpr (EPI == EPI_TOPADJ) {
-                        const float cv = vv[b][v];
-                        const float hb = __builtin_fmaf(rv, cv, y[v]);
-                        const float hdb = g.scale * cv;
-                        const float em = fexp(-g.beta * cl[0][b][v]);   // 1 - sp'(Z)
-                        const float sg = 1.0f - em;
-                        y[v] = sg * hb + g.beta * em * cl[1][b][v] * hdb;
-                        y2[v] = sg * hdb;
-                    }
-                    if constexpr (EPI == EPI_ADJ1) {
-                        // the sweep kept S = sp'(Z) G, so sigma(-beta Z) G = exp(-beta Z) S,
-                        // with exp(-beta Z) = 1 / (e^(beta H) - 1)
-                        const float bh = g.beta * cl[0][b][v];
-                        const float ex = __builtin_amdgcn_rcpf(fexp(bh) - 1.0f);
-                        const float sg = 1.0f - fexp(-bh);
-                        y[v] = sg * y[v] + g.beta * fminf(ex, 1e30f) * cl[1][b][v] * (g.scale * cl[2][b][v]);
-                    }
-                }
-                constexpr bool TWO = (EPI == EPI_TOPADJ);
-                constexpr bool YB = (ST & ST_Y) != 0;
-                if constexpr (!GUARD) {
-                    if constexpr (YB) st_bf16x4(g.Y, p * g.ldy + mb, y);
-                    else *reinterpret_cast<floatx4*>(g.Y + p * g.ldy + mb) = y;
-                    if constexpr (TWO) *reinterpret_cast<floatx4*>(g.Y2 + p * g.ldy + mb) = y2;
-                } else if (pin) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        if (mb + v >= g.M) continue;
-                        if constexpr (YB) st_bf16(g.Y, p * g.ldy + mb + v, y[v]);
-                        else g.Y[p * g.ldy + mb + v] = y[v];
-                        if constexpr (TWO) g.Y2[p * g.ldy + mb + v] = y2[v];
-                    }
-                }
-                if constexpr (GUARD && NC >= 2) __builtin_amdgcn_sched_barrier(0);
-            }
-            if constexpr (EPI == EPI_TOPADJ) {
-                if (g.cpart) {
-                    // the group's share of the output layer's weight gradient,
-                    // sum_p (rowv[p] scale H + scale Hdot) per column: a fixed-order
-                    // sum over the 16 lanes of the same columns (lane bits 0-3:
-                    // the points), one row per (group, wave) into LDS
-#pragma unroll
-                    for (int b = 0; b < TM; ++b) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            float c = pin ? __builtin_fmaf(rv, cl[0][b][v], g.scale * cl[1][b][v]) : 0.0f;
-#pragma unroll
-                            for (int o = 1; o < 16; o <<= 1) c += __shfl_xor(c, o);
-                            if (li == 0) sA[(a * 4 + wv) * (BM / WM) + b * 16 + lg * 4 + v] = c;
-                        }
-                    }
-                }
-            }
-            // the next group's loads stay behind this group's stores
-            if constexpr (NC >= 2) __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < NBV; ++i) {
+            const int v = i * 256 + tid;
+            rb[i] = img[(kc * 3 + v / (BM * 4)) * pv + v % (BM * 4)];
         }
     };
-    const bool aligned = (((g.ldy | g.ldc) & 3) == 0) &&
-                         (((uintptr_t)g.Y | (uintptr_t)g.Y2 | (uintptr_t)g.C | (uintptr_t)g.C2 | (uintptr_t)g.C3) & 15) == 0;
-    if (aligned && p0 + BP <= g.P && m0 + BM <= g.M) epilogue(std::false_type{});
-    else epilogue(std::true_type{});
-    if constexpr (EPI == EPI_TOPADJ) {
-        if (g.cpart) {
-            // the tile's column sums: one thread per column adds the rows of
-            // its waves along points and their groups in a fixed order (the LDS
-            // tiles were last read before the main loop's final barrier; the
-            // rows above were written after it); one partial row per tile
-            __syncthreads();
-            if (tid < BM) {
-                const int wmc = tid / (BM / WM), col = tid % (BM / WM);
-                float t = 0.0f;
-                for (int q = 0; q < WP; ++q)
-                    for (int a = 0; a < TP; ++a) t += sA[(a * 4 + (wmc * WP + q)) * (BM / WM) + col];
-                if (m0 + tid < g.M) g.cpart[(p0 / BP) * (long)g.M + m0 + tid] = t;
+    auto store = [&](int kc) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int u = tid + i * 256;
+            const int row = u >> 2, kg = u & 3;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (PRO == PRO_RELU) ra[i][h][e] = fmaxf(ra[i][h][e], 0.0f);
+                    if constexpr (PRO == PRO_SEED)
+                        ra[i][h][e] = sp_d1_h(ra[i][h][e], g.beta) * g.colv[kc * BK + kg * 8 + h * 4 + e];
+                }
+            bf16x8 part[3];
+            split3_bf16x8(ra[i][0], ra[i][1], part);
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                *reinterpret_cast<bf16x8*>(&sA[(q * (BP / 16) + (row >> 4)) * FT + frag_slot(row & 15, kg) * 8]) = part[q];
+        }
+#pragma unroll
+        for (int i = 0; i < NBV; ++i) *reinterpret_cast<uintx4*>(&sB[(i * 256 + tid) * 8]) = rb[i];
+    };
+    load(0);
+    for (int kc = 0; kc < nk; ++kc) {
+        store(kc);
+        __syncthreads();
+        if (kc + 1 < nk) load(kc + 1);
+#pragma unroll
+        for (int h = 0; h < TM; h += HB) {
+            bf16x8 wf[HB][3];
+#pragma unroll
+            for (int b = 0; b < HB; ++b)
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    wf[b][q] = *reinterpret_cast<const bf16x8*>(&sB[(q * (BM / 16) + wm * TM + h + b) * FT + lane * 8]);
+#pragma unroll
+            for (int a = 0; a < TP; ++a) {
+                bf16x8 af[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    af[q] = *reinterpret_cast<const bf16x8*>(&sA[(q * (BP / 16) + wp * TP + a) * FT + frag_slot(li, lg) * 8]);
+                mfma_split3<HB>(wf, af, &acc[a][h], false);
+                if constexpr (HB < TM) __builtin_amdgcn_sched_barrier(0);
             }
         }
+        __syncthreads();
     }
+    gemm_epilogue<EPI, BP, BM, WP, 0>(g, acc, reinterpret_cast<float*>(sA), p0, m0);
 }
 
 // ----------------------------------------------------------------------------
@@ -529,11 +709,71 @@ enum { EPI2_FWD = 0, EPI2_ADJ = 1 };
 struct DualArgs {
     const float* A; const float* A2; long lda;
     const float* B; long ldb;
+    const uint16_t* Bx;                     // FP32: the split image of B (k_prep_split)
     const float* bias;
     const float* C; const float* C2;        // EPI2_ADJ: [P][ldy]
     float* Y; float* Y2; float* Y3; long ldy;
     long P; int M; int K;
     float beta;
+};
+
+// Epilogue of a dual product: WP waves along points x 2 along outputs, TP x TM
+// tiles per wave.
+template <int EPI2, int BP, int BM, int WP>
+struct DualEpilogue {
+    static constexpr int TP = BP / WP / 16, TM = BM / 2 / 16;
+    float cz[EPI2 == EPI2_ADJ ? TP : 1][TM][4], chd[EPI2 == EPI2_ADJ ? TP : 1][TM][4];
+
+    __device__ __forceinline__ void prefetch(const DualArgs& g, long p0, int m0) {
+        const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, wp = wv % WP, wm = wv / WP, li = lane & 15, lg = lane >> 4;
+        // the adjoint epilogue's operands (Z and Hdot of the layer below) do not
+        // depend on the products: fetch them before the main loop
+        if constexpr (EPI2 == EPI2_ADJ) {
+#pragma unroll
+            for (int a = 0; a < TP; ++a)
+#pragma unroll
+                for (int b = 0; b < TM; ++b) {
+                    const int m = m0 + wm * (BM / 2) + b * 16 + li;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const long p = p0 + wp * (BP / WP) + a * 16 + lg * 4 + v;
+                        const bool in = m < g.M && p < g.P;
+                        cz[a][b][v] = in ? g.C[p * g.ldy + m] : 0.0f;
+                        chd[a][b][v] = in ? g.C2[p * g.ldy + m] : 0.0f;
+                    }
+                }
+        }
+    }
+
+    __device__ __forceinline__ void finish(const DualArgs& g, floatx4 (&acc)[TP][TM], floatx4 (&acd)[TP][TM], long p0, int m0) {
+        const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, wp = wv % WP, wm = wv / WP, li = lane & 15, lg = lane >> 4;
+#pragma unroll
+        for (int a = 0; a < TP; ++a)
+#pragma unroll
+            for (int b = 0; b < TM; ++b) {
+                const int m = m0 + wm * (BM / 2) + b * 16 + li;
+                if (m >= g.M) continue;
+                const float bias = (EPI2 == EPI2_FWD && g.bias) ? g.bias[m] : 0.0f;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const long p = p0 + wp * (BP / WP) + a * 16 + lg * 4 + v;
+                    if (p >= g.P) continue;
+                    const long o = p * g.ldy + m;
+                    if constexpr (EPI2 == EPI2_FWD) {
+                        const float z = acc[a][b][v] + bias;
+                        g.Y[o] = z;
+                        g.Y2[o] = sp_f(z, g.beta);
+                        g.Y3[o] = sp_d1(z, g.beta) * acd[a][b][v];
+                    } else {
+                        const float z = cz[a][b][v], hd = chd[a][b][v];
+                        const float sg = fsig(g.beta * z);
+                        const float hb = acc[a][b][v], hdb = acd[a][b][v];
+                        g.Y[o] = sg * hb + g.beta * (1.0f - sg) * hd * hdb;
+                        g.Y2[o] = sg * hdb;
+                    }
+                }
+            }
+    }
 };
 
 template <int EPI2, int MM, int NW>
@@ -568,24 +808,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_gemm_dual(DualArgs
             acc[a][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
             acd[a][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
         }
-    // the adjoint epilogue's operands (Z and Hdot of the layer below) do not
-    // depend on the products: fetch them before the main loop
-    float cz[TP][TM][4], chd[TP][TM][4];
-    if constexpr (EPI2 == EPI2_ADJ) {
-#pragma unroll
-        for (int a = 0; a < TP; ++a)
-#pragma unroll
-            for (int b = 0; b < TM; ++b) {
-                const int m = m0 + wm * (BM / 2) + b * 16 + li;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const long p = p0 + wp * (BP / WP) + a * 16 + lg * 4 + v;
-                    const bool in = m < g.M && p < g.P;
-                    cz[a][b][v] = in ? g.C[p * g.ldy + m] : 0.0f;
-                    chd[a][b][v] = in ? g.C2[p * g.ldy + m] : 0.0f;
-                }
-            }
-    }
+    DualEpilogue<EPI2, BP, BM, WP> epi;
+    epi.prefetch(g, p0, m0);
     float4 ra[NA], ra2[NA], rb[NB];
     auto load = [&](int k0) {
 #pragma unroll
@@ -627,7 +851,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_gemm_dual(DualArgs
         }
         __syncthreads();
         if (k0 + BK < g.K) load(k0 + BK);
-        if constexpr (MM == MM_FP32) {
+        if constexpr (MM == MM_MFMA32) {
 #pragma unroll
             for (int kk = 0; kk < BK; kk += 16) {
                 floatx4 af[TP], af2[TP], bf[TM];
@@ -715,32 +939,88 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_gemm_dual(DualArgs
         }
         __syncthreads();
     }
+    epi.finish(g, acc, acd, p0, m0);
+}
+
+// the FP32 dual product, operands split in three (k_gemm_nt32): 64 points x BM
+// outputs, 2 x 2 waves
+template <int EPI2, int BM>
+__global__ __launch_bounds__(256, 2) void k_gemm_dual32(DualArgs g) {
+    constexpr int BP = 64, BK = 32, WP = 2, TP = BP / WP / 16, TM = BM / 2 / 16;
+    constexpr int FT = 64 * 8, NBV = 3 * BM * BK / 8 / 256;
+    __shared__ __align__(16) uint16_t sA[2][3 * (BP / 16) * FT];
+    __shared__ __align__(16) uint16_t sB[3 * (BM / 16) * FT];
+    const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+    const int wp = wv % WP, wm = wv / WP;
+    const int li = lane & 15, lg = lane >> 4;
+    const int nmb = (g.M + BM - 1) / BM;
+    const long bid = blockIdx.x;
+    const long grp = bid / (8L * nmb);
+    const int within = (int)(bid % (8L * nmb));
+    const int mb = within / 8;
+    const long pt = grp * 8 + (within % 8);
+    const long p0 = pt * BP;
+    const int m0 = mb * BM;
+    if (p0 >= g.P) return;                       // padding work-groups of the last group
+    floatx4 acc[TP][TM], acd[TP][TM];
 #pragma unroll
     for (int a = 0; a < TP; ++a)
 #pragma unroll
         for (int b = 0; b < TM; ++b) {
-            const int m = m0 + wm * (BM / 2) + b * 16 + li;
-            if (m >= g.M) continue;
-            const float bias = (EPI2 == EPI2_FWD && g.bias) ? g.bias[m] : 0.0f;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const long p = p0 + wp * (BP / WP) + a * 16 + lg * 4 + v;
-                if (p >= g.P) continue;
-                const long o = p * g.ldy + m;
-                if constexpr (EPI2 == EPI2_FWD) {
-                    const float z = acc[a][b][v] + bias;
-                    g.Y[o] = z;
-                    g.Y2[o] = sp_f(z, g.beta);
-                    g.Y3[o] = sp_d1(z, g.beta) * acd[a][b][v];
-                } else {
-                    const float z = cz[a][b][v], hd = chd[a][b][v];
-                    const float sg = fsig(g.beta * z);
-                    const float hb = acc[a][b][v], hdb = acd[a][b][v];
-                    g.Y[o] = sg * hb + g.beta * (1.0f - sg) * hd * hdb;
-                    g.Y2[o] = sg * hdb;
-                }
-            }
+            acc[a][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+            acd[a][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
         }
+    DualEpilogue<EPI2, BP, BM, WP> epi;
+    epi.prefetch(g, p0, m0);
+    const int nk = g.K / BK;
+    const uintx4* img = reinterpret_cast<const uintx4*>(g.Bx) + (long)mb * nk * (NBV * 256);
+    const int row = tid >> 2, kg = tid & 3;
+    const long pr = min(p0 + row, g.P - 1);      // rows beyond the last point repeat it
+    floatx4 ra[2][2];
+    uintx4 rb[NBV];
+    auto load = [&](int kc) {
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            const floatx4* q = reinterpret_cast<const floatx4*>((w ? g.A2 : g.A) + pr * g.lda + kc * BK + kg * 8);
+            ra[w][0] = q[0];
+            ra[w][1] = q[1];
+        }
+#pragma unroll
+        for (int i = 0; i < NBV; ++i) rb[i] = img[(long)kc * (NBV * 256) + i * 256 + tid];
+    };
+    load(0);
+    for (int kc = 0; kc < nk; ++kc) {
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            bf16x8 part[3];
+            split3_bf16x8(ra[w][0], ra[w][1], part);
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                *reinterpret_cast<bf16x8*>(&sA[w][(q * (BP / 16) + (row >> 4)) * FT + frag_slot(row & 15, kg) * 8]) = part[q];
+        }
+#pragma unroll
+        for (int i = 0; i < NBV; ++i) *reinterpret_cast<uintx4*>(&sB[(i * 256 + tid) * 8]) = rb[i];
+        __syncthreads();
+        if (kc + 1 < nk) load(kc + 1);
+        bf16x8 wf[TM][3];
+#pragma unroll
+        for (int b = 0; b < TM; ++b)
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                wf[b][q] = *reinterpret_cast<const bf16x8*>(&sB[(q * (BM / 16) + wm * TM + b) * FT + lane * 8]);
+#pragma unroll
+        for (int a = 0; a < TP; ++a)
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+                bf16x8 af[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    af[q] = *reinterpret_cast<const bf16x8*>(&sA[w][(q * (BP / 16) + wp * TP + a) * FT + frag_slot(li, lg) * 8]);
+                mfma_split3<TM>(wf, af, w ? acd[a] : acc[a], true);
+            }
+        __syncthreads();
+    }
+    epi.finish(g, acc, acd, p0, m0);
 }
 
 // ----------------------------------------------------------------------------
@@ -876,7 +1156,7 @@ __global__ __launch_bounds__(256, MM == MM_BF16 ? 3 : 1) void k_gemm_wg(WgArgs g
                 for (int b = 0; b < 4; ++b)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[b], acc[a][b], 0, 0, 0);
             }
-        } else if constexpr (MM != MM_FP32) {
+        } else {
             // points lg*4 + s and 16 + lg*4 + s (s < 4) fill the 8 k slots of a lane
             floatx4 a0[4], a1[4], b0[4], b1[4];
 #pragma unroll
@@ -908,24 +1188,6 @@ __global__ __launch_bounds__(256, MM == MM_BF16 ? 3 : 1) void k_gemm_wg(WgArgs g
                         acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab[a], bb[b], acc[a][b], 0, 0, 0);
                     }
             }
-        } else {
-#pragma unroll
-            for (int kk = 0; kk < BK; kk += 16) {
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const int r = kk + lg * 4 + s;
-                    float af[4], bf[4];
-#pragma unroll
-                    for (int a = 0; a < 4; ++a) af[a] = sA[r * LW + wp * 64 + a * 16 + li];
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) bf[b] = sB[r * LW + wn * 64 + b * 16 + li];
-#pragma unroll
-                    for (int a = 0; a < 4; ++a)
-#pragma unroll
-                        for (int b = 0; b < 4; ++b)
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[a], bf[b], acc[a][b], 0, 0, 0);
-                }
-            }
         }
         __syncthreads();
     }
@@ -944,6 +1206,156 @@ __global__ __launch_bounds__(256, MM == MM_BF16 ? 3 : 1) void k_gemm_wg(WgArgs g
         }
     if constexpr (BIAS) {
         if (first_n && tid < BM && m0 + tid < g.M) g.bpart[split * (long)g.M + m0 + tid] = bsum;
+    }
+}
+
+// The FP32 weight gradient, both operands split in three (k_gemm_nt32).  The
+// contraction runs over points, so a fragment holds 8 points of one column: wave
+// w loads points 8 w .. 8 w + 7 of two neighbouring columns per lane (512
+// contiguous bytes per row), splits them where they are, and stores each
+// column's 8 points as one 16-byte vector per part.  Column c of a 16-column
+// tile t lies in slot ((c >> 1) | (c & 1) << 3) ^ (t & 1) << 3: the even and the
+// odd columns that 16 lanes store together, and the 16 columns that they load
+// together, then fall on different banks.
+__device__ __forceinline__ int wg_slot(int c, int t) { return ((c >> 1) | ((c & 1) << 3)) ^ ((t & 1) << 3); }
+
+template <int PRO, bool BIAS, int ST = 0>
+__global__ __launch_bounds__(256, 2) void k_gemm_wg32(WgArgs g) {
+    constexpr int BM = 128, BN = 128, BK = 32, FT = 64 * 8;
+    __shared__ __align__(16) uint16_t sA[3 * (BM / 16) * FT];
+    __shared__ __align__(16) uint16_t sB[3 * (BN / 16) * FT];
+    const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+    const int wp = wv % 2, wn = wv / 2;
+    const int li = lane & 15, lg = lane >> 4;
+    // XCD mapping as in k_gemm_wg
+    const int nmb = (g.M + BM - 1) / BM, nnb = (g.Kout + BN - 1) / BN;
+    const long bid = blockIdx.x;
+    const long grp = bid / (8L * nmb * nnb);
+    const int within = (int)(bid % (8L * nmb * nnb));
+    const int tile = within / 8;
+    const long split = grp * 8 + (within % 8);
+    if (split >= g.n_split) return;              // padding work-groups of the last group
+    const int m0 = (tile % nmb) * BM, n0 = (tile / nmb) * BN;
+    const bool first_n = (tile / nmb) == 0;
+    const long pb = split * g.per_split;
+    long pe = pb + g.per_split;
+    if (pe > g.P) pe = g.P;
+    floatx4 acc[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    float2 bsum = make_float2(0.0f, 0.0f);       // sums of A's columns 2 lane, 2 lane + 1 over the wave's points
+    const int ca = m0 + 2 * lane, cb = n0 + 2 * lane;
+    const bool in_a = ca < g.M, in_b = cb < g.Kout;   // column counts are even
+    float2 ra[8], rb[8];
+    uint32_t ra16[8];                            // ST_A: the raw words, widened once they are used
+    auto load = [&](long q0) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const long p = q0 + wv * 8 + j;
+            if constexpr ((ST & ST_A) != 0) ra16[j] = 0u;
+            else ra[j] = make_float2(0.0f, 0.0f);
+            rb[j] = make_float2(0.0f, 0.0f);
+            if (p < pe) {
+                if (in_a) {
+                    if constexpr ((ST & ST_A) != 0)
+                        ra16[j] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint16_t*>(g.A) + p * g.lda + ca);
+                    else
+                        ra[j] = *reinterpret_cast<const float2*>(g.A + p * g.lda + ca);
+                }
+                if (in_b) rb[j] = *reinterpret_cast<const float2*>(g.B + p * g.ldb + cb);
+            }
+        }
+    };
+    // both columns' 8 points, split, into the fragment image of s
+    auto put = [&](uint16_t* s, const float2 (&r)[8]) {
+        const int t = lane >> 3, c = (2 * lane) & 15;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            floatx4 lo, hi;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                lo[j] = h ? r[j].y : r[j].x;
+                hi[j] = h ? r[4 + j].y : r[4 + j].x;
+            }
+            bf16x8 part[3];
+            split3_bf16x8(lo, hi, part);
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                *reinterpret_cast<bf16x8*>(&s[(q * 8 + t) * FT + (wv * 16 + wg_slot(c + h, t)) * 8]) = part[q];
+        }
+    };
+    if (pb < pe) load(pb);
+    for (long q0 = pb; q0 < pe; q0 += BK) {
+        if constexpr ((ST & ST_A) != 0) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                ra[j] = make_float2(__uint_as_float(ra16[j] << 16), __uint_as_float(ra16[j] & 0xffff0000u));
+        }
+        if constexpr (PRO == PRO_RELU) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                rb[j].x = fmaxf(rb[j].x, 0.0f);
+                rb[j].y = fmaxf(rb[j].y, 0.0f);
+            }
+        }
+        if constexpr (BIAS) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                bsum.x += ra[j].x;
+                bsum.y += ra[j].y;
+            }
+        }
+        put(sA, ra);
+        put(sB, rb);
+        __syncthreads();
+        if (q0 + BK < pe) load(q0 + BK);
+        bf16x8 bf[4][3];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                bf[b][q] = *reinterpret_cast<const bf16x8*>(&sB[(q * 8 + wn * 4 + b) * FT + (lg * 16 + wg_slot(li, b)) * 8]);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            bf16x8 af[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                af[q] = *reinterpret_cast<const bf16x8*>(&sA[(q * 8 + wp * 4 + a) * FT + (lg * 16 + wg_slot(li, a)) * 8]);
+            mfma_split3<4>(bf, af, acc[a], true);
+        }
+        __syncthreads();
+    }
+    float* out = g.part + split * (long)g.M * g.Kout;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int k = n0 + wn * 64 + b * 16 + li;
+            if (k >= g.Kout) continue;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int m = m0 + wp * 64 + a * 16 + lg * 4 + v;
+                if (m < g.M) out[(long)m * g.Kout + k] = acc[a][b][v];
+            }
+        }
+    if constexpr (BIAS) {
+        if (first_n) {
+            // the four waves' column sums, added in wave order
+            float2* sb = reinterpret_cast<float2*>(sA);
+            sb[tid] = bsum;
+            __syncthreads();
+            if (wv == 0 && in_a) {
+                float2 t = sb[lane];
+                for (int w = 1; w < 4; ++w) {
+                    t.x += sb[w * 64 + lane].x;
+                    t.y += sb[w * 64 + lane].y;
+                }
+                g.bpart[split * (long)g.M + ca] = t.x;
+                g.bpart[split * (long)g.M + ca + 1] = t.y;
+            }
+        }
     }
 }
 
@@ -1177,35 +1589,20 @@ __global__ void k_fill(float* __restrict__ p, long n, float v) {
     if (o < n) p[o] = v;
 }
 
-// out[c][r] = in[r][c] for r < R, c < C, zero in the padding; out is [Cpad][Rpad]
-__global__ void k_transpose_pad(const float* __restrict__ in, int R, int C, int Rpad, int Cpad,
-                                float* __restrict__ out) {
-    const long o = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= (long)Rpad * Cpad) return;
-    const int c = (int)(o / Rpad), r = (int)(o % Rpad);
-    out[o] = (r < R && c < C) ? in[(long)r * C + c] : 0.0f;
-}
-
-// out[r][c] = in[r][c] zero padded to [R][Cpad]
-__global__ void k_pad_cols(const float* __restrict__ in, int R, int C, int Cpad, float* __restrict__ out) {
-    const long o = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= (long)R * Cpad) return;
-    const int r = (int)(o / Cpad), c = (int)(o % Cpad);
-    out[o] = c < C ? in[(long)r * C + c] : 0.0f;
-}
-
-// All of a call's weight copies in one launch: job k writes elements
-// [begin[k], begin[k+1]) of the concatenated outputs, either in[R][C] zero
-// padded to [R][Cpad] or its transpose zero padded to [Cpad][Rpad].
+// All of a call's weight copies in one launch.  Job k makes an operand
+// [N][K] of a GEMM from the parameters, element (n, k) = in[n * C + k] or, for
+// the transpose, in[k * C + n], zero outside in[R][C]: as FP32 rows (one unit
+// per element), or split in three as the image that the FP32 kernels copy to LDS
+// (one unit per 8 k of a row): [block of BM rows][32 k][part][16-row tile][k / 8][row][8 k].
 constexpr int kPrepJobs = 40;
 struct PrepJob {
     const float* in;
-    float* out;
-    int R, C, Rpad, Cpad, transpose, pad;
+    void* out;
+    int R, C, K, transpose, bm;    // bm: rows per block of the image, 0 for FP32 rows
 };
 struct PrepTable {
     PrepJob job[kPrepJobs];
-    long begin[kPrepJobs + 1];
+    long begin[kPrepJobs + 1];     // in units
     int n;
 };
 __global__ void k_prep_weights(PrepTable t) {
@@ -1214,11 +1611,30 @@ __global__ void k_prep_weights(PrepTable t) {
         int k = 0;
         while (k + 1 < t.n && o >= t.begin[k + 1]) ++k;
         const PrepJob& j = t.job[k];
-        const long q = o - t.begin[k];
-        int r, c;
-        if (j.transpose) { c = (int)(q / j.Rpad); r = (int)(q % j.Rpad); }
-        else { r = (int)(q / j.Cpad); c = (int)(q % j.Cpad); }
-        j.out[q] = (r < j.R && c < j.C) ? j.in[(long)r * j.C + c] : 0.0f;
+        const long u = o - t.begin[k];
+        auto at = [&](int n, int kk) {
+            const int r = j.transpose ? kk : n, c = j.transpose ? n : kk;
+            return (r < j.R && c < j.C) ? j.in[(long)r * j.C + c] : 0.0f;
+        };
+        if (j.bm == 0) {
+            reinterpret_cast<float*>(j.out)[u] = at((int)(u / j.K), (int)(u % j.K));
+        } else {
+            const int slot = (int)(u % 64), tiles = j.bm / 16, nk = j.K / 32;
+            const int tile = (int)(u / 64) % tiles;
+            const int blk = (int)(u / 64 / tiles);             // block of rows * nk + 32-wide k chunk
+            const int n = (blk / nk) * j.bm + tile * 16 + (slot & 15), k0 = (blk % nk) * 32 + (slot >> 4) * 8;
+            floatx4 lo, hi;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                lo[e] = at(n, k0 + e);
+                hi[e] = at(n, k0 + 4 + e);
+            }
+            bf16x8 part[3];
+            split3_bf16x8(lo, hi, part);
+            uint16_t* out = reinterpret_cast<uint16_t*>(j.out) + (long)blk * 3 * tiles * 512;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<bf16x8*>(&out[((long)q * tiles + tile) * 512 + slot * 8]) = part[q];
+        }
     }
 }
 
@@ -1291,59 +1707,95 @@ Layout layout(const rfvr_mlp* n) {
 inline unsigned blocks(long n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
 // device copies of the weights in the layouts the GEMMs read, 256-byte
-// aligned (the flat parameter vector has matrices at odd offsets)
+// aligned: the split image x for the FP32 products, FP32 rows f for the others
+// (in the 16-bit forms only the last sweep product, WT[0], reads an image)
+struct WMat {
+    float* f = nullptr;
+    uint16_t* x = nullptr;
+};
 struct Weights {
-    float* Wp[16];         // W_l [W][fin_pad], zero padded
-    float* WT[16];         // W_l^T [fin_pad][W]
-    float* Whp[4];         // Wh_h [HW][fin]
-    float* WhT[4];         // Wh_h^T [fin][HW]
+    WMat Wp[16];           // W_l [W][fin_pad], zero padded
+    WMat WT[16];           // W_l^T [fin_pad][W]
+    WMat Whp[4];           // Wh_h [HW][fin]
+    WMat WhT[4];           // Wh_h^T [fin][HW]
 };
 
-size_t weights_bytes(const Layout& l) {
+size_t image_words(int N, int K) { return (size_t)((N + block_rows(N) - 1) / block_rows(N)) * block_rows(N) * K * 3; }
+size_t wmat_bytes(int N, int K, bool split) {
+    return align256(split ? sizeof(uint16_t) * image_words(N, K) : sizeof(float) * (size_t)N * K);
+}
+WMat take_wmat(WsCursor& cur, int N, int K, bool split) {
+    WMat w;
+    if (split) w.x = cur.take<uint16_t>(image_words(N, K));
+    else w.f = cur.take<float>((size_t)N * K);
+    return w;
+}
+
+struct PrepList {
+    PrepTable t = {};
+    long total = 0;
+    // operand [N][K] of in[R][C] (or of its transpose)
+    void add(const float* in, const WMat& w, int R, int C, int N, int K, int transpose) {
+        PrepJob& j = t.job[t.n];
+        j.in = in; j.R = R; j.C = C; j.K = K; j.transpose = transpose;
+        j.bm = w.x ? block_rows(N) : 0;
+        j.out = w.x ? (void*)w.x : (void*)w.f;
+        t.begin[t.n] = total;
+        total += w.x ? (long)(image_words(N, K) / 24) : (long)N * K;
+        ++t.n;
+    }
+    hipError_t launch(hipStream_t st) {
+        t.begin[t.n] = total;
+        long nb = (total + 255) / 256;
+        if (nb > 2048) nb = 2048;
+        hipLaunchKernelGGL(k_prep_weights, dim3((unsigned)nb), dim3(256), 0, st, t);
+        return hipGetLastError();
+    }
+};
+
+size_t weights_bytes(const Layout& l, int precision) {
+    const bool f32 = precision == RFVR_PREC_FP32;
     size_t b = 0;
-    for (int i = 0; i < l.L; ++i) b += 2 * align256(sizeof(float) * (i == 0 ? l.in0p : l.W) * l.W);
-    for (int h = 0; h < l.HL; ++h) b += 2 * align256(sizeof(float) * (h == 0 ? l.W : l.HW) * l.HW);
+    for (int i = 0; i < l.L; ++i) {
+        const int fin = i == 0 ? l.in0p : l.W;
+        b += wmat_bytes(l.W, fin, f32) + wmat_bytes(fin, l.W, f32 || i == 0);
+    }
+    for (int h = 0; h < l.HL; ++h) {
+        const int fin = h == 0 ? l.W : l.HW;
+        b += wmat_bytes(l.HW, fin, f32) + wmat_bytes(fin, l.HW, f32);
+    }
     return b;
 }
 
-Weights take_weights(WsCursor& cur, const Layout& l) {
+Weights take_weights(WsCursor& cur, const Layout& l, int precision) {
+    const bool f32 = precision == RFVR_PREC_FP32;
     Weights w;
     for (int i = 0; i < l.L; ++i) {
-        w.Wp[i] = cur.take<float>((size_t)(i == 0 ? l.in0p : l.W) * l.W);
-        w.WT[i] = cur.take<float>((size_t)(i == 0 ? l.in0p : l.W) * l.W);
+        const int fin = i == 0 ? l.in0p : l.W;
+        w.Wp[i] = take_wmat(cur, l.W, fin, f32);
+        w.WT[i] = take_wmat(cur, fin, l.W, f32 || i == 0);
     }
     for (int h = 0; h < l.HL; ++h) {
-        w.Whp[h] = cur.take<float>((size_t)(h == 0 ? l.W : l.HW) * l.HW);
-        w.WhT[h] = cur.take<float>((size_t)(h == 0 ? l.W : l.HW) * l.HW);
+        const int fin = h == 0 ? l.W : l.HW;
+        w.Whp[h] = take_wmat(cur, l.HW, fin, f32);
+        w.WhT[h] = take_wmat(cur, fin, l.HW, f32);
     }
     return w;
 }
 
 hipError_t prep_weights(const Layout& l, const float* P, const Weights& w, hipStream_t st) {
-    PrepTable t = {};
-    long total = 0;
-    auto add = [&](const float* in, float* out, int R, int C, int Rpad, int Cpad, int transpose) {
-        PrepJob& j = t.job[t.n];
-        j.in = in; j.out = out; j.R = R; j.C = C; j.Rpad = Rpad; j.Cpad = Cpad; j.transpose = transpose;
-        t.begin[t.n] = total;
-        total += (long)Rpad * Cpad;
-        ++t.n;
-    };
+    PrepList q;
     for (int i = 0; i < l.L; ++i) {          // at most 16 layers and 4 head layers: <= 40 jobs
         const int fin = i == 0 ? l.in0 : l.W, finp = i == 0 ? l.in0p : l.W;
-        add(P + l.oW[i], w.Wp[i], l.W, fin, l.W, finp, 0);
-        add(P + l.oW[i], w.WT[i], l.W, fin, l.W, finp, 1);
+        q.add(P + l.oW[i], w.Wp[i], l.W, fin, l.W, finp, 0);
+        q.add(P + l.oW[i], w.WT[i], l.W, fin, finp, l.W, 1);
     }
     for (int h = 0; h < l.HL; ++h) {
         const int fin = h == 0 ? l.W : l.HW;
-        add(P + l.oWh[h], w.Whp[h], l.HW, fin, l.HW, fin, 0);
-        add(P + l.oWh[h], w.WhT[h], l.HW, fin, l.HW, fin, 1);
+        q.add(P + l.oWh[h], w.Whp[h], l.HW, fin, l.HW, fin, 0);
+        q.add(P + l.oWh[h], w.WhT[h], l.HW, fin, fin, l.HW, 1);
     }
-    t.begin[t.n] = total;
-    long nb = (total + 255) / 256;
-    if (nb > 2048) nb = 2048;
-    hipLaunchKernelGGL(k_prep_weights, dim3((unsigned)nb), dim3(256), 0, st, t);
-    return hipGetLastError();
+    return q.launch(st);
 }
 
 // operand form of the forward products (layers, head, the grad_x f sweep) and
@@ -1365,16 +1817,36 @@ struct Cx {
     int mm;        // MM_*
 };
 
+// point tiles of tp points x output blocks, 8 point tiles per XCD group
+dim3 gemm_grid(long P, int tp, int M, int bm) {
+    const long groups = ((P + tp - 1) / tp + 7) / 8;
+    return dim3((unsigned)(groups * 8 * ((M + bm - 1) / bm)));
+}
+
+// Tile of the FP32 products: 128 x 128 where they fill the 256 CUs; below that the
+// 64 x 64 ones put four times the work-groups on the chip (a forward of the
+// 8 x 256 network at 5120 points, 80 large tiles: 345 us with them, 213 with
+// the small ones).
+int split_tile(long P, int M) { return M <= 64 || gemm_grid(P, 128, M, 128).x < 384 ? 64 : 128; }
+
 template <int PRO, int EPI, int MM, int ST = 0>
 void gemm_launch(const GemmArgs& a, hipStream_t st) {
-    const long tiles = (a.P + 127) / 128;
-    const long groups = (tiles + 7) / 8;                 // 8 point tiles per XCD group
-    if (a.M <= 64) {
-        hipLaunchKernelGGL((k_gemm_nt<PRO, EPI, 64, MM, ST>), dim3((unsigned)(groups * 8)), dim3(256), 0, st, a);
+    const int bm = block_rows(a.M);
+    const dim3 grid = gemm_grid(a.P, 128, a.M, bm);
+    if constexpr (MM == MM_FP32) {
+        static_assert(ST == 0, "the FP32 kernel has no BF16 storage");
+        // up to two large tiles a CU take all their outputs at a time (training
+        // pair at 32768 points, 512 tiles: 3.21 ms in halves, 3.12)
+        const dim3 g128 = gemm_grid(a.P, 128, a.M, 128);
+        if (split_tile(a.P, a.M) == 64)
+            hipLaunchKernelGGL((k_gemm_nt32<PRO, EPI, 64, 2>), gemm_grid(a.P, 64, a.M, 64), dim3(256), 0, st, a);
+        else if (g128.x <= 512)
+            hipLaunchKernelGGL((k_gemm_nt32<PRO, EPI, 128, 4>), g128, dim3(256), 0, st, a);
+        else
+            hipLaunchKernelGGL((k_gemm_nt32<PRO, EPI, 128, 2>), g128, dim3(256), 0, st, a);
     } else {
-        const long nmb = (a.M + 127) / 128;
-        hipLaunchKernelGGL((k_gemm_nt<PRO, EPI, 128, MM, ST>), dim3((unsigned)(groups * 8 * nmb)), dim3(256), 0,
-                           st, a);
+        if (bm == 64) hipLaunchKernelGGL((k_gemm_nt<PRO, EPI, 64, MM, ST>), grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((k_gemm_nt<PRO, EPI, 128, MM, ST>), grid, dim3(256), 0, st, a);
     }
 }
 
@@ -1391,10 +1863,24 @@ void gemm(const GemmArgs& a, const Cx& cx) {
     } else gemm_launch<PRO, EPI, MM_FP32>(a, cx.st);
 }
 
-// FP32 GEMM whatever the context (first layer: its operand is the encoding)
-template <int PRO, int EPI, int ST = 0>
+// FP32 GEMM whatever the context (the last sweep product: its result is the
+// encoding's adjoint)
+template <int PRO, int EPI>
 void gemm32(const GemmArgs& a, const Cx& cx) {
-    gemm_launch<PRO, EPI, MM_FP32, ST>(a, cx.st);
+    gemm_launch<PRO, EPI, MM_FP32>(a, cx.st);
+}
+
+// The first layer's products, FP32 in every form (their operand is the
+// encoding).  The 16-bit forms keep the FP32 instruction: a last-bit change of
+// this layer would move the 16-bit roundings of all that follow (6e-5 of the
+// gradient in the FP16 form), and a product over at most 96 k is bound by the
+// activations it writes either way.
+template <int EPI, int ST = 0>
+void gemm_first(const GemmArgs& a, const Cx& cx) {
+    if constexpr (ST == 0) {
+        if (!a.B) return gemm_launch<PRO_ID, EPI, MM_FP32>(a, cx.st);
+    }
+    gemm_launch<PRO_ID, EPI, MM_MFMA32, ST>(a, cx.st);
 }
 
 // BF16 GEMM of the single-rounded BF16 backward with the ST_* operands in BF16
@@ -1409,33 +1895,40 @@ void gemm_b16(const GemmArgs& a, const Cx& cx) {
 #endif
 template <int EPI2>
 void gemm_dual(const DualArgs& a, int mm, hipStream_t st) {
-    constexpr int NW = RFVR_DUAL_NW, BP = NW == 8 ? 128 : 64, BM = 128;
-    const long tiles = (a.P + BP - 1) / BP;
-    const long groups = (tiles + 7) / 8;
-    const long nmb = (a.M + BM - 1) / BM;
-    const dim3 grid((unsigned)(groups * 8 * nmb));
-    if (mm == MM_BF16) hipLaunchKernelGGL((k_gemm_dual<EPI2, MM_BF16, NW>), grid, dim3(NW * 64), 0, st, a);
-    else if (mm == MM_BF16X3) hipLaunchKernelGGL((k_gemm_dual<EPI2, MM_BF16X3, NW>), grid, dim3(NW * 64), 0, st, a);
-    else if constexpr (EPI2 == EPI2_FWD) {
-        if (mm == MM_F16) hipLaunchKernelGGL((k_gemm_dual<EPI2, MM_F16, NW>), grid, dim3(NW * 64), 0, st, a);
-        else hipLaunchKernelGGL((k_gemm_dual<EPI2, MM_FP32, NW>), grid, dim3(NW * 64), 0, st, a);
-    } else hipLaunchKernelGGL((k_gemm_dual<EPI2, MM_FP32, NW>), grid, dim3(NW * 64), 0, st, a);
+    if (mm == MM_FP32) {
+        const int bm = block_rows(a.M);
+        const dim3 grid = gemm_grid(a.P, 64, a.M, bm);
+        if (bm == 64) hipLaunchKernelGGL((k_gemm_dual32<EPI2, 64>), grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((k_gemm_dual32<EPI2, 128>), grid, dim3(256), 0, st, a);
+        return;
+    }
+    constexpr int NW = RFVR_DUAL_NW, BP = NW == 8 ? 128 : 64;
+    const dim3 grid = gemm_grid(a.P, BP, a.M, 128);
+    if constexpr (EPI2 == EPI2_FWD) {
+        if (mm == MM_F16 || mm == MM_MFMA32) {
+            if (mm == MM_F16) hipLaunchKernelGGL((k_gemm_dual<EPI2, MM_F16, NW>), grid, dim3(NW * 64), 0, st, a);
+            else hipLaunchKernelGGL((k_gemm_dual<EPI2, MM_MFMA32, NW>), grid, dim3(NW * 64), 0, st, a);
+            return;
+        }
+    }
+    if (mm == MM_BF16X3) hipLaunchKernelGGL((k_gemm_dual<EPI2, MM_BF16X3, NW>), grid, dim3(NW * 64), 0, st, a);
+    else hipLaunchKernelGGL((k_gemm_dual<EPI2, MM_BF16, NW>), grid, dim3(NW * 64), 0, st, a);
 }
 
-DualArgs da(const float* A, const float* A2, long lda, const float* B, long ldb, const float* bias,
+DualArgs da(const float* A, const float* A2, long lda, const WMat& B, long ldb, const float* bias,
             const float* C, const float* C2, float* Y, float* Y2, float* Y3, long ldy,
             long P, int M, int K, float beta) {
     DualArgs g;
-    g.A = A; g.A2 = A2; g.lda = lda; g.B = B; g.ldb = ldb; g.bias = bias; g.C = C; g.C2 = C2;
+    g.A = A; g.A2 = A2; g.lda = lda; g.B = B.f; g.ldb = ldb; g.Bx = B.x; g.bias = bias; g.C = C; g.C2 = C2;
     g.Y = Y; g.Y2 = Y2; g.Y3 = Y3; g.ldy = ldy; g.P = P; g.M = M; g.K = K; g.beta = beta;
     return g;
 }
 
-GemmArgs ga(const float* A, long lda, const float* B, long ldb, const float* bias,
+GemmArgs ga(const float* A, long lda, const WMat& B, long ldb, const float* bias,
             float* Y, long ldy, long P, int M, int K, float beta, const float* C = nullptr,
             long ldc = 0, float* Y2 = nullptr) {
     GemmArgs g = {};
-    g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.bias = bias; g.C = C; g.ldc = ldc;
+    g.A = A; g.lda = lda; g.B = B.f; g.ldb = ldb; g.Bx = B.x; g.bias = bias; g.C = C; g.ldc = ldc;
     g.Y = Y; g.ldy = ldy; g.Y2 = Y2; g.P = P; g.M = M; g.K = K; g.beta = beta;
     return g;
 }
@@ -1458,8 +1951,8 @@ void wgrad(const float* A, long lda, int M, const float* B, const float* B2, lon
             if (bpart) hipLaunchKernelGGL((k_gemm_wg<PRO, true, MM_BF16, ST>), grid, dim3(256), 0, st, g);
             else hipLaunchKernelGGL((k_gemm_wg<PRO, false, MM_BF16, ST>), grid, dim3(256), 0, st, g);
         } else {
-            if (bpart) hipLaunchKernelGGL((k_gemm_wg<PRO, true, MM_FP32, ST>), grid, dim3(256), 0, st, g);
-            else hipLaunchKernelGGL((k_gemm_wg<PRO, false, MM_FP32, ST>), grid, dim3(256), 0, st, g);
+            if (bpart) hipLaunchKernelGGL((k_gemm_wg32<PRO, true, ST>), grid, dim3(256), 0, st, g);
+            else hipLaunchKernelGGL((k_gemm_wg32<PRO, false, ST>), grid, dim3(256), 0, st, g);
         }
     } else if (cx.mm == MM_BF16) {
         if (bpart) hipLaunchKernelGGL((k_gemm_wg<PRO, true, MM_BF16>), grid, dim3(256), 0, st, g);
@@ -1468,8 +1961,8 @@ void wgrad(const float* A, long lda, int M, const float* B, const float* B2, lon
         if (bpart) hipLaunchKernelGGL((k_gemm_wg<PRO, true, MM_BF16X3>), grid, dim3(256), 0, st, g);
         else hipLaunchKernelGGL((k_gemm_wg<PRO, false, MM_BF16X3>), grid, dim3(256), 0, st, g);
     } else {
-        if (bpart) hipLaunchKernelGGL((k_gemm_wg<PRO, true, MM_FP32>), grid, dim3(256), 0, st, g);
-        else hipLaunchKernelGGL((k_gemm_wg<PRO, false, MM_FP32>), grid, dim3(256), 0, st, g);
+        if (bpart) hipLaunchKernelGGL((k_gemm_wg32<PRO, true>), grid, dim3(256), 0, st, g);
+        else hipLaunchKernelGGL((k_gemm_wg32<PRO, false>), grid, dim3(256), 0, st, g);
     }
 }
 
@@ -1490,21 +1983,22 @@ void colsum(const float* X, const float* X2, const float* s, long ldx, long P, i
 
 // --- forward workspace -------------------------------------------------------
 // keep: the layers' (Z, H) go to the caller's reserve instead of the workspace
-size_t fwd_bytes(const Layout& l, long n, bool keep) {
+size_t fwd_bytes(const Layout& l, int prec, long n, bool keep) {
     const long c = n < kChunk ? n : kChunk;
-    return weights_bytes(l) + align256(sizeof(float) * c * l.in0p) +
+    return weights_bytes(l, prec) + align256(sizeof(float) * c * l.in0p) +
            (keep ? 0 : (size_t)l.L * align256(sizeof(float) * c * l.W)) + 2 * align256(sizeof(float) * c * l.W) +
            (keep ? 0 : (size_t)l.HL * align256(sizeof(float) * c * l.HW));   // head Y (else in the reserve)
 }
 
 // --- backward workspace ------------------------------------------------------
-// rows of the top-adjoint GEMM's column partials: one per 128-point tile
-long top_rows(long n) { return (n + 127) / 128; }
+// point rows of the top-adjoint GEMM's column partials: one per point tile
+int top_tile(bool f32, long P, int M) { return f32 ? split_tile(P, M) : 128; }
+long top_rows(long n, int tile) { return (n + tile - 1) / tile; }
 
-size_t bwd_bytes(const Layout& l, long n, bool keep) {
+size_t bwd_bytes(const Layout& l, int prec, long n, bool keep) {
     const long c = n < kChunk ? n : kChunk;
     const long wmax = l.W > l.in0p ? l.W : l.in0p;
-    return weights_bytes(l) + 2 * align256(sizeof(float) * c * l.in0p) +
+    return weights_bytes(l, prec) + 2 * align256(sizeof(float) * c * l.in0p) +
            (keep ? 1 : 3) * (size_t)l.L * align256(sizeof(float) * c * l.W) +  // Hdot (and Z, H)
            4 * align256(sizeof(float) * c * l.W) +                  // Hbar, Hdotbar, Zbar, Zdotbar
            (keep ? 1 : 2) * (size_t)l.HL * align256(sizeof(float) * c * l.HW) +  // head Ybar (and Y)
@@ -1512,7 +2006,7 @@ size_t bwd_bytes(const Layout& l, long n, bool keep) {
            align256(sizeof(float) * 2 * kWgSplits * (size_t)l.W * wmax) +
            align256(sizeof(float) * kWgSplits * (size_t)l.W) +
            align256(sizeof(float) * (size_t)kColBlocks * (l.W > l.HW ? l.W : l.HW)) +
-           align256(sizeof(float) * (size_t)top_rows(c) * l.W);   // output layer column partials
+           align256(sizeof(float) * (size_t)top_rows(c, 64) * l.W);   // output layer column partials
 }
 
 // --- reserve of the training pair, [n][W] per trunk layer: H_i = sp(Z_i) and
@@ -1554,7 +2048,7 @@ int mlp_forward(const rfvr_mlp* net, const float* xyz, long n, float* sdf, float
     }
     const Layout l = layout(net);
     const bool keep = reserve_bytes_ != 0 || reserve != nullptr;
-    if ((rc = check_buffers(ws, ws_bytes, fwd_bytes(l, n, keep), reserve, reserve_bytes_,
+    if ((rc = check_buffers(ws, ws_bytes, fwd_bytes(l, net->precision, n, keep), reserve, reserve_bytes_,
                             keep ? reserve_bytes(l, n) : 0)))
         return rc;
     const Cx cx{st, mm_fwd(net->precision)};
@@ -1562,7 +2056,7 @@ int mlp_forward(const rfvr_mlp* net, const float* xyz, long n, float* sdf, float
     const float beta = net->softplus_beta, half = net->half_size, inv_half = 1.0f / net->half_size;
     const long chunk = n < kChunk ? n : kChunk;
     WsCursor cur{reinterpret_cast<char*>(ws), 0};
-    const Weights w = take_weights(cur, l);
+    const Weights w = take_weights(cur, l, net->precision);
     float* X0 = cur.take<float>((size_t)chunk * l.in0p);
     float* Hw[16];
     for (int i = 0; i < l.L && !keep; ++i) Hw[i] = cur.take<float>((size_t)chunk * l.W);
@@ -1580,7 +2074,7 @@ int mlp_forward(const rfvr_mlp* net, const float* xyz, long n, float* sdf, float
         // the workspace's until the sweep has used them)
         float* H[16];
         for (int i = 0; i < l.L; ++i) H[i] = keep ? reserve_h(reserve, l, n, i) + c0 * l.W : Hw[i];
-        gemm32<PRO_ID, EPI_BIAS_SP>(ga(X0, l.in0p, w.Wp[0], l.in0p, P + l.ob[0], H[0], l.W, m, l.W, l.in0p, beta),
+        gemm_first<EPI_BIAS_SP>(ga(X0, l.in0p, w.Wp[0], l.in0p, P + l.ob[0], H[0], l.W, m, l.W, l.in0p, beta),
                                     cx);
         for (int i = 1; i < l.L; ++i)
             gemm<PRO_ID, EPI_BIAS_SP>(ga(H[i - 1], l.W, w.Wp[i], l.W, P + l.ob[i], H[i], l.W, m, l.W, l.W, beta),
@@ -1688,7 +2182,7 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
     if (flags & ~(uint32_t)RFVR_ACCUMULATE) { set_error("only RFVR_ACCUMULATE is meaningful here"); return RFVR_E_INVALID; }
     const Layout l = layout(net);
     const bool keep = reserve_bytes_ != 0 || reserve != nullptr;
-    if ((rc = check_buffers(ws, ws_bytes, bwd_bytes(l, n, keep), reserve, reserve_bytes_,
+    if ((rc = check_buffers(ws, ws_bytes, bwd_bytes(l, net->precision, n, keep), reserve, reserve_bytes_,
                             keep ? reserve_bytes(l, n) : 0)))
         return rc;
     // cxf: the plain backward's recompute of the forward products, in the
@@ -1715,7 +2209,7 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
     const long chunk = n < kChunk ? n : kChunk;
     const long wmax = l.W > l.in0p ? l.W : l.in0p;
     WsCursor cur{reinterpret_cast<char*>(ws), 0};
-    const Weights w = take_weights(cur, l);
+    const Weights w = take_weights(cur, l, net->precision);
     float* X0 = cur.take<float>((size_t)chunk * l.in0p);
     float* X0d = cur.take<float>((size_t)chunk * l.in0p);
     float *Zw[16], *Hw[16], *Hd[16];
@@ -1733,7 +2227,7 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
     float* part = cur.take<float>((size_t)2 * kWgSplits * l.W * wmax);
     float* bpart = cur.take<float>((size_t)kWgSplits * l.W);
     float* cpart = cur.take<float>((size_t)kColBlocks * (l.W > l.HW ? l.W : l.HW));
-    float* tpart = cur.take<float>((size_t)top_rows(chunk) * l.W);
+    float* tpart = cur.take<float>((size_t)top_rows(chunk, 64) * l.W);
     if ((rc = hip_status(prep_weights(l, P, w, st), "mlp weight prep"))) return rc;
 
     for (long c0 = 0; c0 < n; c0 += chunk) {
@@ -1755,8 +2249,8 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
             // tangent only: Hdot_i = sp'(Z_i) (Hdot_{i-1} W_i^T), sp'(Z_i) from the
             // reserve's H_i
             const GemmArgs a0 = ga(X0d, l.in0p, w.Wp[0], l.in0p, nullptr, Hd[0], l.W, m, l.W, l.in0p, beta, H[0], l.W);
-            if (b16) gemm32<PRO_ID, EPI_DSPMUL, ST_Y>(a0, cx);
-            else gemm32<PRO_ID, EPI_DSPMUL>(a0, cx);
+            if (b16) gemm_first<EPI_DSPMUL, ST_Y>(a0, cx);
+            else gemm_first<EPI_DSPMUL>(a0, cx);
             for (int i = 1; i < l.L; ++i) {
                 const GemmArgs a = ga(Hd[i - 1], l.W, w.Wp[i], l.W, nullptr, Hd[i], l.W, m, l.W, l.W, beta, H[i], l.W);
                 if (b16) gemm_b16<PRO_ID, EPI_DSPMUL, ST_A | ST_Y>(a, cx);
@@ -1765,7 +2259,7 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
         } else {
             // one dual GEMM per layer: (Z_i, H_i) and Hdot_i share W_i
             gemm_dual<EPI2_FWD>(da(X0, X0d, l.in0p, w.Wp[0], l.in0p, P + l.ob[0], nullptr, nullptr, Z[0], H[0], Hd[0],
-                                   l.W, m, l.W, l.in0p, beta), MM_FP32, st);
+                                   l.W, m, l.W, l.in0p, beta), w.Wp[0].f ? MM_MFMA32 : MM_FP32, st);
             for (int i = 1; i < l.L; ++i)
                 gemm_dual<EPI2_FWD>(da(H[i - 1], Hd[i - 1], l.W, w.Wp[i], l.W, P + l.ob[i], nullptr, nullptr, Z[i],
                                        H[i], Hd[i], l.W, m, l.W, l.W, beta), cxf.mm, st);
@@ -1818,7 +2312,8 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
             else gemm<PRO_ID, EPI_TOPADJ>(a, cx);
         }
         // sdf output layer: w_out_bar from the partials, b_out_bar = half sum g_f
-        hipLaunchKernelGGL(k_colsum_final, dim3(l.W), dim3(256), 0, st, tpart, (int)top_rows(m), l.W, 1.0f,
+        hipLaunchKernelGGL(k_colsum_final, dim3(l.W), dim3(256), 0, st, tpart,
+                           (int)top_rows(m, top_tile(cx.mm == MM_FP32, m, l.W)), l.W, 1.0f,
                            GP + l.o_wout, acc);
         if (gf) colsum(gf, nullptr, nullptr, 1, m, 1, 0, beta, half, cpart, GP + l.o_bout, acc, st);
         else if (!acc) hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, st, GP + l.o_bout, 1L, 0.0f);
@@ -1896,12 +2391,12 @@ int64_t rfvr_mlp_param_count(const rfvr_mlp* net) {
 
 size_t rfvr_mlp_forward_ws_bytes(const rfvr_mlp* net, int64_t n) {
     if (check_net(net) || n < 1 || n > RFVR_MAX_POINTS) return 0;
-    return fwd_bytes(layout(net), (long)n, false);
+    return fwd_bytes(layout(net), net->precision, (long)n, false);
 }
 
 size_t rfvr_mlp_backward_ws_bytes(const rfvr_mlp* net, int64_t n) {
     if (check_net(net) || n < 1 || n > RFVR_MAX_POINTS) return 0;
-    return bwd_bytes(layout(net), (long)n, false);
+    return bwd_bytes(layout(net), net->precision, (long)n, false);
 }
 
 int rfvr_mlp_forward(const rfvr_mlp* net, const float* xyz, int64_t n, float* sdf, float* grad,
@@ -1924,12 +2419,12 @@ size_t rfvr_mlp_reserve_bytes(const rfvr_mlp* net, int64_t n) {
 
 size_t rfvr_mlp_forward_train_ws_bytes(const rfvr_mlp* net, int64_t n) {
     if (check_net(net) || n < 1 || n > RFVR_MAX_POINTS) return 0;
-    return fwd_bytes(layout(net), (long)n, true);
+    return fwd_bytes(layout(net), net->precision, (long)n, true);
 }
 
 size_t rfvr_mlp_backward_train_ws_bytes(const rfvr_mlp* net, int64_t n) {
     if (check_net(net) || n < 1 || n > RFVR_MAX_POINTS) return 0;
-    return bwd_bytes(layout(net), (long)n, true);
+    return bwd_bytes(layout(net), net->precision, (long)n, true);
 }
 
 int rfvr_mlp_forward_train(const rfvr_mlp* net, const float* xyz, int64_t n, float* sdf, float* grad,
@@ -1991,7 +2486,10 @@ PLayout playout(const rfvr_proposal* n) {
 
 size_t pweights_bytes(const PLayout& l) {
     size_t b = 0;
-    for (int i = 0; i < l.layers; ++i) b += 2 * align256(sizeof(float) * (i == 0 ? l.in0p : l.W) * l.W);
+    for (int i = 0; i < l.layers; ++i) {
+        const int finp = i == 0 ? l.in0p : l.W;
+        b += wmat_bytes(l.W, finp, true) + wmat_bytes(finp, l.W, true);
+    }
     return b;
 }
 
@@ -2056,10 +2554,11 @@ static int proposal_pass(const rfvr_proposal* net, const float* xyz, int64_t n, 
     const float* P = net->params;
     const long chunk = n < kChunk ? (long)n : kChunk;
     WsCursor cur{reinterpret_cast<char*>(ws), 0};
-    float *Wp[4], *WT[4];
+    WMat Wp[4], WT[4];
     for (int i = 0; i < l.layers; ++i) {
-        Wp[i] = cur.take<float>((size_t)(i == 0 ? l.in0p : l.W) * l.W);
-        WT[i] = cur.take<float>((size_t)(i == 0 ? l.in0p : l.W) * l.W);
+        const int finp = i == 0 ? l.in0p : l.W;
+        Wp[i] = take_wmat(cur, l.W, finp, true);
+        WT[i] = take_wmat(cur, finp, l.W, true);
     }
     float* X0 = cur.take<float>((size_t)chunk * l.in0p);
     float* A[4];
@@ -2072,13 +2571,13 @@ static int proposal_pass(const rfvr_proposal* net, const float* xyz, int64_t n, 
         bpart = cur.take<float>((size_t)kWgSplits * l.W);
         cpart = cur.take<float>((size_t)kColBlocks * l.W);
     }
+    PrepList prep;
     for (int i = 0; i < l.layers; ++i) {
         const int fin = i == 0 ? l.in0 : l.W, finp = i == 0 ? l.in0p : l.W;
-        hipLaunchKernelGGL(k_pad_cols, dim3(blocks((long)l.W * finp)), dim3(256), 0, st, P + l.oW[i], l.W,
-                           fin, finp, Wp[i]);
-        hipLaunchKernelGGL(k_transpose_pad, dim3(blocks((long)l.W * finp)), dim3(256), 0, st, P + l.oW[i],
-                           l.W, fin, l.W, finp, WT[i]);
+        prep.add(P + l.oW[i], Wp[i], l.W, fin, l.W, finp, 0);
+        if (bwd && i > 0) prep.add(P + l.oW[i], WT[i], l.W, fin, finp, l.W, 1);
     }
+    if ((rc = hip_status(prep.launch(st), "proposal weight prep"))) return rc;
     const float beta = 1.0f, inv_half = 1.0f / net->half_size;
     for (long c0 = 0; c0 < n; c0 += chunk) {
         const long m = (n - c0) < chunk ? (n - c0) : chunk;
