@@ -113,7 +113,7 @@ static int check_bistatic_weight(const RenderGeom& g) {
 
 // transmitter records, and receiver records of a bistatic aperture (g.rxa set
 // to them); fl: the fields whose phi_tx / phi_rx shift the transmittance, or
-// NULL when the shift is off
+// NULL when the shift is off.  For the moment kernels the plan writes them.
 static int build_ant_records(const rfvr_aperture* ap, const rfvr_fields* fl, AntRec* ant, AntRec* rxa,
                              RenderGeom& g, hipStream_t st) {
     int rc;
@@ -161,6 +161,14 @@ struct ChebWs {
     MeasCheb* meas;
 };
 
+static int build_plan(const rfvr_aperture* ap, const rfvr_fields* fl, const float* xyz, long n, AntRec* ant, AntRec* rxa,
+                      RenderGeom& g, const ChebWs& cw, hipStream_t st) {
+    g.rxa = rxa;
+    return hip_status(launch_cheb_plan(xyz, n, ap->tx, fl ? fl->phi_tx : nullptr, ap->rx, fl ? fl->phi_rx : nullptr, ant,
+                                       rxa, ap->n_meas, g.Kd, ap->n_freq, cw.bbox, cw.meas, cw.plan, st),
+                      "term plan");
+}
+
 static ChebWs take_cheb(WsCursor& cur, long n_pts, int n_meas) {
     ChebWs c;
     c.bbox = cur.take<float>((size_t)6 * cheb_bbox_blocks(n_pts));
@@ -184,8 +192,12 @@ static size_t ant_bytes(int n_meas, bool bi) { return (bi ? 2 : 1) * align256(si
 static size_t ws_render_forward(const RenderGeom& g) {
     const int ns = render_splits(g);
     return ant_bytes(g.n_meas, g.bi) + align256(sizeof(PtRec) * g.n_pts) +
-           align256(sizeof(float2) * partial_count(g.n_pts, g.n_meas, g.n_freq, ns)) +
-           align256(sizeof(float2) * (size_t)g.n_meas * kChebMaxOrder) + ws_cheb(g.n_pts, g.n_meas);
+           align256(sizeof(float2) * partial_count(g.n_pts, g.n_meas, g.n_freq, ns)) + ws_cheb(g.n_pts, g.n_meas);
+}
+
+static size_t bwd_part_bytes(long n_pts, int n_meas) {
+    const int ns = cheb_meas_splits(n_pts, n_meas);
+    return ns > 1 ? align256(sizeof(float) * 5 * ns * (size_t)n_pts) : 0;
 }
 
 static size_t ws_render_backward(const RenderGeom& g) {
@@ -196,15 +208,25 @@ static size_t ws_render_backward(const RenderGeom& g) {
            align256(sizeof(float) * g.n_pts) +                   // g_alpha
            align256(sizeof(float2) * g.n_meas * np) +            // padded g_signal
            2 * align256(sizeof(float) * g.n_ray) +               // per-ray partials
+           bwd_part_bytes(g.n_pts, g.n_meas) +                   // sums of the measurement splits
            align256(sizeof(float2) * (size_t)g.n_meas * kChebMaxOrder) + ws_cheb(g.n_pts, g.n_meas);
 }
 
+// what the filter forward cannot do without; its query adds the sums of the
+// measurement splits, of which a call takes as many as its workspace holds
 static size_t ws_mf_forward(const rfvr_aperture* ap, long n_q, int two) {
     const size_t np = padded_freq(ap->n_freq);
     return ant_bytes(ap->n_meas, ap->rx != nullptr) +
            (two ? 2 : 1) * (align256(sizeof(float2) * ap->n_meas * np) +
                             align256(sizeof(float2) * (size_t)ap->n_meas * kChebMaxOrder)) +
            ws_cheb(n_q, ap->n_meas);
+}
+
+static size_t mf_part_bytes(long n_q, int two) { return align256(sizeof(float2) * (two ? 2 : 1) * (size_t)n_q); }
+
+static size_t ws_mf_forward_full(const rfvr_aperture* ap, long n_q, int two) {
+    const int ns = cheb_meas_splits(n_q, ap->n_meas);
+    return ws_mf_forward(ap, n_q, two) + (ns > 1 ? ns * mf_part_bytes(n_q, two) : 0);
 }
 
 static int mf_splits(const rfvr_aperture* ap, long n_q) {
@@ -215,8 +237,7 @@ static int mf_splits(const rfvr_aperture* ap, long n_q) {
 static size_t ws_mf_backward(const rfvr_aperture* ap, long n_q) {
     const int ns = mf_splits(ap, n_q);
     return ant_bytes(ap->n_meas, ap->rx != nullptr) + align256(sizeof(QRec) * n_q) +
-           align256(sizeof(float2) * partial_count(n_q, ap->n_meas, ap->n_freq, ns)) +
-           align256(sizeof(float2) * (size_t)ap->n_meas * kChebMaxOrder) + ws_cheb(n_q, ap->n_meas);
+           align256(sizeof(float2) * partial_count(n_q, ap->n_meas, ap->n_freq, ns)) + ws_cheb(n_q, ap->n_meas);
 }
 
 static int loss_blocks(long n) {
@@ -302,23 +323,22 @@ int rfvr_render_forward(const rfvr_aperture* ap, const rfvr_samples* sm, const r
     PtRec* rec = cur.take<PtRec>(g.n_pts);
     const int ns = render_splits(g);
     float2* partial = cur.take<float2>(partial_count(g.n_pts, g.n_meas, g.n_freq, ns));
-    float2* M = cur.take<float2>((size_t)g.n_meas * kChebMaxOrder);
     const ChebWs cw = take_cheb(cur, g.n_pts, g.n_meas);
     const int use_phi = (fl->phi_ray && fl->phi_tx) ? 1 : 0;
-    if ((rc = build_ant_records(ap, use_phi ? fl : nullptr, ant, rxa, g, st))) return rc;
+    const bool cheb = use_cheb(flags);
+    if ((rc = cheb ? build_plan(ap, use_phi ? fl : nullptr, sm->xyz, g.n_pts, ant, rxa, g, cw, st)
+                   : build_ant_records(ap, use_phi ? fl : nullptr, ant, rxa, g, st)))
+        return rc;
     if ((rc = hip_status(launch_render_prep(g, sm->xyz, sm->ray_weight, sm->point_weight, fl->sdf, fl->grad, fl->refl,
                                             fl->phi_ray, use_phi, fl->s, fl->log_s_ptr, fl->amp_tx, fl->amp_ptr, rec,
                                             alpha_out, trans_out, st),
                          "render prep")))
         return rc;
     const ChebPlan* sel = nullptr;
-    if (use_cheb(flags)) {
-        if ((rc = hip_status(launch_cheb_plan(sm->xyz, g.n_pts, ant, g.rxa, g.n_meas, g.Kd, g.n_freq, cw.bbox, cw.meas,
-                                              cw.plan, st), "term plan")))
-            return rc;
+    if (cheb) {
         sel = cw.plan;
         if ((rc = hip_status(launch_cheb_points(g, 0, flags, ant, cw.meas, cw.plan, rec,
-                                                cheb_point_splits(g.n_pts, g.n_meas), partial, M,
+                                                cheb_point_splits(g.n_pts, g.n_meas), partial,
                                                 reinterpret_cast<float2*>(signal), 0, st),
                              "render moment kernels")))
             return rc;
@@ -366,33 +386,36 @@ int rfvr_render_backward(const rfvr_aperture* ap, const rfvr_samples* sm, const 
     float2* gpad = cur.take<float2>((size_t)g.n_meas * np);
     float* pamp = cur.take<float>(g.n_ray);
     float* ps = cur.take<float>(g.n_ray);
+    const int ns = cheb_meas_splits(g.n_pts, g.n_meas);
+    float* part = ns > 1 ? cur.take<float>(5 * ns * (size_t)g.n_pts) : nullptr;
     float2* B = cur.take<float2>((size_t)g.n_meas * kChebMaxOrder);
     const ChebWs cw = take_cheb(cur, g.n_pts, g.n_meas);
     const int use_phi = (fl->phi_ray && fl->phi_tx) ? 1 : 0;
-    if ((rc = build_ant_records(ap, use_phi ? fl : nullptr, ant, rxa, g, st))) return rc;
+    const bool cheb = use_cheb(flags);
+    if ((rc = cheb ? build_plan(ap, use_phi ? fl : nullptr, sm->xyz, g.n_pts, ant, rxa, g, cw, st)
+                   : build_ant_records(ap, use_phi ? fl : nullptr, ant, rxa, g, st)))
+        return rc;
     if ((rc = hip_status(launch_render_prep(g, sm->xyz, sm->ray_weight, nullptr, fl->sdf, fl->grad, fl->refl,
                                             fl->phi_ray, use_phi, fl->s, fl->log_s_ptr, fl->amp_tx, fl->amp_ptr, rec,
                                             alpha, trans, st),
                          "render prep")))
         return rc;
-    if ((rc = hip_status(launch_pad_signal(reinterpret_cast<const float2*>(g_signal), g.n_meas,
-                                           g.n_freq, np, gpad, st),
-                         "pad g_signal")))
-        return rc;
+    const float2* gsig = reinterpret_cast<const float2*>(g_signal);
+    if (np != g.n_freq) {
+        if ((rc = hip_status(launch_pad_signal(gsig, g.n_meas, g.n_freq, np, gpad, st), "pad g_signal"))) return rc;
+        gsig = gpad;
+    }
     const ChebPlan* sel = nullptr;
-    if (use_cheb(flags)) {
-        if ((rc = hip_status(launch_cheb_plan(sm->xyz, g.n_pts, ant, g.rxa, g.n_meas, g.Kd, g.n_freq, cw.bbox, cw.meas,
-                                              cw.plan, st), "term plan")))
-            return rc;
+    if (cheb) {
         sel = cw.plan;
         if ((rc = hip_status(launch_cheb_coef(g, cw.plan, cw.meas, reinterpret_cast<const float2*>(g_signal), B,
                                               st), "render adjoint coefficients")))
             return rc;
-        if ((rc = hip_status(launch_cheb_render_bwd(g, flags, cw.plan, ant, cw.meas, rec, B, gb, gT, gn, st),
+        if ((rc = hip_status(launch_cheb_render_bwd(g, flags, cw.plan, ant, cw.meas, rec, B, gb, gT, gn, ns, part, st),
                              "render adjoint series kernels")))
             return rc;
     }
-    if ((rc = hip_status(launch_render_bwd_points(g, ant, rec, gpad, np, flags, gb, gT, gn, sel, st),
+    if ((rc = hip_status(launch_render_bwd_points(g, ant, rec, gsig, np, flags, gb, gT, gn, sel, st),
                          "render adjoint term kernel")))
         return rc;
     if ((rc = hip_status(launch_scan_adjoint(g, sm->ray_weight, fl->sdf, fl->grad, fl->refl, fl->s,
@@ -401,17 +424,14 @@ int rfvr_render_backward(const rfvr_aperture* ap, const rfvr_samples* sm, const 
                                              g_sdf, g_grad, g_refl, acc, st),
                          "scan adjoint")))
         return rc;
-    if (g_amp && (rc = hip_status(launch_sum_scalars(pamp, g.n_ray, g_amp, acc, st), "sum g_amp")))
-        return rc;
-    if (g_s && (rc = hip_status(launch_sum_scalars(ps, g.n_ray, g_s, acc, st), "sum g_s")))
-        return rc;
-    return RFVR_OK;
+    if (!g_amp && !g_s) return RFVR_OK;
+    return hip_status(launch_sum_scalars(pamp, g_amp, ps, g_s, g.n_ray, acc, st), "sum g_amp, g_s");
 }
 
 // ---------------------------------------------------------------- matched filter
 size_t rfvr_mf_forward_ws_bytes(const rfvr_aperture* ap, int64_t n_q, int two_signals) {
     if (check_aperture(ap) || !count_ok(n_q)) return 0;
-    return ws_mf_forward(ap, (long)n_q, two_signals);
+    return ws_mf_forward_full(ap, (long)n_q, two_signals);
 }
 
 int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, uint32_t flags,
@@ -438,19 +458,24 @@ int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, ui
     float2* B = cur.take<float2>((size_t)ap->n_meas * kChebMaxOrder);
     float2* B2 = two ? cur.take<float2>((size_t)ap->n_meas * kChebMaxOrder) : nullptr;
     const ChebWs cw = take_cheb(cur, (long)n_q, ap->n_meas);
-    if ((rc = build_ant_records(ap, nullptr, ant, rxa, g, st))) return rc;
-    if ((rc = hip_status(launch_pad_signal(reinterpret_cast<const float2*>(signal), ap->n_meas,
-                                           ap->n_freq, np, sp, st), "pad signal")))
+    const bool cheb = use_cheb(flags);
+    if ((rc = cheb ? build_plan(ap, nullptr, xyz_q, (long)n_q, ant, rxa, g, cw, st)
+                   : build_ant_records(ap, nullptr, ant, rxa, g, st)))
         return rc;
-    if (two && (rc = hip_status(launch_pad_signal(reinterpret_cast<const float2*>(signal2),
-                                                  ap->n_meas, ap->n_freq, np, sp2, st), "pad signal2")))
-        return rc;
+    const float2 *ps = reinterpret_cast<const float2*>(signal), *ps2 = reinterpret_cast<const float2*>(signal2);
+    if (np != ap->n_freq) {
+        if ((rc = hip_status(launch_pad_signal(ps, ap->n_meas, ap->n_freq, np, sp, st), "pad signal"))) return rc;
+        if (two && (rc = hip_status(launch_pad_signal(ps2, ap->n_meas, ap->n_freq, np, sp2, st), "pad signal2"))) return rc;
+        ps = sp;
+        ps2 = sp2;
+    }
     const ChebPlan* sel = nullptr;
-    if (use_cheb(flags)) {
-        if ((rc = hip_status(launch_cheb_plan(xyz_q, (long)n_q, ant, g.rxa, ap->n_meas, g.Kd, ap->n_freq, cw.bbox,
-                                              cw.meas, cw.plan, st), "term plan")))
-            return rc;
+    if (cheb) {
         sel = cw.plan;
+        // measurement splits: as many as the workspace has room for
+        int ns = cheb_meas_splits((long)n_q, ap->n_meas);
+        const size_t room = (ws_bytes - cur.used) / mf_part_bytes((long)n_q, two);
+        if (room < (size_t)ns) ns = room < 1 ? 1 : (int)room;
         if ((rc = hip_status(launch_cheb_coef(g, cw.plan, cw.meas, reinterpret_cast<const float2*>(signal), B, st),
                              "mf coefficients")))
             return rc;
@@ -459,10 +484,11 @@ int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, ui
             return rc;
         if ((rc = hip_status(launch_cheb_mf(g, cw.plan, (long)n_q, xyz_q, ant, cw.meas, B, B2,
                                             reinterpret_cast<float2*>(z), power, reinterpret_cast<float2*>(z2),
-                                            power2, st), "mf series kernels")))
+                                            power2, ns, reinterpret_cast<float2*>(cur.base + cur.used), st),
+                             "mf series kernels")))
             return rc;
     }
-    return hip_status(launch_mf_forward(g, ant, xyz_q, (long)n_q, sp, sp2, np, flags,
+    return hip_status(launch_mf_forward(g, ant, xyz_q, (long)n_q, ps, ps2, np, flags,
                                         reinterpret_cast<float2*>(z), power,
                                         reinterpret_cast<float2*>(z2), power2, sel, st),
                       "mf forward");
@@ -512,21 +538,20 @@ int rfvr_mf_backward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, c
     AntRec* rxa = g.bi ? cur.take<AntRec>(ap->n_meas) : nullptr;
     QRec* rec = cur.take<QRec>((size_t)n_q);
     float2* partial = cur.take<float2>(partial_count((long)n_q, ap->n_meas, ap->n_freq, ns));
-    float2* M = cur.take<float2>((size_t)ap->n_meas * kChebMaxOrder);
     const ChebWs cw = take_cheb(cur, (long)n_q, ap->n_meas);
     const int acc = (flags & RFVR_ACCUMULATE) ? 1 : 0;
-    if ((rc = build_ant_records(ap, nullptr, ant, rxa, g, st))) return rc;
+    const bool cheb = use_cheb(flags);
+    if ((rc = cheb ? build_plan(ap, nullptr, xyz_q, (long)n_q, ant, rxa, g, cw, st)
+                   : build_ant_records(ap, nullptr, ant, rxa, g, st)))
+        return rc;
     if ((rc = hip_status(launch_mf_bwd_records(xyz_q, (long)n_q, reinterpret_cast<const float2*>(z),
                                                power, g_power, rec, st), "mf adjoint records")))
         return rc;
     const ChebPlan* sel = nullptr;
-    if (use_cheb(flags)) {
-        if ((rc = hip_status(launch_cheb_plan(xyz_q, (long)n_q, ant, g.rxa, ap->n_meas, g.Kd, ap->n_freq, cw.bbox,
-                                              cw.meas, cw.plan, st), "term plan")))
-            return rc;
+    if (cheb) {
         sel = cw.plan;
         if ((rc = hip_status(launch_cheb_points(g, 1, flags, ant, cw.meas, cw.plan, rec,
-                                                cheb_point_splits((long)n_q, ap->n_meas), partial, M,
+                                                cheb_point_splits((long)n_q, ap->n_meas), partial,
                                                 reinterpret_cast<float2*>(g_signal), acc, st),
                              "mf adjoint moment kernels")))
             return rc;
@@ -558,10 +583,7 @@ int rfvr_term_order(const rfvr_aperture* ap, const float* xyz, int64_t n_pts, in
     AntRec* ant = cur.take<AntRec>(ap->n_meas);
     AntRec* rxa = g.bi ? cur.take<AntRec>(ap->n_meas) : nullptr;
     const ChebWs cw = take_cheb(cur, (long)n_pts, ap->n_meas);
-    if ((rc = build_ant_records(ap, nullptr, ant, rxa, g, st))) return rc;
-    if ((rc = hip_status(launch_cheb_plan(xyz, (long)n_pts, ant, g.rxa, ap->n_meas, g.Kd, ap->n_freq, cw.bbox, cw.meas,
-                                          cw.plan, st), "term plan")))
-        return rc;
+    if ((rc = build_plan(ap, nullptr, xyz, (long)n_pts, ant, rxa, g, cw, st))) return rc;
     return hip_status(launch_cheb_order(cw.plan, order, st), "term order");
 }
 

@@ -39,9 +39,9 @@
 // Per pair both cost 3 FP32 operations per order (recurrence of T_k and a
 // complex multiply-add by a real), against 4 per frequency in the
 // per-frequency kernels; the FP64 range and the one phasor exp(-+j 2 pi Kc r)
-// (hardware sin / cos of the FP64-reduced phase, at Kc) are set up once per pair.  Bessel values come from Miller's backward
-// recurrence in FP64 (first pass: normalisation J_0 + 2 sum J_2m = 1 and the
-// number of rescalings; second pass: the values, consumed as produced).
+// (hardware sin / cos of the FP64-reduced phase, at Kc) are set up once per pair.
+// The Bessel coefficients themselves are not formed: interpolation at a few
+// Chebyshev nodes more than orders gives the same series (k_cheb_coef, k_cheb_out).
 #include <cmath>
 #include <type_traits>
 
@@ -94,51 +94,74 @@ __global__ __launch_bounds__(256) void k_bbox_partial(const float* __restrict__ 
     if (t < 6) part[(long)blockIdx.x * 6 + t] = s[t][0];
 }
 
+// log K! of the candidate orders
+constexpr int kChebNK = (int)(sizeof(kChebKs) / sizeof(kChebKs[0]));
+__device__ constexpr double kChebLogFact[] = {54.784729398112319, 67.889743137181540, 81.557959456115037,
+                                              110.32063971475740, 140.67392364823426, 205.16819948264120};
+static_assert(sizeof(kChebLogFact) / sizeof(double) == kChebNK, "one per order");
+
 // log of 2 (z/2)^K / K! / (1 - z/(2K+2)), the truncation bound; +inf when the
 // geometric tail does not converge
-__device__ double cheb_log_bound(int K, double z) {
+__device__ double cheb_log_bound(int K, double log_fact, double z) {
     const double q = 0.5 * z;
     if (q <= 0.0) return -INFINITY;
     if (q >= (double)(K + 1)) return INFINITY;
-    double lf = 0.0;
-    for (int m = 2; m <= K; ++m) lf += log((double)m);
-    return (double)K * log(q) - lf + log(2.0) - log1p(-q / (double)(K + 1));
+    return (double)K * log(q) - log_fact + log(2.0) - log1p(-q / (double)(K + 1));
 }
 
-__global__ __launch_bounds__(256) void k_cheb_plan(const float* __restrict__ part, int nb,
-                                                   const AntRec* __restrict__ ant,
-                                                   const AntRec* __restrict__ rxa, int n_meas, double Kd,
-                                                   int n_freq, MeasCheb* __restrict__ meas,
-                                                   ChebPlan* __restrict__ plan) {
-    __shared__ float sb[6][256];
-    __shared__ double sz[256];
-    const int t = threadIdx.x;
-    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int b = t; b < nb; b += 256) {
+// min (or max) over a wave, then over the work-group's waves through sh
+template <bool MAX, class T>
+__device__ __forceinline__ T block_extreme(T v, T* sh, int waves) {
+    auto pick = [](T a, T b) { return MAX ? (a > b ? a : b) : (a < b ? a : b); };
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            lo[c] = fminf(lo[c], part[6 * b + c]);
-            hi[c] = fmaxf(hi[c], part[6 * b + 3 + c]);
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        sb[c][t] = lo[c];
-        sb[3 + c][t] = hi[c];
-    }
+    for (int o = 32; o >= 1; o >>= 1) v = pick(v, __shfl_xor(v, o, 64));
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if (t < w) {
+    for (int w = 0; w < waves; ++w) v = pick(v, sh[w]);
+    __syncthreads();
+    return v;
+}
+
+// The launch's plan, one work-group: the measurement records (transmitters, and
+// receivers of a bistatic aperture), the bounding box of the points (from the
+// partials of k_bbox_partial, or for nb = 0 from the few points themselves), each
+// measurement's range interval, and the order.
+constexpr int kPlanThreads = 1024;
+__global__ __launch_bounds__(kPlanThreads) void k_cheb_plan(const float* __restrict__ xyz, long n,
+                                                            const float* __restrict__ part, int nb,
+                                                            const float* __restrict__ tx, const float* __restrict__ phi_tx,
+                                                            const float* __restrict__ rx, const float* __restrict__ phi_rx,
+                                                            AntRec* __restrict__ ant, AntRec* __restrict__ rxa,
+                                                            int n_meas, double Kd, int n_freq,
+                                                            MeasCheb* __restrict__ meas, ChebPlan* __restrict__ plan) {
+    __shared__ float sf[kPlanThreads / 64];
+    __shared__ double sz[kPlanThreads / 64];
+    const int t = threadIdx.x, waves = kPlanThreads / 64;
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    if (nb == 0) {
+        for (long j = t; j < n; j += kPlanThreads) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                sb[c][t] = fminf(sb[c][t], sb[c][t + w]);
-                sb[3 + c][t] = fmaxf(sb[3 + c][t], sb[3 + c][t + w]);
+                const float v = xyz[3 * j + c];
+                lo[c] = fminf(lo[c], v);
+                hi[c] = fmaxf(hi[c], v);
             }
         }
-        __syncthreads();
+    } else {
+        for (int b = t; b < nb; b += kPlanThreads) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                lo[c] = fminf(lo[c], part[6 * b + c]);
+                hi[c] = fmaxf(hi[c], part[6 * b + 3 + c]);
+            }
+        }
     }
-    const double bl[3] = {(double)sb[0][0], (double)sb[1][0], (double)sb[2][0]};
-    const double bh[3] = {(double)sb[3][0], (double)sb[4][0], (double)sb[5][0]};
+    double bl[3], bh[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        bl[c] = (double)block_extreme<false>(lo[c], sf, waves);
+        bh[c] = (double)block_extreme<true>(hi[c], sf, waves);
+    }
     const bool finite = isfinite(bl[0]) && isfinite(bl[1]) && isfinite(bl[2]) && isfinite(bh[0]) &&
                         isfinite(bh[1]) && isfinite(bh[2]);
     // distances from an antenna to the box: nearest face, farthest corner
@@ -155,13 +178,26 @@ __global__ __launch_bounds__(256) void k_cheb_plan(const float* __restrict__ par
         lo_ = sqrt(n2);
         hi_ = sqrt(f2);
     };
+    auto record = [](const float* x, const float* phi, int i) {
+        AntRec a;
+        a.x = (double)x[3 * i];
+        a.y = (double)x[3 * i + 1];
+        a.z = (double)x[3 * i + 2];
+        a.phi = phi ? phi[i] : 0.0f;
+        a.pad = 0.0f;
+        return a;
+    };
     double zl = 0.0;
-    for (int i = t; i < n_meas; i += 256) {
+    for (int i = t; i < n_meas; i += kPlanThreads) {
         double rlo, rhi;
-        band(ant[i], rlo, rhi);
+        const AntRec a = record(tx, phi_tx, i);
+        ant[i] = a;
+        band(a, rlo, rhi);
         if (rxa) {
             double lo2, hi2;
-            band(rxa[i], lo2, hi2);
+            const AntRec r = record(rx, phi_rx, i);
+            rxa[i] = r;
+            band(r, lo2, hi2);
             rlo = 0.5 * (rlo + lo2);
             rhi = 0.5 * (rhi + hi2);
         }
@@ -174,83 +210,19 @@ __global__ __launch_bounds__(256) void k_cheb_plan(const float* __restrict__ par
         meas[i] = m;
         zl = fmax(zl, 6.283185307179586 * (0.5 * (double)(n_freq - 1)) * Kd * m.h);
     }
-    sz[t] = zl;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if (t < w) sz[t] = fmax(sz[t], sz[t + w]);
-        __syncthreads();
-    }
-    if (t == 0) {
-        const double zmax = sz[0];
-        int K = 0;
-        if (finite) {
-            for (int c = 0; c < (int)(sizeof(kChebKs) / sizeof(kChebKs[0])); ++c) {
-                const int k = kChebKs[c];
-                if (k >= n_freq) break;
-                if (cheb_log_bound(k, zmax) <= log(kChebTol)) { K = k; break; }
-            }
+    const double zmax = block_extreme<true>(zl, sz, waves);
+    // one lane per candidate order, the smallest that qualifies
+    if (t < 64) {
+        const int c = t < kChebNK ? t : kChebNK - 1, k = kChebKs[c];
+        const bool ok = t < kChebNK && finite && k < n_freq && cheb_log_bound(k, kChebLogFact[c], zmax) <= log(kChebTol);
+        const unsigned long long m = __ballot(ok);
+        if (t == 0) {
+            ChebPlan p;
+            p.K = m ? kChebKs[__ffsll(m) - 1] : 0;
+            p.pad = 0;
+            p.zmax = zmax;
+            *plan = p;
         }
-        ChebPlan p;
-        p.K = K;
-        p.pad = 0;
-        p.zmax = zmax;
-        *plan = p;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Bessel values J_k(z), k < nk, by Miller's backward recurrence (FP64).
-// visit(k, J_k) is called for k = nk-1 down to 0.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ int miller_start(int nk, double z) {
-    const int a = nk > (int)z + 1 ? nk : (int)z + 1;
-    return 2 * ((a + 20 + (int)(3.0 * cbrt(z + 1.0)) + (int)sqrt(40.0 * a)) / 2);
-}
-
-template <class Visit>
-__device__ __forceinline__ void bessel_j_desc_pos(double z, int nk, Visit visit) {
-    if (!(z > 1e-300)) {
-        for (int k = nk - 1; k >= 1; --k) visit(k, 0.0);
-        visit(0, 1.0);
-        return;
-    }
-    const int m0 = miller_start(nk, z);
-    const double iz2 = 2.0 / z;
-    double jp = 0.0, jc = 1e-200, norm = 0.0;
-    int stot = 0;
-    for (int m = m0; m >= 1; --m) {
-        const double jm = (double)m * iz2 * jc - jp;
-        jp = jc;
-        jc = jm;
-        const int k = m - 1;
-        if (k > 0 && (k & 1) == 0) norm += 2.0 * jc;
-        if (fabs(jc) > 1e200) { jp *= 1e-200; jc *= 1e-200; norm *= 1e-200; ++stot; }
-    }
-    norm += jc;
-    const double inv = 1.0 / norm;
-    jp = 0.0;
-    jc = 1e-200;
-    int s = 0;
-    for (int m = m0; m >= 1; --m) {
-        const double jm = (double)m * iz2 * jc - jp;
-        jp = jc;
-        jc = jm;
-        const int k = m - 1;
-        if (k < nk) {
-            const int d = stot - s;
-            visit(k, d == 0 ? jc * inv : (d == 1 ? jc * 1e-200 * inv : 0.0));
-        }
-        if (fabs(jc) > 1e200) { jp *= 1e-200; jc *= 1e-200; ++s; }
-    }
-}
-
-// J_k(z) for z of either sign: J_k(-z) = (-1)^k J_k(z)
-template <class Visit>
-__device__ __forceinline__ void bessel_j_desc(double z, int nk, Visit visit) {
-    if (z >= 0.0) {
-        bessel_j_desc_pos(z, nk, visit);
-    } else {
-        bessel_j_desc_pos(-z, nk, [&](int k, double J) { visit(k, (k & 1) ? -J : J); });
     }
 }
 
@@ -262,11 +234,10 @@ __device__ __forceinline__ void bessel_j_desc(double z, int nk, Visit visit) {
 // partial[split][meas][kChebKMax] (k < K written).
 // ---------------------------------------------------------------------------
 template <int K, int KIND, int SPEC, bool BI>
-__global__ __launch_bounds__(256) void k_cheb_points(
+__device__ __forceinline__ void cheb_points_body(
     int n_meas, const AntRec* __restrict__ ant, const AntRec* __restrict__ rxa, const MeasCheb* __restrict__ meas,
-    const ChebPlan* __restrict__ plan, double Kc, const void* __restrict__ recs_v, long n_pts,
+    double Kc, const void* __restrict__ recs_v, long n_pts,
     long pts_per_split, int n_split, int gx, float2* __restrict__ partial) {
-    if (plan->K != K) return;
     using Rec = typename std::conditional<KIND == 0, PtRec, QRec>::type;
     const long bid = blockIdx.x;
     const int lb = (int)((bid / 8) % gx);
@@ -373,128 +344,214 @@ __global__ __launch_bounds__(256) void k_cheb_points(
     }
 }
 
-// fixed-order sum over the splits of the moments: M[i][k] for k < K.  A
-// work-group takes 32 outputs; its 8 thread groups sum every 8th split in FP64,
-// then the 8 group sums are added in order.
-constexpr int kMsOut = 32, kMsGroups = 8;
-__global__ __launch_bounds__(256) void k_cheb_moment_sum(const float2* __restrict__ partial, int n_split,
-                                                         int n_meas, const ChebPlan* __restrict__ plan,
-                                                         float2* __restrict__ M) {
-    __shared__ double sr[kMsGroups][kMsOut], si[kMsGroups][kMsOut];
-    const int K = plan->K;
-    if (K == 0) return;
-    const int ol = threadIdx.x % kMsOut, gi = threadIdx.x / kMsOut;
-    const long o = (long)blockIdx.x * kMsOut + ol;
-    const bool live = o < (long)n_meas * kChebKMax && (int)(o % kChebKMax) < K;
-    double ar = 0.0, ai = 0.0;
-    if (live) {
-        for (int s = gi; s < n_split; s += kMsGroups) {
-            const float2 v = partial[(size_t)s * n_meas * kChebKMax + o];
-            ar += v.x;
-            ai += v.y;
-        }
+// One launch per order (ORDER), all but the plan's returning at once; or one
+// launch for all orders (ORDER 0), in which the larger ones' registers and code
+// lie beside the one that runs: see one_launch().
+#define RFVR_CP_PARAMS                                                                                               \
+    int n_meas, const AntRec* __restrict__ ant, const AntRec* __restrict__ rxa, const MeasCheb* __restrict__ meas,   \
+        double Kc, const void* __restrict__ recs_v, long n_pts, long pts_per_split, int n_split, int gx,             \
+        float2* __restrict__ partial
+#define RFVR_CP_ARGS n_meas, ant, rxa, meas, Kc, recs_v, n_pts, pts_per_split, n_split, gx, partial
+// body<K>(args) for the plan's order K, of those that the launch serves
+#define RFVR_BY_ORDER(ORDER, CALL)                              \
+    const int order = plan->K;                                  \
+    if constexpr (ORDER != 0) {                                 \
+        if (order == ORDER) CALL(ORDER);                        \
+    } else {                                                    \
+        switch (order) {                                        \
+            case 24: return CALL(24);                           \
+            case 28: return CALL(28);                           \
+            case 32: return CALL(32);                           \
+            case 40: return CALL(40);                           \
+            case 48: return CALL(48);                           \
+            case 64: return CALL(64);                           \
+            default: return;                                    \
+        }                                                       \
     }
-    sr[gi][ol] = ar;
-    si[gi][ol] = ai;
-    __syncthreads();
-    if (gi != 0 || !live) return;
-    double tr = 0.0, ti = 0.0;
-    for (int g = 0; g < kMsGroups; ++g) {
-        tr += sr[g][ol];
-        ti += si[g][ol];
-    }
-    M[o] = make_float2((float)tr, (float)ti);
+
+template <int ORDER, int KIND, int SPEC, bool BI>
+__global__ __launch_bounds__(256) void k_cheb_points(const ChebPlan* __restrict__ plan, RFVR_CP_PARAMS) {
+#define RFVR_CALL(K) cheb_points_body<K, KIND, SPEC, BI>(RFVR_CP_ARGS)
+    RFVR_BY_ORDER(ORDER, RFVR_CALL)
+#undef RFVR_CALL
 }
 
-// out[i][n] (+)= exp(-j 2 pi dn Kd rc_i) sum_k eps_k (-j)^k J_k(z_in) M_ik
-__global__ __launch_bounds__(256) void k_cheb_out(const ChebPlan* __restrict__ plan,
-                                                  const MeasCheb* __restrict__ meas,
-                                                  const float2* __restrict__ M, int n_meas, int n_freq,
-                                                  double Kd, int accumulate, float2* __restrict__ out) {
-    const int K = plan->K;
-    if (K == 0) return;
-    const long o = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= (long)n_meas * n_freq) return;
-    const int i = (int)(o / n_freq), n = (int)(o % n_freq);
-    const MeasCheb mc = meas[i];
-    const double dn = (double)n - 0.5 * (double)(n_freq - 1);
-    const double z = 6.283185307179586 * dn * Kd * mc.h;
-    const float2* Mi = M + (size_t)i * kChebKMax;
-    double ar = 0.0, ai = 0.0;
-    bessel_j_desc(z, K, [&](int k, double J) {
-        const double e = k == 0 ? J : 2.0 * J;
-        const float2 m = Mi[k];
-        // (-j)^k: 1, -j, -1, j
-        double vr, vi;
-        switch (k & 3) {
-            case 0: vr = m.x; vi = m.y; break;
-            case 1: vr = m.y; vi = -m.x; break;
-            case 2: vr = -m.x; vi = -m.y; break;
-            default: vr = -m.y; vi = m.x; break;
-        }
-        ar += e * vr;
-        ai += e * vi;
-    });
+// ---------------------------------------------------------------------------
+// Between moments or coefficients and frequencies.  With f(x) = sum_n g_n
+// exp(+j 2 pi dn Kd (rc + h x)) the series coefficients are those of f's Chebyshev
+// interpolation at N nodes x_l = cos((2l+1) pi / 2N),
+//   B_k = (2 - [k=0]) / N sum_l f(x_l) T_k(x_l),
+// and the way from moments to frequencies is the transpose.  N = K + 8: what
+// interpolation adds to the cut series are its terms from order 2N - K on, below
+// 1e-12 wherever the cut at K meets its tolerance.  Everything in FP64, one
+// work-group per measurement; the phasors of a node at n = 16 a + b are products
+// of two tables in LDS, 32 sines and cosines per node and 256 frequencies, where
+// Bessel functions by backward recurrence took 160 dependent FP64 steps per
+// frequency (coefficients of 1024 measurements x 128 frequencies: 67 -> 13 us, of
+// 64 x 32: 36 -> 6; sum of the splits and outputs of 64 x 32: 38 -> 10).
+// ---------------------------------------------------------------------------
+constexpr int kNodeMax = kChebKMax + 8, kTabLd = 17;
+struct NodeTables {
+    double2 A[kNodeMax * kTabLd];    // [node][a]: exp(j 2 pi (n0 + 16 a - nc) Kd r)
+    double2 B[kNodeMax * kTabLd];    // [node][b]: exp(j 2 pi b Kd r)
+    double r[kNodeMax];              // range of the node
+};
+
+__device__ __forceinline__ double2 turn(double rev, double sign) {
     double s, c;
-    const double ph = dn * Kd * mc.rc;
-    sincos(6.283185307179586 * (ph - floor(ph)), &s, &c);
-    // times exp(-j phase)
-    const float re = (float)(ar * c + ai * s), im = (float)(ai * c - ar * s);
-    if (accumulate) {
-        float2 v = out[o];
-        v.x += re;
-        v.y += im;
-        out[o] = v;
-    } else {
-        out[o] = make_float2(re, im);
+    sincospi(2.0 * (rev - floor(rev)), &s, &c);
+    return make_double2(c, sign * s);
+}
+__device__ __forceinline__ double2 cmul(double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
+
+// nodes and the b table (call once), and the a table of frequencies n0 .. n0 + 255
+__device__ __forceinline__ void node_begin(NodeTables& t, int N, const MeasCheb& mc, double Kd, double sign) {
+    for (int l = threadIdx.x; l < N; l += 256) t.r[l] = mc.rc + mc.h * cospi((double)(2 * l + 1) / (double)(2 * N));
+    __syncthreads();
+    for (int e = threadIdx.x; e < 16 * N; e += 256) t.B[(e >> 4) * kTabLd + (e & 15)] = turn((double)(e & 15) * Kd * t.r[e >> 4], sign);
+}
+__device__ __forceinline__ void node_block(NodeTables& t, int N, int n0, double nc, double Kd, double sign) {
+    for (int e = threadIdx.x; e < 16 * N; e += 256)
+        t.A[(e >> 4) * kTabLd + (e & 15)] = turn(((double)(n0 + 16 * (e & 15)) - nc) * Kd * t.r[e >> 4], sign);
+}
+
+// moments M[i][k] = sum over the splits (FP64, fixed order: 8 thread groups take
+// every 8th split, their sums are added in order), then
+// out[i][n] (+)= sum_l u_l exp(-j 2 pi dn Kd r_l), u_l = sum_k (2 - [k=0]) / N T_k(x_l) M_k
+__global__ __launch_bounds__(256) void k_cheb_out(const ChebPlan* __restrict__ plan, const MeasCheb* __restrict__ meas,
+                                                  const float2* __restrict__ partial, int n_split, int n_meas, int n_freq,
+                                                  double Kd, int accumulate, float2* __restrict__ out) {
+    __shared__ NodeTables t;
+    __shared__ double2 grp[8][32];
+    __shared__ double2 M[kChebKMax], u[kNodeMax];
+    const int K = plan->K;
+    if (K == 0) return;
+    const int i = blockIdx.x, N = K + 8, tid = threadIdx.x;
+    for (int k0 = 0; k0 < K; k0 += 32) {
+        const int k = k0 + (tid & 31), gi = tid >> 5;
+        double ar = 0.0, ai = 0.0;
+        if (k < K) {
+#pragma unroll 8
+            for (int s = gi; s < n_split; s += 8) {
+                const float2 v = partial[((size_t)s * n_meas + i) * kChebKMax + k];
+                ar += v.x;
+                ai += v.y;
+            }
+        }
+        grp[gi][tid & 31] = make_double2(ar, ai);
+        __syncthreads();
+        if (gi == 0 && k < K) {
+            double2 m = grp[0][tid];
+            for (int g = 1; g < 8; ++g) {
+                m.x += grp[g][tid].x;
+                m.y += grp[g][tid].y;
+            }
+            M[k] = m;
+        }
+        __syncthreads();
+    }
+    const MeasCheb mc = meas[i];
+    node_begin(t, N, mc, Kd, -1.0);
+    if (tid < N) {
+        const double x = cospi((double)(2 * tid + 1) / (double)(2 * N));
+        double tm = 1.0, tk = x, ur = 0.5 * M[0].x + x * M[1].x, ui = 0.5 * M[0].y + x * M[1].y;
+        for (int k = 2; k < K; ++k) {
+            const double tn = 2.0 * x * tk - tm;
+            tm = tk;
+            tk = tn;
+            ur += tn * M[k].x;
+            ui += tn * M[k].y;
+        }
+        u[tid] = make_double2(2.0 / N * ur, 2.0 / N * ui);
+    }
+    const double nc = 0.5 * (double)(n_freq - 1);
+    for (int n0 = 0; n0 < n_freq; n0 += 256) {
+        node_block(t, N, n0, nc, Kd, -1.0);
+        __syncthreads();
+        for (int e = tid; e < 16 * N; e += 256) {
+            double2& a = t.A[(e >> 4) * kTabLd + (e & 15)];
+            a = cmul(a, u[e >> 4]);
+        }
+        __syncthreads();
+        const int n = n0 + tid;
+        if (n < n_freq) {
+            double re = 0.0, im = 0.0;
+            for (int l = 0; l < N; ++l) {
+                const double2 v = cmul(t.A[l * kTabLd + (tid >> 4)], t.B[l * kTabLd + (tid & 15)]);
+                re += v.x;
+                im += v.y;
+            }
+            float2* o = out + (size_t)i * n_freq + n;
+            float2 v = make_float2((float)re, (float)im);
+            if (accumulate) {
+                v.x += o->x;
+                v.y += o->y;
+            }
+            *o = v;
+        }
+        __syncthreads();
     }
 }
 
-// B[i][k] = eps_k j^k sum_n g[i][n] exp(+j 2 pi dn Kd rc_i) J_k(z_in), k < K;
-// one wave per measurement, lane-private sums in LDS, then a fixed-order sum
-// over lanes per k
-__global__ __launch_bounds__(64) void k_cheb_coef(const ChebPlan* __restrict__ plan,
-                                                  const MeasCheb* __restrict__ meas,
-                                                  const float2* __restrict__ g, int n_meas, int n_freq,
-                                                  double Kd, float2* __restrict__ B) {
-    __shared__ double2 acc[kChebKMax][64];
+// B[i][k], k < K, from g[i][n]
+__global__ __launch_bounds__(256) void k_cheb_coef(const ChebPlan* __restrict__ plan,
+                                                   const MeasCheb* __restrict__ meas,
+                                                   const float2* __restrict__ g, int n_meas, int n_freq,
+                                                   double Kd, float2* __restrict__ B) {
+    __shared__ NodeTables t;
+    __shared__ double2 f[kNodeMax];
+    __shared__ float2 gs[256];
     const int K = plan->K;
     if (K == 0) return;
-    const int i = blockIdx.x, lane = threadIdx.x;
+    const int i = blockIdx.x, N = K + 8, tid = threadIdx.x;
     const MeasCheb mc = meas[i];
-    for (int k = 0; k < K; ++k) acc[k][lane] = make_double2(0.0, 0.0);
-    for (int n = lane; n < n_freq; n += 64) {
-        const float2 gv = g[(size_t)i * n_freq + n];
-        const double dn = (double)n - 0.5 * (double)(n_freq - 1);
-        const double ph = dn * Kd * mc.rc;
-        double s, c;
-        sincos(6.283185307179586 * (ph - floor(ph)), &s, &c);
-        const double wr = gv.x * c - gv.y * s, wi = gv.x * s + gv.y * c;   // g exp(+j phase)
-        const double z = 6.283185307179586 * dn * Kd * mc.h;
-        bessel_j_desc(z, K, [&](int k, double J) {
-            double2 a = acc[k][lane];
-            a.x += wr * J;
-            a.y += wi * J;
-            acc[k][lane] = a;
-        });
+    const double nc = 0.5 * (double)(n_freq - 1);
+    if (tid < N) f[tid] = make_double2(0.0, 0.0);
+    node_begin(t, N, mc, Kd, 1.0);
+    for (int n0 = 0; n0 < n_freq; n0 += 256) {
+        gs[tid] = n0 + tid < n_freq ? g[(size_t)i * n_freq + n0 + tid] : make_float2(0.0f, 0.0f);
+        node_block(t, N, n0, nc, Kd, 1.0);
+        __syncthreads();
+        // (node, a): sum over b, times the a phasor
+        for (int e = tid; e < 16 * N; e += 256) {
+            const int l = e >> 4, a = e & 15;
+            double sr = 0.0, si = 0.0;
+#pragma unroll 4
+            for (int b = 0; b < 16; ++b) {
+                const double2 w = t.B[l * kTabLd + b];
+                const float2 v = gs[16 * a + b];
+                sr += w.x * v.x - w.y * v.y;
+                si += w.x * v.y + w.y * v.x;
+            }
+            double2& o = t.A[l * kTabLd + a];
+            o = cmul(o, make_double2(sr, si));
+        }
+        __syncthreads();
+        if (tid < N) {
+            double2 v = f[tid];
+            for (int a = 0; a < 16; ++a) {
+                v.x += t.A[tid * kTabLd + a].x;
+                v.y += t.A[tid * kTabLd + a].y;
+            }
+            f[tid] = v;
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    for (int k = lane; k < K; k += 64) {
-        double sr = 0.0, si = 0.0;
-        for (int l = 0; l < 64; ++l) {
-            sr += acc[k][l].x;
-            si += acc[k][l].y;
+    if (tid < K) {
+        // cos(k (2l+1) pi / 2N) for l = 0, 1, ... by its recurrence in l
+        const double w = (double)tid / (double)(2 * N);
+        double cm = cospi(w), c0 = cm;                   // l = -1 and l = 0 (even in 2l+1)
+        const double c2 = 2.0 * cospi(2.0 * w);
+        double br = 0.0, bi = 0.0;
+        for (int l = 0; l < N; ++l) {
+            br += c0 * f[l].x;
+            bi += c0 * f[l].y;
+            const double cn = c2 * c0 - cm;
+            cm = c0;
+            c0 = cn;
         }
-        const double e = k == 0 ? 1.0 : 2.0;
-        // j^k: 1, j, -1, -j
-        double vr, vi;
-        switch (k & 3) {
-            case 0: vr = sr; vi = si; break;
-            case 1: vr = -si; vi = sr; break;
-            case 2: vr = -sr; vi = -si; break;
-            default: vr = si; vi = -sr; break;
-        }
-        B[(size_t)i * kChebKMax + k] = make_float2((float)(e * vr), (float)(e * vi));
+        const double e = (tid == 0 ? 1.0 : 2.0) / N;
+        B[(size_t)i * kChebKMax + tid] = make_float2((float)(e * br), (float)(e * bi));
     }
 }
 
@@ -557,21 +614,30 @@ __device__ __forceinline__ void cheb_series2(const float2* __restrict__ Bi, cons
 // matched filter forward: lane = query point, loop over measurements
 // (records, plan and coefficients are wave-uniform loads)
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ void mf_store(float2* z, float* power, long q, float zr, float zi) {
+    if (z) z[q] = make_float2(zr, zi);
+    if (power) power[q] = sqrtf(zr * zr + zi * zi);
+}
+
+// Per split of the measurements (blockIdx.y) `per` of them.  part: of several
+// splits the sums [split][1 or 2][n_q], else NULL.  (The arrays the loop reads
+// are kernel arguments of their own, marked as not aliased: only then are the
+// wave-uniform reads scalar loads.)
+#define RFVR_MF_PARAMS                                                                                              \
+    long n_q, const float* __restrict__ xq, int n_meas, int per, const AntRec* __restrict__ ant,                    \
+        const AntRec* __restrict__ rxa, const MeasCheb* __restrict__ meas, const float2* __restrict__ B,            \
+        const float2* __restrict__ B2, double Kc, float2* __restrict__ z, float* __restrict__ power,                \
+        float2* __restrict__ z2, float* __restrict__ power2, float2* __restrict__ part
+#define RFVR_MF_ARGS n_q, xq, n_meas, per, ant, rxa, meas, B, B2, Kc, z, power, z2, power2, part
+
 template <int K, bool TWO, bool BI>
-__global__ __launch_bounds__(256) void k_cheb_mf(const ChebPlan* __restrict__ plan, long n_q,
-                                                 const float* __restrict__ xq, int n_meas,
-                                                 const AntRec* __restrict__ ant,
-                                                 const AntRec* __restrict__ rxa,
-                                                 const MeasCheb* __restrict__ meas,
-                                                 const float2* __restrict__ B, const float2* __restrict__ B2,
-                                                 double Kc, float2* __restrict__ z, float* __restrict__ power,
-                                                 float2* __restrict__ z2, float* __restrict__ power2) {
-    if (plan->K != K) return;
+__device__ __forceinline__ void cheb_mf_body(RFVR_MF_PARAMS) {
+    const int i0 = blockIdx.y * per, i1 = min(i0 + per, n_meas);
     const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const long qc = q < n_q ? q : n_q - 1;
     const double px = (double)xq[3 * qc], py = (double)xq[3 * qc + 1], pz = (double)xq[3 * qc + 2];
     float zr = 0.0f, zi = 0.0f, z2r = 0.0f, z2i = 0.0f;
-    for (int i = 0; i < n_meas; ++i) {
+    for (int i = i0; i < i1; ++i) {
         const AntRec A = ant[i];
         const MeasCheb mc = meas[i];
         float y;
@@ -597,11 +663,38 @@ __global__ __launch_bounds__(256) void k_cheb_mf(const ChebPlan* __restrict__ pl
         zi = __builtin_fmaf(c0, si, __builtin_fmaf(s0, sr, zi));
     }
     if (q >= n_q) return;
-    if (z) z[q] = make_float2(zr, zi);
-    if (power) power[q] = sqrtf(zr * zr + zi * zi);
-    if constexpr (TWO) {
-        if (z2) z2[q] = make_float2(z2r, z2i);
-        if (power2) power2[q] = sqrtf(z2r * z2r + z2i * z2i);
+    if (part) {
+        float2* p = part + (size_t)blockIdx.y * (TWO ? 2 : 1) * n_q + q;
+        p[0] = make_float2(zr, zi);
+        if constexpr (TWO) p[n_q] = make_float2(z2r, z2i);
+        return;
+    }
+    mf_store(z, power, q, zr, zi);
+    if constexpr (TWO) mf_store(z2, power2, q, z2r, z2i);
+}
+
+template <int ORDER, bool TWO, bool BI>
+__global__ __launch_bounds__(256) void k_cheb_mf(const ChebPlan* __restrict__ plan, RFVR_MF_PARAMS) {
+#define RFVR_CALL(K) cheb_mf_body<K, TWO, BI>(RFVR_MF_ARGS)
+    RFVR_BY_ORDER(ORDER, RFVR_CALL)
+#undef RFVR_CALL
+}
+
+// fixed-order sum over the measurement splits
+__global__ __launch_bounds__(256) void k_cheb_mf_sum(const ChebPlan* __restrict__ plan, long n_q,
+                                                     const float2* __restrict__ part, int n_split, int two,
+                                                     float2* z, float* power, float2* z2, float* power2) {
+    if (plan->K == 0) return;
+    const long q = (long)blockIdx.x * 256 + threadIdx.x;
+    if (q >= n_q) return;
+    for (int w = 0; w <= two; ++w) {
+        float zr = 0.0f, zi = 0.0f;
+        for (int s = 0; s < n_split; ++s) {
+            const float2 v = part[((size_t)s * (two + 1) + w) * n_q + q];
+            zr += v.x;
+            zi += v.y;
+        }
+        mf_store(w ? z2 : z, w ? power2 : power, q, zr, zi);
     }
 }
 
@@ -610,20 +703,32 @@ __global__ __launch_bounds__(256) void k_cheb_mf(const ChebPlan* __restrict__ pl
 // G = Re(sum_n g[i][n] exp(+j 2 pi (K0 + n Kd) r)) then the chain rule of the
 // per-frequency kernel
 // ---------------------------------------------------------------------------
+// part: of several measurement splits the sums [split][5][n_pts], else NULL
+#define RFVR_BWD_PARAMS                                                                                       \
+    long n_pts, const PtRec* __restrict__ rec, int n_meas, int per, const AntRec* __restrict__ ant,           \
+        const AntRec* __restrict__ rxa, const MeasCheb* __restrict__ meas, const float2* __restrict__ B,      \
+        double Kc, float* __restrict__ g_b, float* __restrict__ g_T, float* __restrict__ g_n, float* __restrict__ part
+#define RFVR_BWD_ARGS n_pts, rec, n_meas, per, ant, rxa, meas, B, Kc, g_b, g_T, g_n, part
+
+// a point's sums over its pairs, times the factors common to them
+template <bool BI>
+__device__ __forceinline__ void bwd_store(float* g_b, float* g_T, float* g_n, long j, float b, float gb, float gt,
+                                          float gn0, float gn1, float gn2) {
+    g_b[j] = gb;
+    g_T[j] = b * gt;
+    const float b4 = (BI ? -2.0f : 4.0f) * b;
+    g_n[3 * j] = b4 * gn0;
+    g_n[3 * j + 1] = b4 * gn1;
+    g_n[3 * j + 2] = b4 * gn2;
+}
+
 template <int K, int SPEC, bool BI>
-__global__ __launch_bounds__(256) void k_cheb_render_bwd(const ChebPlan* __restrict__ plan, long n_pts,
-                                                         const PtRec* __restrict__ rec, int n_meas,
-                                                         const AntRec* __restrict__ ant,
-                                                         const AntRec* __restrict__ rxa,
-                                                         const MeasCheb* __restrict__ meas,
-                                                         const float2* __restrict__ B, double Kc,
-                                                         float* __restrict__ g_b, float* __restrict__ g_T,
-                                                         float* __restrict__ g_n) {
-    if (plan->K != K) return;
+__device__ __forceinline__ void cheb_bwd_body(RFVR_BWD_PARAMS) {
+    const int i0 = blockIdx.y * per, i1 = min(i0 + per, n_meas);
     const long j = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const PtRec P = rec[j < n_pts ? j : n_pts - 1];
     float gb = 0.0f, gt = 0.0f, gn0 = 0.0f, gn1 = 0.0f, gn2 = 0.0f;
-    for (int i = 0; i < n_meas; ++i) {
+    for (int i = i0; i < i1; ++i) {
         const AntRec A = ant[i];
         const MeasCheb mc = meas[i];
         const double dx = P.x - A.x, dy = P.y - A.y, dz = P.z - A.z;
@@ -698,12 +803,38 @@ __global__ __launch_bounds__(256) void k_cheb_render_bwd(const ChebPlan* __restr
         }
     }
     if (j >= n_pts) return;
-    g_b[j] = gb;
-    g_T[j] = P.b * gt;
-    const float b4 = (BI ? -2.0f : 4.0f) * P.b;
-    g_n[3 * j] = b4 * gn0;
-    g_n[3 * j + 1] = b4 * gn1;
-    g_n[3 * j + 2] = b4 * gn2;
+    if (part) {
+        float* p = part + (size_t)blockIdx.y * 5 * n_pts + j;
+        p[0] = gb;
+        p[n_pts] = gt;
+        p[2 * n_pts] = gn0;
+        p[3 * n_pts] = gn1;
+        p[4 * n_pts] = gn2;
+        return;
+    }
+    bwd_store<BI>(g_b, g_T, g_n, j, P.b, gb, gt, gn0, gn1, gn2);
+}
+
+template <int ORDER, int SPEC, bool BI>
+__global__ __launch_bounds__(256) void k_cheb_render_bwd(const ChebPlan* __restrict__ plan, RFVR_BWD_PARAMS) {
+#define RFVR_CALL(K) cheb_bwd_body<K, SPEC, BI>(RFVR_BWD_ARGS)
+    RFVR_BY_ORDER(ORDER, RFVR_CALL)
+#undef RFVR_CALL
+}
+
+// fixed-order sum over the measurement splits
+template <bool BI>
+__global__ __launch_bounds__(256) void k_cheb_bwd_sum(const ChebPlan* __restrict__ plan, long n_pts,
+                                                      const PtRec* __restrict__ rec, const float* __restrict__ part,
+                                                      int n_split, float* g_b, float* g_T, float* g_n) {
+    if (plan->K == 0) return;
+    const long j = (long)blockIdx.x * 256 + threadIdx.x;
+    if (j >= n_pts) return;
+    float v[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    for (int s = 0; s < n_split; ++s)
+#pragma unroll
+        for (int c = 0; c < 5; ++c) v[c] += part[((size_t)s * 5 + c) * n_pts + j];
+    bwd_store<BI>(g_b, g_T, g_n, j, rec[j].b, v[0], v[1], v[2], v[3], v[4]);
 }
 
 __global__ void k_cheb_order(const ChebPlan* __restrict__ plan, int32_t* __restrict__ order) {
@@ -713,6 +844,9 @@ __global__ void k_cheb_order(const ChebPlan* __restrict__ plan, int32_t* __restr
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+// up to this many points the plan's work-group takes the bounding box itself
+// (a launch less; 16 points per thread)
+constexpr long kPlanPoints = 16384;
 int cheb_bbox_blocks(long n) {
     long b = (n + 4095) / 4096;
     return (int)(b < 1 ? 1 : (b > 1024 ? 1024 : b));
@@ -723,48 +857,78 @@ hipError_t launch_cheb_order(const ChebPlan* plan, int32_t* order, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_cheb_plan(const float* xyz, long n, const AntRec* ant, const AntRec* rxa, int n_meas,
-                            double Kd, int n_freq, float* bbox_part, MeasCheb* meas, ChebPlan* plan,
-                            hipStream_t st) {
-    const int nb = cheb_bbox_blocks(n);
-    const long per = (n + nb - 1) / nb;
-    hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(256), 0, st, xyz, n, per, bbox_part);
-    hipLaunchKernelGGL(k_cheb_plan, dim3(1), dim3(256), 0, st, bbox_part, nb, ant, rxa, n_meas, Kd, n_freq, meas,
-                       plan);
+hipError_t launch_cheb_plan(const float* xyz, long n, const float* tx, const float* phi_tx, const float* rx,
+                            const float* phi_rx, AntRec* ant, AntRec* rxa, int n_meas, double Kd, int n_freq,
+                            float* bbox_part, MeasCheb* meas, ChebPlan* plan, hipStream_t st) {
+    int nb = 0;
+    if (n > kPlanPoints) {
+        nb = cheb_bbox_blocks(n);
+        const long per = (n + nb - 1) / nb;
+        hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(256), 0, st, xyz, n, per, bbox_part);
+    }
+    hipLaunchKernelGGL(k_cheb_plan, dim3(1), dim3(kPlanThreads), 0, st, xyz, n, bbox_part, nb, tx, phi_tx, rx, phi_rx, ant,
+                       rxa, n_meas, Kd, n_freq, meas, plan);
     return hipGetLastError();
 }
 
 // wavenumber at the centre of the band (revolutions per metre of range)
 static double band_centre(const RenderGeom& g) { return g.K0 + 0.5 * (double)(g.n_freq - 1) * g.Kd; }
 
+// Below 2^23 pairs one launch serves every order: an empty launch costs 2 to 5 us,
+// a moment kernel of 4096 points x 64 measurements 14.  Above, one per order:
+// the order that runs does not pay for the registers and the schedule of the
+// others (10^9 pairs at K = 28: 5.8 ms against 6.8 of a kernel for 24 and 28).
+static bool one_launch(long n_pts, int n_meas) { return (double)n_pts * n_meas < 8388608.0; }
+
+template <class Go>
+static void by_order(long n_pts, int n_meas, Go go) {
+    if (one_launch(n_pts, n_meas)) return go(std::integral_constant<int, 0>{});
+    go(std::integral_constant<int, 24>{});
+    go(std::integral_constant<int, 28>{});
+    go(std::integral_constant<int, 32>{});
+    go(std::integral_constant<int, 40>{});
+    go(std::integral_constant<int, 48>{});
+    go(std::integral_constant<int, 64>{});
+}
+
 template <int KIND, int SPEC, bool BI>
 static void launch_cp_all(const RenderGeom& g, const AntRec* ant, const MeasCheb* meas, const ChebPlan* plan,
                           const void* rec, int n_split, float2* partial, hipStream_t st) {
-    const int gx = (g.n_meas + 255) / 256;
+    // waves per work-group: as many of four as leave few lanes without a measurement
+    int w = 4;
+    while (w > 1 && (g.n_meas + 64 * w - 1) / (64 * w) * w > (g.n_meas + 63) / 64 * 9 / 8) w /= 2;
+    const dim3 block(64 * w);
+    const int gx = (g.n_meas + 64 * w - 1) / (64 * w);
     const long groups = (n_split + 7) / 8;
     dim3 grid((unsigned)(groups * 8 * gx));
     const long per = (g.n_pts + n_split - 1) / n_split;
     const double Kc = band_centre(g);
-#define RFVR_CP(KK)                                                                                           \
-    hipLaunchKernelGGL((k_cheb_points<KK, KIND, SPEC, BI>), grid, dim3(256), 0, st, g.n_meas, ant, g.rxa, meas, \
-                       plan, Kc, rec, g.n_pts, per, n_split, gx, partial)
-    RFVR_CP(24);
-    RFVR_CP(28);
-    RFVR_CP(32);
-    RFVR_CP(40);
-    RFVR_CP(48);
-    RFVR_CP(64);
-#undef RFVR_CP
+    by_order(g.n_pts, g.n_meas, [&](auto order) {
+        hipLaunchKernelGGL((k_cheb_points<decltype(order)::value, KIND, SPEC, BI>), grid, block, 0, st, plan, g.n_meas, ant,
+                           g.rxa, meas, Kc, rec, g.n_pts, per, n_split, gx, partial);
+    });
+}
+
+// Measurement splits of the reductions over frequencies (a lane per point): as
+// many as bring the launch to 8192 waves, eight per SIMD, of at least 8
+// measurements each.  32768 points x 3200 measurements, 512 waves of points:
+// filter forward 1458 us with one split, 286 with 16; render adjoint 1643, 362.
+int cheb_meas_splits(long n_pts, int n_meas) {
+    const long waves = (n_pts + 63) / 64;
+    long ns = (8192 + waves - 1) / waves;
+    if (ns > n_meas / 8) ns = n_meas / 8;
+    return (int)(ns < 1 ? 1 : ns);
 }
 
 // Point splits of the moment kernels: twice the waves of the per-frequency
 // kernels' rule (8192, eight per SIMD).  A lane's work per point is short at
 // the lower orders, where five waves per SIMD fit, and more resident waves
-// hide the per-tile barriers and LDS reads; >= 128 points per split.
+// hide the scalar loads; >= 32 points per split (4096 points x 64
+// measurements: 48 us with 32 splits of 128 points, 14 with 128).
 int cheb_point_splits(long n_pts, int n_meas) {
     const long waves_per_split = (n_meas + 63) / 64;
     long ns = (8192 + waves_per_split - 1) / waves_per_split;
-    const long max_by_pts = (n_pts + 127) / 128;
+    const long max_by_pts = (n_pts + 31) / 32;
     if (ns > max_by_pts) ns = max_by_pts;
     if (ns < 1) ns = 1;
     if (ns > 65535) ns = 65535;
@@ -773,7 +937,7 @@ int cheb_point_splits(long n_pts, int n_meas) {
 
 hipError_t launch_cheb_points(const RenderGeom& g, int kind, uint32_t flags, const AntRec* ant,
                               const MeasCheb* meas, const ChebPlan* plan, const void* rec, int n_split,
-                              float2* partial, float2* M, float2* out, int accumulate, hipStream_t st) {
+                              float2* partial, float2* out, int accumulate, hipStream_t st) {
     const auto all = [&](auto kind_c, auto spec_c) {
         constexpr int KI = decltype(kind_c)::value, SP = decltype(spec_c)::value;
         if (g.rxa) launch_cp_all<KI, SP, true>(g, ant, meas, plan, rec, n_split, partial, st);
@@ -790,83 +954,75 @@ hipError_t launch_cheb_points(const RenderGeom& g, int kind, uint32_t flags, con
             default: all(I0{}, std::integral_constant<int, RFVR_SPEC_CLAMP>{}); break;
         }
     }
-    const long nm = (long)g.n_meas * kChebKMax;
-    hipLaunchKernelGGL(k_cheb_moment_sum, dim3((unsigned)((nm + kMsOut - 1) / kMsOut)), dim3(kMsOut * kMsGroups), 0,
-                       st, partial, n_split, g.n_meas, plan, M);
-    const long no = (long)g.n_meas * g.n_freq;
-    hipLaunchKernelGGL(k_cheb_out, dim3((unsigned)((no + 255) / 256)), dim3(256), 0, st, plan, meas, M, g.n_meas,
-                       g.n_freq, g.Kd, accumulate, out);
+    hipLaunchKernelGGL(k_cheb_out, dim3(g.n_meas), dim3(256), 0, st, plan, meas, partial, n_split, g.n_meas, g.n_freq,
+                       g.Kd, accumulate, out);
     return hipGetLastError();
 }
 
 hipError_t launch_cheb_coef(const RenderGeom& g, const ChebPlan* plan, const MeasCheb* meas, const float2* sig,
                             float2* B, hipStream_t st) {
-    hipLaunchKernelGGL(k_cheb_coef, dim3(g.n_meas), dim3(64), 0, st, plan, meas, sig, g.n_meas, g.n_freq, g.Kd,
+    hipLaunchKernelGGL(k_cheb_coef, dim3(g.n_meas), dim3(256), 0, st, plan, meas, sig, g.n_meas, g.n_freq, g.Kd,
                        B);
     return hipGetLastError();
 }
 
-template <bool TWO, bool BI>
-static void launch_cmf_all(const RenderGeom& g, const ChebPlan* plan, long n_q, const float* xq,
-                           const AntRec* ant, const MeasCheb* meas, const float2* B, const float2* B2,
-                           float2* z, float* power, float2* z2, float* power2, hipStream_t st) {
-    dim3 grid((unsigned)((n_q + 255) / 256));
-    const double Kc = band_centre(g);
-#define RFVR_CMF(KK)                                                                                     \
-    hipLaunchKernelGGL((k_cheb_mf<KK, TWO, BI>), grid, dim3(256), 0, st, plan, n_q, xq, g.n_meas, ant, g.rxa, \
-                       meas, B, B2, Kc, z, power, z2, power2)
-    RFVR_CMF(24);
-    RFVR_CMF(28);
-    RFVR_CMF(32);
-    RFVR_CMF(40);
-    RFVR_CMF(48);
-    RFVR_CMF(64);
-#undef RFVR_CMF
-}
-
 hipError_t launch_cheb_mf(const RenderGeom& g, const ChebPlan* plan, long n_q, const float* xq,
                           const AntRec* ant, const MeasCheb* meas, const float2* B, const float2* B2,
-                          float2* z, float* power, float2* z2, float* power2, hipStream_t st) {
-    if (B2) {
-        if (g.rxa) launch_cmf_all<true, true>(g, plan, n_q, xq, ant, meas, B, B2, z, power, z2, power2, st);
-        else launch_cmf_all<true, false>(g, plan, n_q, xq, ant, meas, B, B2, z, power, z2, power2, st);
-    } else {
-        if (g.rxa) launch_cmf_all<false, true>(g, plan, n_q, xq, ant, meas, B, B2, z, power, z2, power2, st);
-        else launch_cmf_all<false, false>(g, plan, n_q, xq, ant, meas, B, B2, z, power, z2, power2, st);
-    }
-    return hipGetLastError();
-}
-
-template <int SPEC, bool BI>
-static void launch_crb_all(const RenderGeom& g, const ChebPlan* plan, const AntRec* ant, const MeasCheb* meas,
-                           const PtRec* rec, const float2* B, float* g_b, float* g_T, float* g_n,
-                           hipStream_t st) {
-    dim3 grid((unsigned)((g.n_pts + 255) / 256));
+                          float2* z, float* power, float2* z2, float* power2, int n_split, float2* part,
+                          hipStream_t st) {
+    const int per = (g.n_meas + n_split - 1) / n_split;
+    const dim3 grid((unsigned)((n_q + 255) / 256), (unsigned)n_split);
+    if (n_split == 1) part = nullptr;
     const double Kc = band_centre(g);
-#define RFVR_CRB(KK)                                                                                        \
-    hipLaunchKernelGGL((k_cheb_render_bwd<KK, SPEC, BI>), grid, dim3(256), 0, st, plan, g.n_pts, rec, g.n_meas,  \
-                       ant, g.rxa, meas, B, Kc, g_b, g_T, g_n)
-    RFVR_CRB(24);
-    RFVR_CRB(28);
-    RFVR_CRB(32);
-    RFVR_CRB(40);
-    RFVR_CRB(48);
-    RFVR_CRB(64);
-#undef RFVR_CRB
+    const auto all = [&](auto two, auto bi) {
+        by_order(n_q, g.n_meas, [&](auto order) {
+            hipLaunchKernelGGL((k_cheb_mf<decltype(order)::value, decltype(two)::value, decltype(bi)::value>), grid, dim3(256),
+                               0, st, plan, n_q, xq, g.n_meas, per, ant, g.rxa, meas, B, B2, Kc, z, power, z2, power2, part);
+        });
+    };
+    if (B2) {
+        if (g.rxa) all(std::true_type{}, std::true_type{});
+        else all(std::true_type{}, std::false_type{});
+    } else {
+        if (g.rxa) all(std::false_type{}, std::true_type{});
+        else all(std::false_type{}, std::false_type{});
+    }
+    if (n_split > 1)
+        hipLaunchKernelGGL(k_cheb_mf_sum, dim3(grid.x), dim3(256), 0, st, plan, n_q, part, n_split, B2 ? 1 : 0, z, power,
+                           z2, power2);
+    return hipGetLastError();
 }
 
 hipError_t launch_cheb_render_bwd(const RenderGeom& g, uint32_t flags, const ChebPlan* plan, const AntRec* ant,
                                   const MeasCheb* meas, const PtRec* rec, const float2* B, float* g_b,
-                                  float* g_T, float* g_n, hipStream_t st) {
+                                  float* g_T, float* g_n, int n_split, float* part, hipStream_t st) {
+    const int per = (g.n_meas + n_split - 1) / n_split;
+    const dim3 grid((unsigned)((g.n_pts + 255) / 256), (unsigned)n_split);
+    if (n_split == 1) part = nullptr;
+    const double Kc = band_centre(g);
     const auto all = [&](auto spec_c) {
         constexpr int SP = decltype(spec_c)::value;
-        if (g.rxa) launch_crb_all<SP, true>(g, plan, ant, meas, rec, B, g_b, g_T, g_n, st);
-        else launch_crb_all<SP, false>(g, plan, ant, meas, rec, B, g_b, g_T, g_n, st);
+        by_order(g.n_pts, g.n_meas, [&](auto order) {
+            constexpr int O = decltype(order)::value;
+            if (g.rxa)
+                hipLaunchKernelGGL((k_cheb_render_bwd<O, SP, true>), grid, dim3(256), 0, st, plan, g.n_pts, rec, g.n_meas,
+                                   per, ant, g.rxa, meas, B, Kc, g_b, g_T, g_n, part);
+            else
+                hipLaunchKernelGGL((k_cheb_render_bwd<O, SP, false>), grid, dim3(256), 0, st, plan, g.n_pts, rec, g.n_meas,
+                                   per, ant, g.rxa, meas, B, Kc, g_b, g_T, g_n, part);
+        });
     };
     switch (flags & RFVR_SPEC_MASK) {
         case RFVR_SPEC_RAW: all(std::integral_constant<int, RFVR_SPEC_RAW>{}); break;
         case RFVR_SPEC_OFF: all(std::integral_constant<int, RFVR_SPEC_OFF>{}); break;
         default: all(std::integral_constant<int, RFVR_SPEC_CLAMP>{}); break;
+    }
+    if (n_split > 1) {
+        const auto sum = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(grid.x), dim3(256), 0, st, plan, g.n_pts, rec, part, n_split, g_b, g_T, g_n);
+        };
+        if (g.rxa) sum(k_cheb_bwd_sum<true>);
+        else sum(k_cheb_bwd_sum<false>);
     }
     return hipGetLastError();
 }

@@ -746,10 +746,16 @@ hipError_t launch_scan_adjoint(const RenderGeom& g, const float* ray_w, const fl
     return hipGetLastError();
 }
 
-// deterministic sum of n floats into out[0] (one work-group, fixed order)
-__global__ __launch_bounds__(256) void k_sum_scalars(const float* __restrict__ part, int n,
-                                                     float* __restrict__ out, int accumulate) {
+// deterministic sums of n floats into out[0] and out2[0] (a work-group each, fixed order)
+__global__ __launch_bounds__(256) void k_sum_scalars(const float* __restrict__ part, float* __restrict__ out,
+                                                     const float* __restrict__ part2, float* __restrict__ out2, int n,
+                                                     int accumulate) {
     __shared__ double sh[256];
+    if (blockIdx.x == 1) {
+        part = part2;
+        out = out2;
+    }
+    if (!out) return;
     double acc = 0.0;
     for (int k = threadIdx.x; k < n; k += 256) acc += (double)part[k];
     sh[threadIdx.x] = acc;
@@ -764,9 +770,9 @@ __global__ __launch_bounds__(256) void k_sum_scalars(const float* __restrict__ p
     }
 }
 
-hipError_t launch_sum_scalars(const float* part, int n, float* out, int accumulate,
+hipError_t launch_sum_scalars(const float* part, float* out, const float* part2, float* out2, int n, int accumulate,
                               hipStream_t st) {
-    hipLaunchKernelGGL(k_sum_scalars, dim3(1), dim3(256), 0, st, part, n, out, accumulate);
+    hipLaunchKernelGGL(k_sum_scalars, dim3(2), dim3(256), 0, st, part, out, part2, out2, n, accumulate);
     return hipGetLastError();
 }
 

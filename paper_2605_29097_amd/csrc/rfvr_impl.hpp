@@ -358,7 +358,8 @@ hipError_t launch_scan_adjoint(const RenderGeom& g, const float* ray_w, const fl
                                const float* g_b, const float* g_T, const float* g_n,
                                float* g_alpha_tmp, float* part_amp, float* part_s, float* g_sdf,
                                float* g_grad, float* g_refl, int accumulate, hipStream_t st);
-hipError_t launch_sum_scalars(const float* part, int n, float* out, int accumulate,
+// out[0] (+)= sum of part, out2[0] (+)= sum of part2 (either output may be NULL)
+hipError_t launch_sum_scalars(const float* part, float* out, const float* part2, float* out2, int n, int accumulate,
                               hipStream_t st);
 
 // Launchers (mf.hip)
@@ -395,19 +396,22 @@ constexpr int kChebMaxOrder = 64;
 int cheb_bbox_blocks(long n);
 int cheb_point_splits(long n_pts, int n_meas);
 hipError_t launch_cheb_order(const ChebPlan* plan, int32_t* order, hipStream_t st);
-hipError_t launch_cheb_plan(const float* xyz, long n, const AntRec* ant, const AntRec* rxa, int n_meas,
-                            double Kd, int n_freq, float* bbox_part, MeasCheb* meas, ChebPlan* plan,
-                            hipStream_t st);
+// also writes the measurement records ant (and rxa of a bistatic aperture)
+hipError_t launch_cheb_plan(const float* xyz, long n, const float* tx, const float* phi_tx, const float* rx,
+                            const float* phi_rx, AntRec* ant, AntRec* rxa, int n_meas, double Kd, int n_freq,
+                            float* bbox_part, MeasCheb* meas, ChebPlan* plan, hipStream_t st);
+int cheb_meas_splits(long n_pts, int n_meas);
 hipError_t launch_cheb_points(const RenderGeom& g, int kind, uint32_t flags, const AntRec* ant,
                               const MeasCheb* meas, const ChebPlan* plan, const void* rec, int n_split,
-                              float2* partial, float2* M, float2* out, int accumulate, hipStream_t st);
+                              float2* partial, float2* out, int accumulate, hipStream_t st);
 hipError_t launch_cheb_coef(const RenderGeom& g, const ChebPlan* plan, const MeasCheb* meas, const float2* sig,
                             float2* B, hipStream_t st);
 hipError_t launch_cheb_mf(const RenderGeom& g, const ChebPlan* plan, long n_q, const float* xq,
                           const AntRec* ant, const MeasCheb* meas, const float2* B, const float2* B2,
-                          float2* z, float* power, float2* z2, float* power2, hipStream_t st);
+                          float2* z, float* power, float2* z2, float* power2, int n_split, float2* part,
+                          hipStream_t st);
 hipError_t launch_cheb_render_bwd(const RenderGeom& g, uint32_t flags, const ChebPlan* plan, const AntRec* ant,
                                   const MeasCheb* meas, const PtRec* rec, const float2* B, float* g_b,
-                                  float* g_T, float* g_n, hipStream_t st);
+                                  float* g_T, float* g_n, int n_split, float* part, hipStream_t st);
 
 }  // namespace rfvr
