@@ -22,6 +22,7 @@
 // the tangent pass's adjoints from S (Zdot_bar = half_size S), so one adjoint
 // GEMM per layer remains.
 // Weight gradients reduce over points in fixed splits (no atomics).
+#include <algorithm>
 #include <mutex>
 
 #include "rfvr_impl.hpp"
@@ -1359,30 +1360,42 @@ __global__ __launch_bounds__(256, 2) void k_gemm_wg32(WgArgs g) {
     }
 }
 
-// dst[m][k] (row stride k_real, k < k_real) (+)= sum_s part[s][m][k]
-// fixed-order sum of partials t0 <= t < t1 with eight interleaved chains
-// (t mod 8), which keep eight loads in flight
+// dst[m][k] (row stride k_real, k < k_real) (+)= sum_{t < n1} part[t][m][k]
+//   + scale2 sum_{n1 <= t < n_split} part[t][m][k]
+// A work-group takes 64 outputs; its four waves sum every fourth split, with
+// eight interleaved chains that keep eight loads in flight, and the four sums are
+// added in order.  Bound by HBM (the partials are read once); one thread per
+// output instead left 256 of them per CU waiting on 96 loads each (2 x 384 splits
+// of 256 x 256: 57 -> 29 us).
 __device__ __forceinline__ float wg_chain_sum(const float* __restrict__ q, long stride, int t0, int t1) {
     float c[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
     int t = t0;
-    for (; t + 8 <= t1; t += 8) {
+    for (; t + 32 <= t1 + 3; t += 32) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) c[u] += q[(long)(t + u) * stride];
+        for (int u = 0; u < 8; ++u) c[u] += t + 4 * u < t1 ? q[(long)(t + 4 * u) * stride] : 0.0f;
     }
-    for (; t < t1; ++t) c[(t - t0) & 7] += q[(long)t * stride];
+    for (int u = 0; t < t1; t += 4, ++u) c[u & 7] += q[(long)t * stride];
     return ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
 }
 
-// dst (+)= sum_{t < n1} part[t] + scale2 sum_{n1 <= t < n_split} part[t]
-__global__ void k_wg_reduce(const float* __restrict__ part, int n_split, int n1, float scale2, int M, int Kout,
-                            int k_real, float* __restrict__ dst, int accumulate) {
-    const long o = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= (long)M * k_real) return;
-    const int m = (int)(o / k_real), k = (int)(o % k_real);
-    const long stride = (long)M * Kout;
-    const float* q = part + (long)m * Kout + k;
-    float s = wg_chain_sum(q, stride, 0, n1);
-    if (n1 < n_split) s = __builtin_fmaf(scale2, wg_chain_sum(q, stride, n1, n_split), s);
+__global__ __launch_bounds__(256) void k_wg_reduce(const float* __restrict__ part, int n_split, int n1, float scale2, int M,
+                                                   int Kout, int k_real, float* __restrict__ dst, int accumulate) {
+    __shared__ float sh[4][64];
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const long o = (long)blockIdx.x * 64 + lane;
+    const bool live = o < (long)M * k_real;
+    float s = 0.0f;
+    if (live) {
+        const int m = (int)(o / k_real), k = (int)(o % k_real);
+        const long stride = (long)M * Kout;
+        const float* q = part + (long)m * Kout + k;
+        s = wg_chain_sum(q, stride, wv, n1);
+        if (n1 < n_split) s = __builtin_fmaf(scale2, wg_chain_sum(q, stride, n1 + wv, n_split), s);
+    }
+    sh[wv][lane] = s;
+    __syncthreads();
+    if (wv != 0 || !live) return;
+    s = ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
     dst[o] = accumulate ? dst[o] + s : s;
 }
 
@@ -1391,26 +1404,34 @@ __global__ void k_wg_reduce(const float* __restrict__ part, int n_split, int n1,
 //   mode 0: X[p][m]      mode 1: s[p] relu(X[p][m])
 //   mode 3: s[p] X[p][m] + X2[p][m]   (s may be NULL)
 // ----------------------------------------------------------------------------
+// 256 / w threads share a column, w the columns rounded up to a power of two
 __global__ __launch_bounds__(256) void k_colsum_partial(const float* __restrict__ X,
                                                         const float* __restrict__ X2,
                                                         const float* __restrict__ s, long ldx,
-                                                        long P, int M, long rows_per, int mode,
+                                                        long P, int M, int w, long rows_per, int mode,
                                                         float beta, float* __restrict__ part) {
-    const int m = threadIdx.x;
-    if (m >= M) return;
+    __shared__ float sh[256];
+    const int m = threadIdx.x & (w - 1), step = 256 / w;
     const long rb = (long)blockIdx.x * rows_per;
     long re = rb + rows_per;
     if (re > P) re = P;
     float acc = 0.0f;
+    if (m < M) {
 #pragma unroll 8
-    for (long p = rb; p < re; ++p) {
-        const float x = X[p * ldx + m];
-        float d;
-        if (mode == 0) d = x;
-        else if (mode == 1) d = s[p] * fmaxf(x, 0.0f);
-        else d = (s ? s[p] * x : 0.0f) + X2[p * ldx + m];
-        acc += d;
+        for (long p = rb + threadIdx.x / w; p < re; p += step) {
+            const float x = X[p * ldx + m];
+            float d;
+            if (mode == 0) d = x;
+            else if (mode == 1) d = s[p] * fmaxf(x, 0.0f);
+            else d = (s ? s[p] * x : 0.0f) + X2[p * ldx + m];
+            acc += d;
+        }
     }
+    sh[threadIdx.x] = acc;
+    __syncthreads();
+    if (threadIdx.x >= M) return;
+    acc = sh[m];
+    for (int r = 1; r < step; ++r) acc += sh[r * w + m];
     part[(long)blockIdx.x * M + m] = acc;
 }
 
@@ -1644,10 +1665,17 @@ __global__ void k_prep_weights(PrepTable t) {
 namespace {
 
 constexpr long kChunk = 1 << 20;          // points per pass (bounds the workspace)
+// Weight-gradient point splits of a pass over P points: at most kWgSplits (three
+// rounds of the 512 work-groups that are resident, four tiles of a 256 x 256
+// gradient each), of at least 256 points each (a split writes and the reduction reads
+// its whole M x K partial: the training pair of 32768 points took 3.12 ms with 342
+// splits of 96 points, 2.45 with 128 of 256).  At 2^20 points 256 splits are equal
+// and 128 slower (one round of work-groups: 46.5, 46.3 and 47.7 ms).
 #ifndef RFVR_WG_SPLITS
 #define RFVR_WG_SPLITS 384
 #endif
-constexpr int kWgSplits = RFVR_WG_SPLITS; // weight-gradient point splits per pass
+constexpr int kWgSplits = RFVR_WG_SPLITS;
+int wg_splits(long P) { return (int)std::min<long>(kWgSplits, std::max<long>((P + 255) / 256, 1)); }
 constexpr int kColBlocks = 2048;          // column-sum partial blocks
 
 struct Layout {
@@ -1940,11 +1968,12 @@ void wgrad(const float* A, long lda, int M, const float* B, const float* B2, lon
     hipStream_t st = cx.st;
     WgArgs g;
     g.A = A; g.lda = lda; g.B = B; g.B2 = B2; g.ldb = ldb; g.part = part; g.bpart = bpart; g.P = P;
-    g.M = M; g.Kout = Kout; g.per_split = ((P + kWgSplits - 1) / kWgSplits + 31) / 32 * 32;
-    g.n_split = kWgSplits;
+    const int ns = wg_splits(P);
+    g.M = M; g.Kout = Kout; g.per_split = ((P + ns - 1) / ns + 31) / 32 * 32;
+    g.n_split = ns;
     g.beta = beta;
     const long tiles = (long)((M + 127) / 128) * ((Kout + 127) / 128);
-    const long groups = (kWgSplits + 7) / 8;
+    const long groups = (ns + 7) / 8;
     const dim3 grid((unsigned)(groups * 8 * tiles));
     if constexpr (ST != 0) {
         if (cx.mm == MM_BF16) {
@@ -1968,17 +1997,18 @@ void wgrad(const float* A, long lda, int M, const float* B, const float* B2, lon
 
 void wg_reduce(const float* part, int n_split, int M, int Kout, int k_real, float* dst, int acc,
                hipStream_t st, int n1 = -1, float scale2 = 1.0f) {
-    hipLaunchKernelGGL(k_wg_reduce, dim3(blocks((long)M * k_real)), dim3(256), 0, st, part, n_split,
+    hipLaunchKernelGGL(k_wg_reduce, dim3(blocks((long)M * k_real, 64)), dim3(256), 0, st, part, n_split,
                        n1 < 0 ? n_split : n1, scale2, M, Kout, k_real, dst, acc);
 }
 
 void colsum(const float* X, const float* X2, const float* s, long ldx, long P, int M, int mode,
             float beta, float scale, float* part, float* dst, int acc, hipStream_t st) {
-    const long per = (P + kColBlocks - 1) / kColBlocks;
-    hipLaunchKernelGGL(k_colsum_partial, dim3(kColBlocks), dim3(256), 0, st, X, X2, s, ldx, P, M, per,
-                       mode, beta, part);
-    hipLaunchKernelGGL(k_colsum_final, dim3(M), dim3(256), 0, st, part, kColBlocks, M, scale,
-                       dst, acc);
+    // at least 64 rows per work-group
+    const long nb = std::min<long>(kColBlocks, (P + 63) / 64), per = (P + nb - 1) / nb;
+    int w = 1;
+    while (w < M) w *= 2;
+    hipLaunchKernelGGL(k_colsum_partial, dim3((unsigned)nb), dim3(256), 0, st, X, X2, s, ldx, P, M, w, per, mode, beta, part);
+    hipLaunchKernelGGL(k_colsum_final, dim3(M), dim3(256), 0, st, part, (int)nb, M, scale, dst, acc);
 }
 
 // --- forward workspace -------------------------------------------------------
@@ -2233,6 +2263,7 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
     for (long c0 = 0; c0 < n; c0 += chunk) {
         const long m = (n - c0) < chunk ? (n - c0) : chunk;
         const int acc = (c0 > 0 || (flags & RFVR_ACCUMULATE)) ? 1 : 0;
+        const int ns = wg_splits(m);
         const float* x = xyz + 3 * c0;
         const float* gf = g_sdf ? g_sdf + c0 : nullptr;
         const float* ga_ = g_refl ? g_refl + c0 : nullptr;
@@ -2284,15 +2315,15 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
             float* Yb = Ybh[h];
             if (h > 0) {
                 wgrad<PRO_RELU>(Yb, l.HW, l.HW, Yh[h - 1], nullptr, l.HW, l.HW, m, beta, part, cx, bpart);
-                wg_reduce(part, kWgSplits, l.HW, l.HW, l.HW, GP + l.oWh[h], acc, st);
-                hipLaunchKernelGGL(k_colsum_final, dim3(l.HW), dim3(256), 0, st, bpart, kWgSplits, l.HW, 1.0f,
+                wg_reduce(part, ns, l.HW, l.HW, l.HW, GP + l.oWh[h], acc, st);
+                hipLaunchKernelGGL(k_colsum_final, dim3(l.HW), dim3(256), 0, st, bpart, ns, l.HW, 1.0f,
                                GP + l.obh[h], acc);
                 // Ybar_{h-1} = (Ybar_h Wh_h) . relu'(Y_{h-1})
                 gemm<PRO_ID, EPI_RELUMASK>(ga(Yb, l.HW, w.WhT[h], l.HW, nullptr, Ybh[h - 1], l.HW, m, l.HW, l.HW, beta, Yh[h - 1], l.HW), cx);
             } else {
                 wgrad<PRO_ID>(Yb, l.HW, l.HW, Ht, nullptr, l.W, l.W, m, beta, part, cx, bpart);
-                wg_reduce(part, kWgSplits, l.HW, l.W, l.W, GP + l.oWh[0], acc, st);
-                hipLaunchKernelGGL(k_colsum_final, dim3(l.HW), dim3(256), 0, st, bpart, kWgSplits, l.HW, 1.0f,
+                wg_reduce(part, ns, l.HW, l.W, l.W, GP + l.oWh[0], acc, st);
+                hipLaunchKernelGGL(k_colsum_final, dim3(l.HW), dim3(256), 0, st, bpart, ns, l.HW, 1.0f,
                                GP + l.obh[0], acc);
             }
         }
@@ -2333,7 +2364,7 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
                     (rc = hip_status(hipStreamWaitEvent(wst, side->ready[i], 0), "side event wait")))
                     return rc;
             }
-            float* part2 = part + (size_t)kWgSplits * l.W * finp;
+            float* part2 = part + (size_t)ns * l.W * finp;
             if (i == 0) {
                 if (b16) wgrad<PRO_ID, ST_A>(Zb, l.W, l.W, X0, nullptr, l.in0p, finp, m, beta, part, cx32w, bpart);
                 else wgrad<PRO_ID>(Zb, l.W, l.W, X0, nullptr, l.in0p, finp, m, beta, part, cx32w, bpart);
@@ -2345,8 +2376,8 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
                 wgrad<PRO_ID>(Zb, l.W, l.W, H[i - 1], nullptr, l.W, finp, m, beta, part, cxw, bpart);
                 wgrad<PRO_ID>(Zdb, l.W, l.W, Hd[i - 1], nullptr, l.W, finp, m, beta, part2, cxw);
             }
-            wg_reduce(part, 2 * kWgSplits, l.W, finp, fin, GP + l.oW[i], acc, wst, kWgSplits, kept ? half : 1.0f);
-            hipLaunchKernelGGL(k_colsum_final, dim3(l.W), dim3(256), 0, wst, bpart, kWgSplits, l.W, 1.0f,
+            wg_reduce(part, 2 * ns, l.W, finp, fin, GP + l.oW[i], acc, wst, ns, kept ? half : 1.0f);
+            hipLaunchKernelGGL(k_colsum_final, dim3(l.W), dim3(256), 0, wst, bpart, ns, l.W, 1.0f,
                                GP + l.ob[i], acc);
             if (side && (rc = hip_status(hipEventRecord(side->done[i], wst), "side event record"))) return rc;
             if (i > 0 && keep) {
@@ -2581,7 +2612,7 @@ static int proposal_pass(const rfvr_proposal* net, const float* xyz, int64_t n, 
     const float beta = 1.0f, inv_half = 1.0f / net->half_size;
     for (long c0 = 0; c0 < n; c0 += chunk) {
         const long m = (n - c0) < chunk ? (n - c0) : chunk;
-        const int acc = (c0 > 0 || (flags & RFVR_ACCUMULATE)) ? 1 : 0;
+        const int acc = (c0 > 0 || (flags & RFVR_ACCUMULATE)) ? 1 : 0, ns = wg_splits(m);
         hipLaunchKernelGGL(k_pe, dim3(blocks(m * l.in0p)), dim3(256), 0, st, m, xyz + 3 * c0, net->centre[0],
                            net->centre[1], net->centre[2], inv_half, l.L, l.in0p, X0, nullptr, nullptr);
         gemm<PRO_ID, EPI_BIAS>(ga(X0, l.in0p, Wp[0], l.in0p, P + l.ob[0], A[0], l.W, m, l.W, l.in0p, beta), cx);
@@ -2603,8 +2634,8 @@ static int proposal_pass(const rfvr_proposal* net, const float* xyz, int64_t n, 
                     wgrad<PRO_ID>(Ab, l.W, l.W, X0, nullptr, l.in0p, finp, m, beta, part, cx, bpart);
                 else
                     wgrad<PRO_RELU>(Ab, l.W, l.W, A[i - 1], nullptr, l.W, finp, m, beta, part, cx, bpart);
-                wg_reduce(part, kWgSplits, l.W, finp, fin, g_params + l.oW[i], acc, st);
-                hipLaunchKernelGGL(k_colsum_final, dim3(l.W), dim3(256), 0, st, bpart, kWgSplits, l.W, 1.0f,
+                wg_reduce(part, ns, l.W, finp, fin, g_params + l.oW[i], acc, st);
+                hipLaunchKernelGGL(k_colsum_final, dim3(l.W), dim3(256), 0, st, bpart, ns, l.W, 1.0f,
                                g_params + l.ob[i], acc);
                 if (i > 0) {
                     gemm<PRO_ID, EPI_RELUMASK>(ga(Ab, l.W, WT[i], l.W, nullptr, Ab2, l.W, m, l.W, l.W,
