@@ -161,11 +161,34 @@ struct ChebWs {
     MeasCheb* meas;
 };
 
+// Cells of a large launch: rec_bytes per point for the sorted records of a
+// reduction over points, or 0 for the permutation of one over frequencies.
+static size_t ws_cells(long n_pts, int n_meas, size_t rec_bytes) {
+    const int nc = cell_count(n_pts, n_meas, rec_bytes != 0);
+    if (!nc) return 0;
+    return align256(sizeof(CellGrid)) + align256(sizeof(CellIndex)) + align256(sizeof(int) * nc * (size_t)cell_waves(n_pts)) +
+           align256((rec_bytes ? rec_bytes : sizeof(int)) * (size_t)n_pts);
+}
+
+static CellWs take_cells(WsCursor& cur, long n_pts, int n_meas, size_t rec_bytes) {
+    CellWs w = {};
+    const int nc = cell_count(n_pts, n_meas, rec_bytes != 0);
+    if (!nc) return w;
+    w.max_cells = nc;
+    w.grid = cur.take<CellGrid>(1);
+    w.cells = cur.take<CellIndex>(1);
+    w.hist = cur.take<int>(nc * (size_t)cell_waves(n_pts));
+    if (rec_bytes) w.sorted = cur.take<char>(rec_bytes * (size_t)n_pts);
+    else w.perm = cur.take<int>((size_t)n_pts);
+    return w;
+}
+
 static int build_plan(const rfvr_aperture* ap, const rfvr_fields* fl, const float* xyz, long n, AntRec* ant, AntRec* rxa,
-                      RenderGeom& g, const ChebWs& cw, hipStream_t st) {
+                      RenderGeom& g, const ChebWs& cw, const CellWs& cells, hipStream_t st) {
     g.rxa = rxa;
     return hip_status(launch_cheb_plan(xyz, n, ap->tx, fl ? fl->phi_tx : nullptr, ap->rx, fl ? fl->phi_rx : nullptr, ant,
-                                       rxa, ap->n_meas, g.Kd, ap->n_freq, cw.bbox, cw.meas, cw.plan, st),
+                                       rxa, ap->n_meas, g.Kd, ap->n_freq, cw.bbox, cw.meas, cw.plan, cells.grid,
+                                       cells.max_cells, st),
                       "term plan");
 }
 
@@ -178,10 +201,11 @@ static ChebWs take_cheb(WsCursor& cur, long n_pts, int n_meas) {
 }
 
 // split partials of a reduction over points: per-frequency [ns][meas][freq]
-// or moments [ns][meas][kChebMaxOrder] (only one of the two runs)
+// or moments [splits or cell units][meas][kChebMaxOrder] (only one of the two runs)
 static size_t partial_count(long n_pts, int n_meas, int n_freq, int ns_direct) {
     const size_t d = (size_t)ns_direct * n_meas * n_freq;
-    const size_t c = (size_t)cheb_point_splits(n_pts, n_meas) * n_meas * kChebMaxOrder;
+    const size_t units = std::max(cheb_point_splits(n_pts, n_meas), cell_point_units(n_pts, n_meas));
+    const size_t c = units * n_meas * kChebMaxOrder;
     return d > c ? d : c;
 }
 
@@ -192,7 +216,8 @@ static size_t ant_bytes(int n_meas, bool bi) { return (bi ? 2 : 1) * align256(si
 static size_t ws_render_forward(const RenderGeom& g) {
     const int ns = render_splits(g);
     return ant_bytes(g.n_meas, g.bi) + align256(sizeof(PtRec) * g.n_pts) +
-           align256(sizeof(float2) * partial_count(g.n_pts, g.n_meas, g.n_freq, ns)) + ws_cheb(g.n_pts, g.n_meas);
+           align256(sizeof(float2) * partial_count(g.n_pts, g.n_meas, g.n_freq, ns)) + ws_cheb(g.n_pts, g.n_meas) +
+           ws_cells(g.n_pts, g.n_meas, sizeof(PtRec));
 }
 
 static size_t bwd_part_bytes(long n_pts, int n_meas) {
@@ -209,11 +234,12 @@ static size_t ws_render_backward(const RenderGeom& g) {
            align256(sizeof(float2) * g.n_meas * np) +            // padded g_signal
            2 * align256(sizeof(float) * g.n_ray) +               // per-ray partials
            bwd_part_bytes(g.n_pts, g.n_meas) +                   // sums of the measurement splits
-           align256(sizeof(float2) * (size_t)g.n_meas * kChebMaxOrder) + ws_cheb(g.n_pts, g.n_meas);
+           align256(sizeof(float2) * (size_t)g.n_meas * kChebMaxOrder) + ws_cheb(g.n_pts, g.n_meas) +
+           ws_cells(g.n_pts, g.n_meas, 0);
 }
 
-// what the filter forward cannot do without; its query adds the sums of the
-// measurement splits, of which a call takes as many as its workspace holds
+// what the filter forward cannot do without; its query adds the cells, and the
+// sums of the measurement splits: a call uses what its workspace has room for
 static size_t ws_mf_forward(const rfvr_aperture* ap, long n_q, int two) {
     const size_t np = padded_freq(ap->n_freq);
     return ant_bytes(ap->n_meas, ap->rx != nullptr) +
@@ -226,7 +252,7 @@ static size_t mf_part_bytes(long n_q, int two) { return align256(sizeof(float2) 
 
 static size_t ws_mf_forward_full(const rfvr_aperture* ap, long n_q, int two) {
     const int ns = cheb_meas_splits(n_q, ap->n_meas);
-    return ws_mf_forward(ap, n_q, two) + (ns > 1 ? ns * mf_part_bytes(n_q, two) : 0);
+    return ws_mf_forward(ap, n_q, two) + ws_cells(n_q, ap->n_meas, 0) + (ns > 1 ? ns * mf_part_bytes(n_q, two) : 0);
 }
 
 static int mf_splits(const rfvr_aperture* ap, long n_q) {
@@ -237,7 +263,8 @@ static int mf_splits(const rfvr_aperture* ap, long n_q) {
 static size_t ws_mf_backward(const rfvr_aperture* ap, long n_q) {
     const int ns = mf_splits(ap, n_q);
     return ant_bytes(ap->n_meas, ap->rx != nullptr) + align256(sizeof(QRec) * n_q) +
-           align256(sizeof(float2) * partial_count(n_q, ap->n_meas, ap->n_freq, ns)) + ws_cheb(n_q, ap->n_meas);
+           align256(sizeof(float2) * partial_count(n_q, ap->n_meas, ap->n_freq, ns)) + ws_cheb(n_q, ap->n_meas) +
+           ws_cells(n_q, ap->n_meas, sizeof(QRec));
 }
 
 static int loss_blocks(long n) {
@@ -324,9 +351,10 @@ int rfvr_render_forward(const rfvr_aperture* ap, const rfvr_samples* sm, const r
     const int ns = render_splits(g);
     float2* partial = cur.take<float2>(partial_count(g.n_pts, g.n_meas, g.n_freq, ns));
     const ChebWs cw = take_cheb(cur, g.n_pts, g.n_meas);
+    const CellWs cells = take_cells(cur, g.n_pts, g.n_meas, sizeof(PtRec));
     const int use_phi = (fl->phi_ray && fl->phi_tx) ? 1 : 0;
     const bool cheb = use_cheb(flags);
-    if ((rc = cheb ? build_plan(ap, use_phi ? fl : nullptr, sm->xyz, g.n_pts, ant, rxa, g, cw, st)
+    if ((rc = cheb ? build_plan(ap, use_phi ? fl : nullptr, sm->xyz, g.n_pts, ant, rxa, g, cw, cells, st)
                    : build_ant_records(ap, use_phi ? fl : nullptr, ant, rxa, g, st)))
         return rc;
     if ((rc = hip_status(launch_render_prep(g, sm->xyz, sm->ray_weight, sm->point_weight, fl->sdf, fl->grad, fl->refl,
@@ -339,7 +367,7 @@ int rfvr_render_forward(const rfvr_aperture* ap, const rfvr_samples* sm, const r
         sel = cw.plan;
         if ((rc = hip_status(launch_cheb_points(g, 0, flags, ant, cw.meas, cw.plan, rec,
                                                 cheb_point_splits(g.n_pts, g.n_meas), partial,
-                                                reinterpret_cast<float2*>(signal), 0, st),
+                                                reinterpret_cast<float2*>(signal), 0, cells, st),
                              "render moment kernels")))
             return rc;
     }
@@ -390,9 +418,10 @@ int rfvr_render_backward(const rfvr_aperture* ap, const rfvr_samples* sm, const 
     float* part = ns > 1 ? cur.take<float>(5 * ns * (size_t)g.n_pts) : nullptr;
     float2* B = cur.take<float2>((size_t)g.n_meas * kChebMaxOrder);
     const ChebWs cw = take_cheb(cur, g.n_pts, g.n_meas);
+    const CellWs cells = take_cells(cur, g.n_pts, g.n_meas, 0);
     const int use_phi = (fl->phi_ray && fl->phi_tx) ? 1 : 0;
     const bool cheb = use_cheb(flags);
-    if ((rc = cheb ? build_plan(ap, use_phi ? fl : nullptr, sm->xyz, g.n_pts, ant, rxa, g, cw, st)
+    if ((rc = cheb ? build_plan(ap, use_phi ? fl : nullptr, sm->xyz, g.n_pts, ant, rxa, g, cw, cells, st)
                    : build_ant_records(ap, use_phi ? fl : nullptr, ant, rxa, g, st)))
         return rc;
     if ((rc = hip_status(launch_render_prep(g, sm->xyz, sm->ray_weight, nullptr, fl->sdf, fl->grad, fl->refl,
@@ -411,7 +440,7 @@ int rfvr_render_backward(const rfvr_aperture* ap, const rfvr_samples* sm, const 
         if ((rc = hip_status(launch_cheb_coef(g, cw.plan, cw.meas, reinterpret_cast<const float2*>(g_signal), B,
                                               st), "render adjoint coefficients")))
             return rc;
-        if ((rc = hip_status(launch_cheb_render_bwd(g, flags, cw.plan, ant, cw.meas, rec, B, gb, gT, gn, ns, part, st),
+        if ((rc = hip_status(launch_cheb_render_bwd(g, flags, cw.plan, ant, cw.meas, rec, B, gb, gT, gn, ns, part, cells, st),
                              "render adjoint series kernels")))
             return rc;
     }
@@ -458,8 +487,10 @@ int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, ui
     float2* B = cur.take<float2>((size_t)ap->n_meas * kChebMaxOrder);
     float2* B2 = two ? cur.take<float2>((size_t)ap->n_meas * kChebMaxOrder) : nullptr;
     const ChebWs cw = take_cheb(cur, (long)n_q, ap->n_meas);
+    CellWs cells = {};
+    if (ws_cells((long)n_q, ap->n_meas, 0) <= ws_bytes - cur.used) cells = take_cells(cur, (long)n_q, ap->n_meas, 0);
     const bool cheb = use_cheb(flags);
-    if ((rc = cheb ? build_plan(ap, nullptr, xyz_q, (long)n_q, ant, rxa, g, cw, st)
+    if ((rc = cheb ? build_plan(ap, nullptr, xyz_q, (long)n_q, ant, rxa, g, cw, cells, st)
                    : build_ant_records(ap, nullptr, ant, rxa, g, st)))
         return rc;
     const float2 *ps = reinterpret_cast<const float2*>(signal), *ps2 = reinterpret_cast<const float2*>(signal2);
@@ -484,7 +515,7 @@ int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, ui
             return rc;
         if ((rc = hip_status(launch_cheb_mf(g, cw.plan, (long)n_q, xyz_q, ant, cw.meas, B, B2,
                                             reinterpret_cast<float2*>(z), power, reinterpret_cast<float2*>(z2),
-                                            power2, ns, reinterpret_cast<float2*>(cur.base + cur.used), st),
+                                            power2, ns, reinterpret_cast<float2*>(cur.base + cur.used), cells, st),
                              "mf series kernels")))
             return rc;
     }
@@ -541,7 +572,8 @@ int rfvr_mf_backward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, c
     const ChebWs cw = take_cheb(cur, (long)n_q, ap->n_meas);
     const int acc = (flags & RFVR_ACCUMULATE) ? 1 : 0;
     const bool cheb = use_cheb(flags);
-    if ((rc = cheb ? build_plan(ap, nullptr, xyz_q, (long)n_q, ant, rxa, g, cw, st)
+    const CellWs cells = take_cells(cur, (long)n_q, ap->n_meas, sizeof(QRec));
+    if ((rc = cheb ? build_plan(ap, nullptr, xyz_q, (long)n_q, ant, rxa, g, cw, cells, st)
                    : build_ant_records(ap, nullptr, ant, rxa, g, st)))
         return rc;
     if ((rc = hip_status(launch_mf_bwd_records(xyz_q, (long)n_q, reinterpret_cast<const float2*>(z),
@@ -552,7 +584,7 @@ int rfvr_mf_backward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, c
         sel = cw.plan;
         if ((rc = hip_status(launch_cheb_points(g, 1, flags, ant, cw.meas, cw.plan, rec,
                                                 cheb_point_splits((long)n_q, ap->n_meas), partial,
-                                                reinterpret_cast<float2*>(g_signal), acc, st),
+                                                reinterpret_cast<float2*>(g_signal), acc, cells, st),
                              "mf adjoint moment kernels")))
             return rc;
     }
@@ -583,7 +615,7 @@ int rfvr_term_order(const rfvr_aperture* ap, const float* xyz, int64_t n_pts, in
     AntRec* ant = cur.take<AntRec>(ap->n_meas);
     AntRec* rxa = g.bi ? cur.take<AntRec>(ap->n_meas) : nullptr;
     const ChebWs cw = take_cheb(cur, (long)n_pts, ap->n_meas);
-    if ((rc = build_plan(ap, nullptr, xyz, (long)n_pts, ant, rxa, g, cw, st))) return rc;
+    if ((rc = build_plan(ap, nullptr, xyz, (long)n_pts, ant, rxa, g, cw, CellWs{}, st))) return rc;
     return hip_status(launch_cheb_order(cw.plan, order, st), "term order");
 }
 

@@ -314,8 +314,30 @@ struct alignas(16) MeasCheb {
     double rc, h, inv_h, pad;
 };
 struct alignas(16) ChebPlan {
-    int K, pad;
+    int K;        // order over the launch's box, 0: the per-frequency kernels
+    int KC;       // order over a cell (its kernels run in place of the box's), 0: no cells
     double zmax;
+};
+// Cells of a large launch's box: n[0] x n[1] x n[2] of edges w from lo on.
+constexpr int kMaxCells = 512;
+struct CellGrid {
+    double lo[3], w[3];
+    float inv_w[3];
+    int n[3], n_cells;
+};
+// The sorted points: cell c holds positions [start[c], start[c+1]) and units
+// [unit[c], unit[c+1]).
+struct CellIndex {
+    int total[kMaxCells], start[kMaxCells + 1], unit[kMaxCells + 1], n_cells;
+};
+// workspace of the cells (grid NULL and max_cells 0: none)
+struct CellWs {
+    int max_cells;
+    CellGrid* grid;
+    CellIndex* cells;
+    int* hist;      // [cell][wave]
+    int* perm;      // reductions over frequencies: the point at a position
+    void* sorted;   // reductions over points: its record
 };
 
 // Launchers (render.hip)
@@ -399,19 +421,24 @@ hipError_t launch_cheb_order(const ChebPlan* plan, int32_t* order, hipStream_t s
 // also writes the measurement records ant (and rxa of a bistatic aperture)
 hipError_t launch_cheb_plan(const float* xyz, long n, const float* tx, const float* phi_tx, const float* rx,
                             const float* phi_rx, AntRec* ant, AntRec* rxa, int n_meas, double Kd, int n_freq,
-                            float* bbox_part, MeasCheb* meas, ChebPlan* plan, hipStream_t st);
+                            float* bbox_part, MeasCheb* meas, ChebPlan* plan, CellGrid* grid, int max_cells, hipStream_t st);
+// cells of a launch (0: none), waves of their sort, and the most units of a point reduction
+int cell_count(long n_pts, int n_meas, bool over_points);
+int cell_waves(long n);
+int cell_point_units(long n_pts, int n_meas);
 int cheb_meas_splits(long n_pts, int n_meas);
 hipError_t launch_cheb_points(const RenderGeom& g, int kind, uint32_t flags, const AntRec* ant,
                               const MeasCheb* meas, const ChebPlan* plan, const void* rec, int n_split,
-                              float2* partial, float2* out, int accumulate, hipStream_t st);
+                              float2* partial, float2* out, int accumulate, const CellWs& cw, hipStream_t st);
 hipError_t launch_cheb_coef(const RenderGeom& g, const ChebPlan* plan, const MeasCheb* meas, const float2* sig,
                             float2* B, hipStream_t st);
 hipError_t launch_cheb_mf(const RenderGeom& g, const ChebPlan* plan, long n_q, const float* xq,
                           const AntRec* ant, const MeasCheb* meas, const float2* B, const float2* B2,
                           float2* z, float* power, float2* z2, float* power2, int n_split, float2* part,
-                          hipStream_t st);
+                          const CellWs& cw, hipStream_t st);
 hipError_t launch_cheb_render_bwd(const RenderGeom& g, uint32_t flags, const ChebPlan* plan, const AntRec* ant,
                                   const MeasCheb* meas, const PtRec* rec, const float2* B, float* g_b,
-                                  float* g_T, float* g_n, int n_split, float* part, hipStream_t st);
+                                  float* g_T, float* g_n, int n_split, float* part, const CellWs& cw,
+                                  hipStream_t st);
 
 }  // namespace rfvr
