@@ -89,3 +89,32 @@ def test_nan_stays_in_its_row():
         assert torch.equal(w[keep], v[keep])
     # f and grad_x f carry it; the head's relu (fmaxf) does not
     assert bool(torch.isnan(got[0][77])) and bool(torch.isnan(got[1][77]).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,octaves,layers,shift", [(1, 0, 1, 0), (15, 5, 2, 1), (17, 4, 2, 0), (31, 2, 2, 2), (33, 5, 1, 3),
+                                                    (64, 4, 2, 0), (65, 3, 2, 1), (129, 5, 2, 0)])
+def test_narrow_products_match_oracle(n, octaves, layers, shift):
+    """The proposal network's 64 x 64 and 64 x 32 weight gradients (64 x 64 tiles), encoding and ReLU adjoint around
+    their 32- and 64-point chunks and 16-row groups, with parameters at any 4-byte alignment.  Tolerance: three
+    passes over at most 64 FP32 terms, and the encoding's rounding as above."""
+    from paper_2605_29097_amd import rfvr as R
+    from oracle import proposal as op
+    from synth import ProposalSpec, proposal_init
+    spec = ProposalSpec(pe_octaves=octaves, layers=layers)
+    rng = np.random.default_rng(n)
+    p = (proposal_init(spec, 3) + 0.1 * rng.normal(size=proposal_init(spec, 3).shape)).astype(np.float32)
+    x = (np.array(spec.centre) + rng.uniform(-1.0, 1.0, (n, 3)) * spec.half_size).astype(np.float32)
+    g = rng.normal(size=n).astype(np.float32)
+    buf = torch.zeros(p.size + 4, device="cuda")
+    buf[shift:shift + p.size] = torch.from_numpy(p).cuda()
+    m = R.Proposal(params=buf[shift:shift + p.size], pe_octaves=octaves, width=spec.width, layers=layers,
+                   centre=spec.centre, half_size=spec.half_size)
+    xt, gt = torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda()
+    p64 = p.astype(np.float64)
+    z = R.proposal_forward(m, xt).cpu()
+    gp = R.proposal_backward(m, xt, gt).cpu()
+    pe = 2.0 ** -24 * np.pi * 2.0 ** octaves
+    errs = [rel(z, op.forward(p64, spec, x.astype(np.float64))),
+            rel(gp, op.backward(p64, spec, x.astype(np.float64), g.astype(np.float64)))]
+    assert max(errs) < 3 * 2.0 ** -24 * 8 + pe, errs
