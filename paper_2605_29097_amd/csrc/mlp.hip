@@ -62,32 +62,24 @@ __device__ __forceinline__ void split_f16x8(floatx4 lo, floatx4 hi, f16x8& big, 
     }
 }
 
-// x = big + small with big = bf16(x), small = bf16(x - big): 16 significant bits
-__device__ __forceinline__ void split_bf16x8(floatx4 lo, floatx4 hi, bf16x8& big, bf16x8& small) {
-    big = to_bf16x8(lo, hi);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        small[e] = (__bf16)(lo[e] - (float)big[e]);
-        small[4 + e] = (__bf16)(hi[e] - (float)big[4 + e]);
-    }
-}
-
 // x = p[0] + p[1] + p[2], each BF16 (RNE): the first two remainders are exact in
 // FP32 and the third has at most 8 significant bits, so the three parts hold all
-// 24 bits of x (down to where the parts leave BF16's normal range, |x| ~ 1e-33)
+// 24 bits of x (down to where the parts leave BF16's normal range, |x| ~ 1e-33);
+// the first two alone hold 16
 // (two values per conversion instruction: 11 VALU instructions a pair)
 __device__ __forceinline__ uint32_t pk_bf16(float x, float y) {
     typedef float f2 __attribute__((ext_vector_type(2)));
     typedef __bf16 b2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x, y}, b2));
 }
-__device__ __forceinline__ void split3_bf16x8(floatx4 lo, floatx4 hi, bf16x8 p[3]) {
-    uintx4 w[3];
+template <int N>
+__device__ __forceinline__ void split_bf16x8(floatx4 lo, floatx4 hi, bf16x8 (&p)[N]) {
+    uintx4 w[N];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         float x = e < 2 ? lo[2 * e] : hi[2 * e - 4], y = e < 2 ? lo[2 * e + 1] : hi[2 * e - 3];
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
+        for (int q = 0; q < N; ++q) {
             const uint32_t b = pk_bf16(x, y);
             w[q][e] = b;
             x -= __uint_as_float(b << 16);
@@ -95,24 +87,34 @@ __device__ __forceinline__ void split3_bf16x8(floatx4 lo, floatx4 hi, bf16x8 p[3
         }
     }
 #pragma unroll
-    for (int q = 0; q < 3; ++q) p[q] = __builtin_bit_cast(bf16x8, w[q]);
+    for (int q = 0; q < N; ++q) p[q] = __builtin_bit_cast(bf16x8, w[q]);
 }
 
-// An FP32 product of one 16 x 16 tile over 32 k from operands split in three:
-// the six part products down to 2^-16 of the leading one (the three left out
-// are below 2^-25 of it), smallest first.  TM tiles share a point fragment, so
-// that consecutive MFMAs are independent.
-template <int TM>
-__device__ __forceinline__ void mfma_split3(const bf16x8 (&w)[TM][3], const bf16x8 (&a)[3], floatx4* acc,
-                                            bool points_first) {
-    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+// A product of one 16 x 16 tile over 32 k from operands split in N parts, smallest
+// terms first: in three (FP32), the six part products down to 2^-16 of the leading
+// one (the three left out are below 2^-25 of it); in two (BF16X3), three.  TM tiles
+// share a point fragment, so that consecutive MFMAs are independent.
+template <int N, int TM>
+__device__ __forceinline__ void mfma_split(const bf16x8 (&w)[TM][N], const bf16x8 (&a)[N], floatx4* acc,
+                                           bool points_first) {
+    constexpr int NP = N == 3 ? 6 : 3;
+    constexpr int PA[6] = {N - 1, 0, N == 3 ? 1 : 0, 1, 0, 0}, PB[6] = {0, N - 1, N == 3 ? 1 : 0, 0, 1, 0};
 #pragma unroll
-    for (int q = 0; q < 6; ++q)
+    for (int q = 0; q < NP; ++q)
 #pragma unroll
         for (int b = 0; b < TM; ++b)
             acc[b] = points_first ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[PA[q]], w[b][PB[q]], acc[b], 0, 0, 0)
                                   : __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b][PB[q]], a[PA[q]], acc[b], 0, 0, 0);
 }
+
+// The k of a 32-wide chunk that lane group kg multiplies: kg split_k0 .. + 3 and those
+// split_k1 further on.  In three parts eight in a row (a row's chunk is read 128
+// bytes at a time).  In two, four of either half, as the single-rounded kernels
+// have it: the matrix core adds its k in groups, BF16X3's split rounds the
+// activations to 16 bits, and another order moved some across a rounding
+// (1e-5 in the gradients).
+__host__ __device__ constexpr int split_k0(int parts) { return parts == 3 ? 8 : 4; }
+__host__ __device__ constexpr int split_k1(int parts) { return parts == 3 ? 4 : 16; }
 
 // BF16 storage of the single-rounded BF16 backward's arrays (tangents Hdot and
 // adjoints Zbar): the BF16 products that read them round them to BF16 (RNE)
@@ -218,7 +220,7 @@ __host__ __device__ constexpr int block_rows(int M) { return M <= 64 ? 64 : 128;
 struct GemmArgs {
     const float* A; long lda;
     const float* B; long ldb;
-    const uint16_t* Bx;           // FP32: the split image of B (k_prep_split)
+    const uint16_t* Bx;           // split products: the image of B (k_prep_weights)
     const float* bias;            // EPI_BIAS*: [M] or null
     const float* C;               // EPI_RELUMASK / DSPMUL / TOPADJ: [P][ldc]
     const float* C2;              // EPI_TOPADJ, ADJ1: [P][ldc]
@@ -519,28 +521,6 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g) {
                     acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bf[b], ab, acc[a][b], 0, 0, 0);
                 }
             }
-        } else if constexpr (MM == MM_BF16X3) {
-            bf16x8 ab[TP], as[TP], bb[TM], bs[TM];
-#pragma unroll
-            for (int a = 0; a < TP; ++a) {
-                const int row = wp * (BP / WP) + a * 16 + li;
-                split_bf16x8(*reinterpret_cast<const floatx4*>(&A_[off(row, lg)]),
-                             *reinterpret_cast<const floatx4*>(&A_[off(row, lg + 4)]), ab[a], as[a]);
-            }
-#pragma unroll
-            for (int b = 0; b < TM; ++b) {
-                const int row = wm * (BM / WM) + b * 16 + li;
-                split_bf16x8(*reinterpret_cast<const floatx4*>(&B_[off(row, lg)]),
-                             *reinterpret_cast<const floatx4*>(&B_[off(row, lg + 4)]), bb[b], bs[b]);
-            }
-#pragma unroll
-            for (int a = 0; a < TP; ++a)
-#pragma unroll
-                for (int b = 0; b < TM; ++b) {
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bb[b], as[a], acc[a][b], 0, 0, 0);
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bs[b], ab[a], acc[a][b], 0, 0, 0);
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bb[b], ab[a], acc[a][b], 0, 0, 0);
-                }
         } else {
 #pragma unroll
             for (int kk = 0; kk < BK; kk += 16) {
@@ -576,9 +556,9 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g) {
 
 // ----------------------------------------------------------------------------
 // The same product in FP32: every operand split in three BF16 parts
-// (mfma_split3), because six BF16 MFMAs over 32 k take 96 cycles of a SIMD's
+// (mfma_split), because six BF16 MFMAs over 32 k take 96 cycles of a SIMD's
 // matrix core where the FP32 instruction takes 256.  The per-point operand is split once, on
-// its way into LDS; the weights come split from k_prep_split.  Both lie in LDS in
+// its way into LDS; the weights come split from k_prep_weights.  Both lie in LDS in
 // fragment order: [part][16-row tile][slot][8 k], a lane's 16 bytes of a
 // fragment in one ds_read_b128 and a wave's in one linear kilobyte.  The store
 // side has four lanes on a row (32 bytes of k each, for coalesced global loads);
@@ -590,21 +570,27 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g) {
 // (4.7 TB/s) is not hidden behind it.  Tried and slower: persistent work-groups
 // that fetch the next tile's first chunk and their epilogue's operands early
 // (training pair 45.4 -> 49.3 ms).
+// N = 2 is BF16X3 on the same kernel: two parts of the same image, three products.
+// Its former kernels split both operands in registers once per wave that read them
+// (150001 x 256 x 256: softplus layer 130 -> 104 us, sp'(Z) product 151 -> 131, dual
+// forward 288 -> 240, dual adjoint 323 -> 275, a layer's weight gradients 226 -> 203);
+// now bound by HBM and the epilogue, as above.
 // ----------------------------------------------------------------------------
 __device__ __forceinline__ int frag_slot(int row, int kg) { return kg * 16 + (row ^ (kg * 2)); }
 
 // T x T tiles; HB output tiles of a wave are multiplied at a time: with two,
 // three waves fit on a SIMD (all four, at two waves, read less LDS: better
 // where no third work-group would come to the CU anyway).
-template <int PRO, int EPI, int T, int HB>
+template <int PRO, int EPI, int T, int HB, int N = 3>
 __global__ __launch_bounds__(256, T != 128 ? 4 : (HB == 4 || EPI == EPI_TOPADJ) ? 2 : 3) void k_gemm_nt32(GemmArgs g) {
     constexpr int BP = T, BM = T, BK = 32, WP = 2, WM = 2;
     constexpr int TP = BP / WP / 16, TM = BM / WM / 16;
     constexpr int FT = 64 * 8;                   // 16-bit words of one tile of one part
     constexpr int NA = BP / 64;                  // 8-k pieces of the point chunk per thread
-    constexpr int NBV = 3 * BM * BK / 8 / 256;   // 16-byte vectors of the weight chunk per thread
-    __shared__ __align__(16) uint16_t sA[3 * (BP / 16) * FT];
-    __shared__ __align__(16) uint16_t sB[3 * (BM / 16) * FT];
+    constexpr int K0 = split_k0(N), K1 = split_k1(N);
+    constexpr int NBV = N * BM * BK / 8 / 256;   // 16-byte vectors of the weight chunk per thread
+    __shared__ __align__(16) uint16_t sA[N * (BP / 16) * FT];
+    __shared__ __align__(16) uint16_t sB[N * (BM / 16) * FT];
     const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
     const int wp = wv % WP, wm = wv / WP;
     const int li = lane & 15, lg = lane >> 4;
@@ -635,9 +621,9 @@ __global__ __launch_bounds__(256, T != 128 ? 4 : (HB == 4 || EPI == EPI_TOPADJ) 
             const int u = tid + i * 256;
             // rows beyond the last point repeat it: their products are not stored
             const long p = min(p0 + (u >> 2), g.P - 1);
-            const floatx4* q = reinterpret_cast<const floatx4*>(g.A + p * g.lda + kc * BK + (u & 3) * 8);
+            const floatx4* q = reinterpret_cast<const floatx4*>(g.A + p * g.lda + kc * BK + (u & 3) * K0);
             ra[i][0] = q[0];
-            ra[i][1] = q[1];
+            ra[i][1] = q[K1 / 4];
         }
 #pragma unroll
         for (int i = 0; i < NBV; ++i) {
@@ -656,12 +642,12 @@ __global__ __launch_bounds__(256, T != 128 ? 4 : (HB == 4 || EPI == EPI_TOPADJ) 
                 for (int e = 0; e < 4; ++e) {
                     if constexpr (PRO == PRO_RELU) ra[i][h][e] = fmaxf(ra[i][h][e], 0.0f);
                     if constexpr (PRO == PRO_SEED)
-                        ra[i][h][e] = sp_d1_h(ra[i][h][e], g.beta) * g.colv[kc * BK + kg * 8 + h * 4 + e];
+                        ra[i][h][e] = sp_d1_h(ra[i][h][e], g.beta) * g.colv[kc * BK + kg * K0 + h * K1 + e];
                 }
-            bf16x8 part[3];
-            split3_bf16x8(ra[i][0], ra[i][1], part);
+            bf16x8 part[N];
+            split_bf16x8(ra[i][0], ra[i][1], part);
 #pragma unroll
-            for (int q = 0; q < 3; ++q)
+            for (int q = 0; q < N; ++q)
                 *reinterpret_cast<bf16x8*>(&sA[(q * (BP / 16) + (row >> 4)) * FT + frag_slot(row & 15, kg) * 8]) = part[q];
         }
 #pragma unroll
@@ -674,19 +660,19 @@ __global__ __launch_bounds__(256, T != 128 ? 4 : (HB == 4 || EPI == EPI_TOPADJ) 
         if (kc + 1 < nk) load(kc + 1);
 #pragma unroll
         for (int h = 0; h < TM; h += HB) {
-            bf16x8 wf[HB][3];
+            bf16x8 wf[HB][N];
 #pragma unroll
             for (int b = 0; b < HB; ++b)
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
+                for (int q = 0; q < N; ++q)
                     wf[b][q] = *reinterpret_cast<const bf16x8*>(&sB[(q * (BM / 16) + wm * TM + h + b) * FT + lane * 8]);
 #pragma unroll
             for (int a = 0; a < TP; ++a) {
-                bf16x8 af[3];
+                bf16x8 af[N];
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
+                for (int q = 0; q < N; ++q)
                     af[q] = *reinterpret_cast<const bf16x8*>(&sA[(q * (BP / 16) + wp * TP + a) * FT + frag_slot(li, lg) * 8]);
-                mfma_split3<HB>(wf, af, &acc[a][h], false);
+                mfma_split<N, HB>(wf, af, &acc[a][h], false);
                 if constexpr (HB < TM) __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -710,7 +696,7 @@ enum { EPI2_FWD = 0, EPI2_ADJ = 1 };
 struct DualArgs {
     const float* A; const float* A2; long lda;
     const float* B; long ldb;
-    const uint16_t* Bx;                     // FP32: the split image of B (k_prep_split)
+    const uint16_t* Bx;                     // split products: the image of B (k_prep_weights)
     const float* bias;
     const float* C; const float* C2;        // EPI2_ADJ: [P][ldy]
     float* Y; float* Y2; float* Y3; long ldy;
@@ -904,14 +890,11 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_gemm_dual(DualArgs
                 }
             }
         } else {
-            bf16x8 bb[TM], bs[TM];
+            bf16x8 bb[TM];
 #pragma unroll
             for (int b = 0; b < TM; ++b) {
                 const float* r = &sB[(wm * (BM / 2) + b * 16 + li) * LW + lg * 4];
-                if constexpr (MM == MM_BF16)
-                    bb[b] = to_bf16x8(*reinterpret_cast<const floatx4*>(r), *reinterpret_cast<const floatx4*>(r + 16));
-                else
-                    split_bf16x8(*reinterpret_cast<const floatx4*>(r), *reinterpret_cast<const floatx4*>(r + 16), bb[b], bs[b]);
+                bb[b] = to_bf16x8(*reinterpret_cast<const floatx4*>(r), *reinterpret_cast<const floatx4*>(r + 16));
             }
 #pragma unroll
             for (int a = 0; a < TP; ++a) {
@@ -920,21 +903,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_gemm_dual(DualArgs
                 for (int which = 0; which < 2; ++which) {
                     const float* r = which ? &sA2[off] : &sA[off];
                     floatx4* dst = which ? acd[a] : acc[a];
-                    if constexpr (MM == MM_BF16) {
-                        const bf16x8 ab = to_bf16x8(*reinterpret_cast<const floatx4*>(r), *reinterpret_cast<const floatx4*>(r + 16));
+                    const bf16x8 ab = to_bf16x8(*reinterpret_cast<const floatx4*>(r), *reinterpret_cast<const floatx4*>(r + 16));
 #pragma unroll
-                        for (int b = 0; b < TM; ++b)
-                            dst[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab, bb[b], dst[b], 0, 0, 0);
-                    } else {
-                        bf16x8 ab, as;
-                        split_bf16x8(*reinterpret_cast<const floatx4*>(r), *reinterpret_cast<const floatx4*>(r + 16), ab, as);
-#pragma unroll
-                        for (int b = 0; b < TM; ++b) {
-                            dst[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as, bb[b], dst[b], 0, 0, 0);
-                            dst[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab, bs[b], dst[b], 0, 0, 0);
-                            dst[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab, bb[b], dst[b], 0, 0, 0);
-                        }
-                    }
+                    for (int b = 0; b < TM; ++b)
+                        dst[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab, bb[b], dst[b], 0, 0, 0);
                 }
             }
         }
@@ -945,12 +917,12 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_gemm_dual(DualArgs
 
 // the FP32 dual product, operands split in three (k_gemm_nt32): 64 points x BM
 // outputs, 2 x 2 waves
-template <int EPI2, int BM>
+template <int EPI2, int BM, int N>
 __global__ __launch_bounds__(256, 2) void k_gemm_dual32(DualArgs g) {
     constexpr int BP = 64, BK = 32, WP = 2, TP = BP / WP / 16, TM = BM / 2 / 16;
-    constexpr int FT = 64 * 8, NBV = 3 * BM * BK / 8 / 256;
-    __shared__ __align__(16) uint16_t sA[2][3 * (BP / 16) * FT];
-    __shared__ __align__(16) uint16_t sB[3 * (BM / 16) * FT];
+    constexpr int FT = 64 * 8, NBV = N * BM * BK / 8 / 256;
+    __shared__ __align__(16) uint16_t sA[2][N * (BP / 16) * FT];
+    __shared__ __align__(16) uint16_t sB[N * (BM / 16) * FT];
     const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
     const int wp = wv % WP, wm = wv / WP;
     const int li = lane & 15, lg = lane >> 4;
@@ -974,7 +946,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_dual32(DualArgs g) {
     DualEpilogue<EPI2, BP, BM, WP> epi;
     epi.prefetch(g, p0, m0);
     const int nk = g.K / BK;
-    const uintx4* img = reinterpret_cast<const uintx4*>(g.Bx) + (long)mb * nk * (NBV * 256);
+    const uintx4* img = reinterpret_cast<const uintx4*>(g.Bx) + (long)mb * nk * (3 * BM * 4);
     const int row = tid >> 2, kg = tid & 3;
     const long pr = min(p0 + row, g.P - 1);      // rows beyond the last point repeat it
     floatx4 ra[2][2];
@@ -982,42 +954,42 @@ __global__ __launch_bounds__(256, 2) void k_gemm_dual32(DualArgs g) {
     auto load = [&](int kc) {
 #pragma unroll
         for (int w = 0; w < 2; ++w) {
-            const floatx4* q = reinterpret_cast<const floatx4*>((w ? g.A2 : g.A) + pr * g.lda + kc * BK + kg * 8);
+            const floatx4* q = reinterpret_cast<const floatx4*>((w ? g.A2 : g.A) + pr * g.lda + kc * BK + kg * split_k0(N));
             ra[w][0] = q[0];
-            ra[w][1] = q[1];
+            ra[w][1] = q[split_k1(N) / 4];
         }
 #pragma unroll
-        for (int i = 0; i < NBV; ++i) rb[i] = img[(long)kc * (NBV * 256) + i * 256 + tid];
+        for (int i = 0; i < NBV; ++i) rb[i] = img[(long)kc * (3 * BM * 4) + i * 256 + tid];
     };
     load(0);
     for (int kc = 0; kc < nk; ++kc) {
 #pragma unroll
         for (int w = 0; w < 2; ++w) {
-            bf16x8 part[3];
-            split3_bf16x8(ra[w][0], ra[w][1], part);
+            bf16x8 part[N];
+            split_bf16x8(ra[w][0], ra[w][1], part);
 #pragma unroll
-            for (int q = 0; q < 3; ++q)
+            for (int q = 0; q < N; ++q)
                 *reinterpret_cast<bf16x8*>(&sA[w][(q * (BP / 16) + (row >> 4)) * FT + frag_slot(row & 15, kg) * 8]) = part[q];
         }
 #pragma unroll
         for (int i = 0; i < NBV; ++i) *reinterpret_cast<uintx4*>(&sB[(i * 256 + tid) * 8]) = rb[i];
         __syncthreads();
         if (kc + 1 < nk) load(kc + 1);
-        bf16x8 wf[TM][3];
+        bf16x8 wf[TM][N];
 #pragma unroll
         for (int b = 0; b < TM; ++b)
 #pragma unroll
-            for (int q = 0; q < 3; ++q)
+            for (int q = 0; q < N; ++q)
                 wf[b][q] = *reinterpret_cast<const bf16x8*>(&sB[(q * (BM / 16) + wm * TM + b) * FT + lane * 8]);
 #pragma unroll
         for (int a = 0; a < TP; ++a)
 #pragma unroll
             for (int w = 0; w < 2; ++w) {
-                bf16x8 af[3];
+                bf16x8 af[N];
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
+                for (int q = 0; q < N; ++q)
                     af[q] = *reinterpret_cast<const bf16x8*>(&sA[w][(q * (BP / 16) + wp * TP + a) * FT + frag_slot(li, lg) * 8]);
-                mfma_split3<TM>(wf, af, w ? acd[a] : acc[a], true);
+                mfma_split<N, TM>(wf, af, w ? acd[a] : acc[a], true);
             }
         __syncthreads();
     }
@@ -1049,8 +1021,8 @@ struct WgArgs {
     float beta;
 };
 
-template <int PRO, int MM, int ST = 0, int ST2 = -1>
-__global__ __launch_bounds__(256, MM == MM_BF16 ? 3 : 1) void k_gemm_wg(WgArgs g) {
+template <int PRO, int ST = 0, int ST2 = -1>
+__global__ __launch_bounds__(256, 3) void k_gemm_wg(WgArgs g) {
     constexpr int BM = 128, BN = 128, BK = 32, LW = 128 + 4;
     __shared__ float sA[BK * LW];
     __shared__ float sB[BK * LW];
@@ -1136,70 +1108,36 @@ __global__ __launch_bounds__(256, MM == MM_BF16 ? 3 : 1) void k_gemm_wg(WgArgs g
                     for (int r = 0; r < BK; ++r) bsum += sA[r * LW + tid];
                 }
             }
-            if constexpr (MM == MM_BF16) {
-                // points lg*4 + s and 16 + lg*4 + s (s < 4) fill the 8 k slots of a
-                // lane; the B fragments are converted first and each A fragment
-                // just before its products (scheduling barriers keep the order), so
-                // that three waves fit on a SIMD
-                bf16x8 bf[4];
+            // points lg*4 + s and 16 + lg*4 + s (s < 4) fill the 8 k slots of a
+            // lane; the B fragments are converted first and each A fragment
+            // just before its products (scheduling barriers keep the order), so
+            // that three waves fit on a SIMD
+            bf16x8 bf[4];
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    floatx4 b0, b1;
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        const int r = lg * 4 + s;
-                        b0[s] = sB[r * LW + wn * 64 + b * 16 + li];
-                        b1[s] = sB[(r + 16) * LW + wn * 64 + b * 16 + li];
-                    }
-                    bf[b] = to_bf16x8(b0, b1);
-                }
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    floatx4 a0, a1;
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        const int r = lg * 4 + s;
-                        a0[s] = sA[r * LW + wp * 64 + a * 16 + li];
-                        a1[s] = sA[(r + 16) * LW + wp * 64 + a * 16 + li];
-                    }
-                    const bf16x8 af = to_bf16x8(a0, a1);
-#pragma unroll
-                    for (int b = 0; b < 4; ++b)
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[b], acc[a][b], 0, 0, 0);
-                }
-            } else {
-                // points lg*4 + s and 16 + lg*4 + s (s < 4) fill the 8 k slots of a lane
-                floatx4 a0[4], a1[4], b0[4], b1[4];
+            for (int b = 0; b < 4; ++b) {
+                floatx4 b0, b1;
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
                     const int r = lg * 4 + s;
-#pragma unroll
-                    for (int a = 0; a < 4; ++a) {
-                        a0[a][s] = sA[r * LW + wp * 64 + a * 16 + li];
-                        a1[a][s] = sA[(r + 16) * LW + wp * 64 + a * 16 + li];
-                    }
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        b0[b][s] = sB[r * LW + wn * 64 + b * 16 + li];
-                        b1[b][s] = sB[(r + 16) * LW + wn * 64 + b * 16 + li];
-                    }
+                    b0[s] = sB[r * LW + wn * 64 + b * 16 + li];
+                    b1[s] = sB[(r + 16) * LW + wn * 64 + b * 16 + li];
                 }
-                {
-                    bf16x8 ab[4], as[4], bb[4], bs[4];
+                bf[b] = to_bf16x8(b0, b1);
+            }
 #pragma unroll
-                    for (int a = 0; a < 4; ++a) split_bf16x8(a0[a], a1[a], ab[a], as[a]);
+            for (int a = 0; a < 4; ++a) {
+                __builtin_amdgcn_sched_barrier(0);
+                floatx4 a0, a1;
 #pragma unroll
-                    for (int b = 0; b < 4; ++b) split_bf16x8(b0[b], b1[b], bb[b], bs[b]);
-#pragma unroll
-                    for (int a = 0; a < 4; ++a)
-#pragma unroll
-                        for (int b = 0; b < 4; ++b) {
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as[a], bb[b], acc[a][b], 0, 0, 0);
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab[a], bs[b], acc[a][b], 0, 0, 0);
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab[a], bb[b], acc[a][b], 0, 0, 0);
-                        }
+                for (int s = 0; s < 4; ++s) {
+                    const int r = lg * 4 + s;
+                    a0[s] = sA[r * LW + wp * 64 + a * 16 + li];
+                    a1[s] = sA[(r + 16) * LW + wp * 64 + a * 16 + li];
                 }
+                const bf16x8 af = to_bf16x8(a0, a1);
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[b], acc[a][b], 0, 0, 0);
             }
             __syncthreads();
         }
@@ -1238,13 +1176,13 @@ __global__ __launch_bounds__(256, MM == MM_BF16 ? 3 : 1) void k_gemm_wg(WgArgs g
 // together, then fall on different banks.
 __device__ __forceinline__ int wg_slot(int c, int t) { return ((c >> 1) | ((c & 1) << 3)) ^ ((t & 1) << 3); }
 
-template <int PRO, int ST = 0, int ST2 = -1, int T = 128>
+template <int PRO, int ST = 0, int ST2 = -1, int T = 128, int N = 3>
 __global__ __launch_bounds__(256, T == 128 ? 2 : 3) void k_gemm_wg32(WgArgs g) {
     constexpr int BM = T, BN = T, FT = 64 * 8;
     constexpr int LPR = T / 2, KS = 64 / LPR, BK = 32 * KS;   // lanes of a row, 32-point steps per chunk
     constexpr int TW = T / 32;                                // 16 x 16 tiles of a wave, each way
-    __shared__ __align__(16) uint16_t sA[KS * 3 * (BM / 16) * FT];
-    __shared__ __align__(16) uint16_t sB[KS * 3 * (BN / 16) * FT];
+    __shared__ __align__(16) uint16_t sA[KS * N * (BM / 16) * FT];
+    __shared__ __align__(16) uint16_t sB[KS * N * (BN / 16) * FT];
     const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
     const int wp = wv % 2, wn = wv / 2;
     const int li = lane & 15, lg = lane >> 4;
@@ -1304,11 +1242,11 @@ __global__ __launch_bounds__(256, T == 128 ? 2 : 3) void k_gemm_wg32(WgArgs g) {
                     lo[j] = h ? r[j].y : r[j].x;
                     hi[j] = h ? r[4 + j].y : r[4 + j].x;
                 }
-                bf16x8 part[3];
-                split3_bf16x8(lo, hi, part);
+                bf16x8 part[N];
+                split_bf16x8(lo, hi, part);
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
-                    *reinterpret_cast<bf16x8*>(&s[(((oct >> 2) * 3 + q) * (T / 16) + t) * FT + ((oct & 3) * 16 + wg_slot(c + h, t)) * 8]) = part[q];
+                for (int q = 0; q < N; ++q)
+                    *reinterpret_cast<bf16x8*>(&s[(((oct >> 2) * N + q) * (T / 16) + t) * FT + ((oct & 3) * 16 + wg_slot(c + h, t)) * 8]) = part[q];
             }
         };
         if (pb < pe) load(pb);
@@ -1338,21 +1276,21 @@ __global__ __launch_bounds__(256, T == 128 ? 2 : 3) void k_gemm_wg32(WgArgs g) {
             if (q0 + BK < pe) load(q0 + BK);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                bf16x8 bf[TW][3];
+                bf16x8 bf[TW][N];
 #pragma unroll
                 for (int b = 0; b < TW; ++b)
 #pragma unroll
-                    for (int q = 0; q < 3; ++q)
+                    for (int q = 0; q < N; ++q)
                         bf[b][q] = *reinterpret_cast<const bf16x8*>(
-                            &sB[((ks * 3 + q) * (T / 16) + wn * TW + b) * FT + (lg * 16 + wg_slot(li, wn * TW + b)) * 8]);
+                            &sB[((ks * N + q) * (T / 16) + wn * TW + b) * FT + (lg * 16 + wg_slot(li, wn * TW + b)) * 8]);
 #pragma unroll
                 for (int a = 0; a < TW; ++a) {
-                    bf16x8 af[3];
+                    bf16x8 af[N];
 #pragma unroll
-                    for (int q = 0; q < 3; ++q)
+                    for (int q = 0; q < N; ++q)
                         af[q] = *reinterpret_cast<const bf16x8*>(
-                            &sA[((ks * 3 + q) * (T / 16) + wp * TW + a) * FT + (lg * 16 + wg_slot(li, wp * TW + a)) * 8]);
-                    mfma_split3<TW>(bf, af, acc[a], true);
+                            &sA[((ks * N + q) * (T / 16) + wp * TW + a) * FT + (lg * 16 + wg_slot(li, wp * TW + a)) * 8]);
+                    mfma_split<N, TW>(bf, af, acc[a], true);
                 }
             }
             __syncthreads();
@@ -1672,6 +1610,7 @@ struct PrepJob {
     const float* in;
     void* out;
     int R, C, K, transpose, bm;    // bm: rows per block of the image, 0 for FP32 rows
+    int parts;                     // of the products that read the image (split_k)
 };
 struct PrepTable {
     PrepJob job[kPrepJobs];
@@ -1695,15 +1634,15 @@ __global__ void k_prep_weights(PrepTable t) {
             const int slot = (int)(u % 64), tiles = j.bm / 16, nk = j.K / 32;
             const int tile = (int)(u / 64) % tiles;
             const int blk = (int)(u / 64 / tiles);             // block of rows * nk + 32-wide k chunk
-            const int n = (blk / nk) * j.bm + tile * 16 + (slot & 15), k0 = (blk % nk) * 32 + (slot >> 4) * 8;
+            const int n = (blk / nk) * j.bm + tile * 16 + (slot & 15), k0 = (blk % nk) * 32 + (slot >> 4) * split_k0(j.parts);
             floatx4 lo, hi;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 lo[e] = at(n, k0 + e);
-                hi[e] = at(n, k0 + 4 + e);
+                hi[e] = at(n, k0 + split_k1(j.parts) + e);
             }
             bf16x8 part[3];
-            split3_bf16x8(lo, hi, part);
+            split_bf16x8(lo, hi, part);
             uint16_t* out = reinterpret_cast<uint16_t*>(j.out) + (long)blk * 3 * tiles * 512;
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<bf16x8*>(&out[((long)q * tiles + tile) * 512 + slot * 8]) = part[q];
@@ -1792,6 +1731,7 @@ inline unsigned blocks(long n, int t = 256) { return (unsigned)((n + t - 1) / t)
 struct WMat {
     float* f = nullptr;
     uint16_t* x = nullptr;
+    int parts = 3;         // of the products that read x
 };
 struct Weights {
     WMat Wp[16];           // W_l [W][fin_pad], zero padded
@@ -1804,8 +1744,9 @@ size_t image_words(int N, int K) { return (size_t)((N + block_rows(N) - 1) / blo
 size_t wmat_bytes(int N, int K, bool split) {
     return align256(split ? sizeof(uint16_t) * image_words(N, K) : sizeof(float) * (size_t)N * K);
 }
-WMat take_wmat(WsCursor& cur, int N, int K, bool split) {
+WMat take_wmat(WsCursor& cur, int N, int K, bool split, int parts = 3) {
     WMat w;
+    w.parts = parts;
     if (split) w.x = cur.take<uint16_t>(image_words(N, K));
     else w.f = cur.take<float>((size_t)N * K);
     return w;
@@ -1819,6 +1760,7 @@ struct PrepList {
         PrepJob& j = t.job[t.n];
         j.in = in; j.R = R; j.C = C; j.K = K; j.transpose = transpose;
         j.bm = w.x ? block_rows(N) : 0;
+        j.parts = w.parts;
         j.out = w.x ? (void*)w.x : (void*)w.f;
         t.begin[t.n] = total;
         total += w.x ? (long)(image_words(N, K) / 24) : (long)N * K;
@@ -1834,31 +1776,32 @@ struct PrepList {
 };
 
 size_t weights_bytes(const Layout& l, int precision) {
-    const bool f32 = precision == RFVR_PREC_FP32;
+    const bool f32 = precision == RFVR_PREC_FP32, image = f32 || precision == RFVR_PREC_BF16X3;
     size_t b = 0;
     for (int i = 0; i < l.L; ++i) {
         const int fin = i == 0 ? l.in0p : l.W;
-        b += wmat_bytes(l.W, fin, f32) + wmat_bytes(fin, l.W, f32 || i == 0);
+        b += wmat_bytes(l.W, fin, i == 0 ? f32 : image) + wmat_bytes(fin, l.W, image || i == 0);
     }
     for (int h = 0; h < l.HL; ++h) {
         const int fin = h == 0 ? l.W : l.HW;
-        b += wmat_bytes(l.HW, fin, f32) + wmat_bytes(fin, l.HW, f32);
+        b += wmat_bytes(l.HW, fin, image) + wmat_bytes(fin, l.HW, image);
     }
     return b;
 }
 
 Weights take_weights(WsCursor& cur, const Layout& l, int precision) {
-    const bool f32 = precision == RFVR_PREC_FP32;
+    const bool f32 = precision == RFVR_PREC_FP32, image = f32 || precision == RFVR_PREC_BF16X3;
+    const int parts = f32 ? 3 : 2;
     Weights w;
     for (int i = 0; i < l.L; ++i) {
         const int fin = i == 0 ? l.in0p : l.W;
-        w.Wp[i] = take_wmat(cur, l.W, fin, f32);
-        w.WT[i] = take_wmat(cur, fin, l.W, f32 || i == 0);
+        w.Wp[i] = take_wmat(cur, l.W, fin, i == 0 ? f32 : image, parts);
+        w.WT[i] = take_wmat(cur, fin, l.W, image || i == 0, i == 0 ? 3 : parts);
     }
     for (int h = 0; h < l.HL; ++h) {
         const int fin = h == 0 ? l.W : l.HW;
-        w.Whp[h] = take_wmat(cur, l.HW, fin, f32);
-        w.WhT[h] = take_wmat(cur, fin, l.HW, f32);
+        w.Whp[h] = take_wmat(cur, l.HW, fin, image, parts);
+        w.WhT[h] = take_wmat(cur, fin, l.HW, image, parts);
     }
     return w;
 }
@@ -1890,6 +1833,10 @@ int mm_fwd(int precision) {
 }
 int mm_bwd(int precision) { return precision == RFVR_PREC_F16 ? MM_BF16 : mm_fwd(precision); }
 
+// forms that multiply operands split in parts, and how many
+constexpr bool is_split(int mm) { return mm == MM_FP32 || mm == MM_BF16X3; }
+constexpr int split_parts(int mm) { return mm == MM_FP32 ? 3 : 2; }
+
 // launch context of the network passes: stream and matrix-operand precision
 // (16-bit operands, FP32 accumulation; layers reading the encoding stay FP32)
 struct Cx {
@@ -1913,17 +1860,18 @@ template <int PRO, int EPI, int MM, int ST = 0>
 void gemm_launch(const GemmArgs& a, hipStream_t st) {
     const int bm = block_rows(a.M);
     const dim3 grid = gemm_grid(a.P, 128, a.M, bm);
-    if constexpr (MM == MM_FP32) {
-        static_assert(ST == 0, "the FP32 kernel has no BF16 storage");
+    if constexpr (MM == MM_FP32 || MM == MM_BF16X3) {
+        static_assert(ST == 0, "the split kernel has no BF16 storage");
+        constexpr int N = split_parts(MM);
         // up to two large tiles a CU take all their outputs at a time (training
         // pair at 32768 points, 512 tiles: 3.21 ms in halves, 3.12)
         const dim3 g128 = gemm_grid(a.P, 128, a.M, 128);
         if (split_tile(a.P, a.M) == 64)
-            hipLaunchKernelGGL((k_gemm_nt32<PRO, EPI, 64, 2>), gemm_grid(a.P, 64, a.M, 64), dim3(256), 0, st, a);
+            hipLaunchKernelGGL((k_gemm_nt32<PRO, EPI, 64, 2, N>), gemm_grid(a.P, 64, a.M, 64), dim3(256), 0, st, a);
         else if (g128.x <= 512)
-            hipLaunchKernelGGL((k_gemm_nt32<PRO, EPI, 128, 4>), g128, dim3(256), 0, st, a);
+            hipLaunchKernelGGL((k_gemm_nt32<PRO, EPI, 128, 4, N>), g128, dim3(256), 0, st, a);
         else
-            hipLaunchKernelGGL((k_gemm_nt32<PRO, EPI, 128, 2>), g128, dim3(256), 0, st, a);
+            hipLaunchKernelGGL((k_gemm_nt32<PRO, EPI, 128, 2, N>), g128, dim3(256), 0, st, a);
     } else {
         if (bm == 64) hipLaunchKernelGGL((k_gemm_nt<PRO, EPI, 64, MM, ST>), grid, dim3(256), 0, st, a);
         else hipLaunchKernelGGL((k_gemm_nt<PRO, EPI, 128, MM, ST>), grid, dim3(256), 0, st, a);
@@ -1975,11 +1923,16 @@ void gemm_b16(const GemmArgs& a, const Cx& cx) {
 #endif
 template <int EPI2>
 void gemm_dual(const DualArgs& a, int mm, hipStream_t st) {
-    if (mm == MM_FP32) {
+    if (is_split(mm)) {
         const int bm = block_rows(a.M);
         const dim3 grid = gemm_grid(a.P, 64, a.M, bm);
-        if (bm == 64) hipLaunchKernelGGL((k_gemm_dual32<EPI2, 64>), grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((k_gemm_dual32<EPI2, 128>), grid, dim3(256), 0, st, a);
+        const auto go = [&](auto n) {
+            constexpr int N = decltype(n)::value;
+            if (bm == 64) hipLaunchKernelGGL((k_gemm_dual32<EPI2, 64, N>), grid, dim3(256), 0, st, a);
+            else hipLaunchKernelGGL((k_gemm_dual32<EPI2, 128, N>), grid, dim3(256), 0, st, a);
+        };
+        if (mm == MM_FP32) go(std::integral_constant<int, 3>{});
+        else go(std::integral_constant<int, 2>{});
         return;
     }
     constexpr int NW = RFVR_DUAL_NW, BP = NW == 8 ? 128 : 64;
@@ -1991,8 +1944,7 @@ void gemm_dual(const DualArgs& a, int mm, hipStream_t st) {
             return;
         }
     }
-    if (mm == MM_BF16X3) hipLaunchKernelGGL((k_gemm_dual<EPI2, MM_BF16X3, NW>), grid, dim3(NW * 64), 0, st, a);
-    else hipLaunchKernelGGL((k_gemm_dual<EPI2, MM_BF16, NW>), grid, dim3(NW * 64), 0, st, a);
+    hipLaunchKernelGGL((k_gemm_dual<EPI2, MM_BF16, NW>), grid, dim3(NW * 64), 0, st, a);
 }
 
 DualArgs da(const float* A, const float* A2, long lda, const WMat& B, long ldb, const float* bias,
@@ -2032,19 +1984,20 @@ void wgrad(const float* A, long lda, int M, const float* B, long ldb, int Kout, 
     const int ns = wg_splits(P);
     g.M = M; g.Kout = Kout; g.per_split = ((P + ns - 1) / ns + 31) / 32 * 32;
     g.n_split = ns;
-    const bool narrow = cx.mm == MM_FP32 && wg_narrow(M, Kout);
+    const bool narrow = is_split(cx.mm) && wg_narrow(M, Kout);
     const int T = narrow ? 64 : 128;
     const long tiles = (long)((M + T - 1) / T) * ((Kout + T - 1) / T);
     const long groups = (ns + 7) / 8;
     const dim3 grid((unsigned)(groups * 8 * tiles));
     // 16-bit storage comes with single BF16 products, or with FP32 ones (the first layer)
     if (cx.mm == MM_BF16) {
-        hipLaunchKernelGGL((k_gemm_wg<PRO, MM_BF16, ST, ST2>), grid, dim3(256), 0, cx.st, g);
+        hipLaunchKernelGGL((k_gemm_wg<PRO, ST, ST2>), grid, dim3(256), 0, cx.st, g);
         return;
     }
     if constexpr (ST == 0 && ST2 <= 0) {
         if (cx.mm == MM_BF16X3) {
-            hipLaunchKernelGGL((k_gemm_wg<PRO, MM_BF16X3, 0, ST2>), grid, dim3(256), 0, cx.st, g);
+            if (narrow) hipLaunchKernelGGL((k_gemm_wg32<PRO, ST, ST2, 64, 2>), grid, dim3(256), 0, cx.st, g);
+            else hipLaunchKernelGGL((k_gemm_wg32<PRO, ST, ST2, 128, 2>), grid, dim3(256), 0, cx.st, g);
             return;
         }
     }
@@ -2087,7 +2040,7 @@ size_t fwd_bytes(const Layout& l, int prec, long n, bool keep) {
 
 // --- backward workspace ------------------------------------------------------
 // point rows of the top-adjoint GEMM's column partials: one per point tile
-int top_tile(bool f32, long P, int M) { return f32 ? split_tile(P, M) : 128; }
+int top_tile(int mm, long P, int M) { return is_split(mm) ? split_tile(P, M) : 128; }
 long top_rows(long n, int tile) { return (n + tile - 1) / tile; }
 
 size_t bwd_bytes(const Layout& l, int prec, long n, bool keep) {
@@ -2406,7 +2359,7 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
         }
         // sdf output layer: w_out_bar from the partials, b_out_bar = half sum g_f
         hipLaunchKernelGGL(k_colsum_final, dim3(l.W), dim3(256), 0, st, tpart,
-                           (int)top_rows(m, top_tile(cx.mm == MM_FP32, m, l.W)), l.W, 1.0f,
+                           (int)top_rows(m, top_tile(cx.mm, m, l.W)), l.W, 1.0f,
                            GP + l.o_wout, acc);
         if (gf) colsum(gf, nullptr, nullptr, 1, m, 1, 0, beta, half, cpart, GP + l.o_bout, acc, st);
         else if (!acc) hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, st, GP + l.o_bout, 1L, 0.0f);

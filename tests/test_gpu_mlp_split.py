@@ -118,3 +118,27 @@ def test_narrow_products_match_oracle(n, octaves, layers, shift):
     errs = [rel(z, op.forward(p64, spec, x.astype(np.float64))),
             rel(gp, op.backward(p64, spec, x.astype(np.float64), g.astype(np.float64)))]
     assert max(errs) < 3 * 2.0 ** -24 * 8 + pe, errs
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,width,octaves,head,layers", [
+    (1, 64, 2, 64, 1), (63, 128, 4, 64, 2), (65, 192, 10, 128, 3), (128, 256, 0, 64, 1), (129, 256, 12, 256, 4), (4133, 256, 6, 64, 2)])
+@pytest.mark.parametrize("pair", [True, False])
+def test_two_part_products_match_oracle(n, width, octaves, head, layers, pair):
+    """BF16X3 on the same tiles: two parts hold 16 bits, so an operand is within 2^-17 and a product of K terms with
+    errors of either sign within 2^-16 of its norm; 8 layers give 1.3e-4 for f and a at most, 16 times that for the
+    gradients as above."""
+    from paper_2605_29097_amd import rfvr as R
+    spec = MLPSpec(n_layers=4, width=width, pe_octaves=octaves, head_width=head, head_layers=layers)
+    p, m = net(spec)
+    m.precision = R.PREC_BF16X3
+    x, gf, gg, ga = inputs(n)
+    t = [torch.from_numpy(a).cuda() for a in (x, gf, gg, ga)]
+    res = R.mlp_reserve(m, n, "cuda") if pair else None
+    f, g, a = R.mlp_forward(m, t[0], reserve=res)
+    gp = R.mlp_backward(m, t[0], t[1], t[2], t[3], reserve=res)
+    fo, go, ao = omlp.forward(p, spec, x)
+    gpo = omlp.backward(p, spec, x, gf, gg, ga)
+    pe = 2.0 ** -24 * np.pi * 2.0 ** octaves
+    errs = [rel(f.cpu(), fo), rel(a.cpu(), ao), rel(g.cpu(), go), rel(gp.cpu(), gpo)]
+    assert max(errs[:2]) < 1.3e-4 + pe and max(errs[2:]) < 2e-3 + 4 * pe, errs
