@@ -31,7 +31,7 @@
 // most 2 (z/2)^K / K! / (1 - z / (2K + 2)) (z = max |z_n|) times the sum of the
 // magnitudes of its terms' weights.  A one-block plan kernel takes the largest
 // z of the launch and picks the smallest K of kChebKs whose
-// bound is below kChebTol, or 0 (the per-frequency kernels) when none is (a
+// bound is below 1e-6, or 0 (the per-frequency kernels) when none is (a
 // wide range spread) or K is not below the number of frequencies.  The choice
 // stays on the device: every candidate kernel is launched and all but the
 // chosen one return at once, so no host synchronisation is needed.
@@ -55,7 +55,7 @@ constexpr int kChebKMax = kChebMaxOrder;
 // truncation bound, relative to the sum of the term magnitudes: of the order of
 // the FP32 rounding of the sums themselves (a lane's moments accumulate a
 // point split of ~2k points in FP32)
-constexpr double kChebTol = 1e-6;
+constexpr double kChebLogTol = -13.815510557964274;   // log 1e-6
 
 // ---------------------------------------------------------------------------
 // bounding box of a launch's points: per-block min / max, then the plan
@@ -101,13 +101,13 @@ __device__ constexpr double kChebLogFact[] = {54.784729398112319, 67.88974313718
                                               110.32063971475740, 140.67392364823426, 205.16819948264120};
 static_assert(sizeof(kChebLogFact) / sizeof(double) == kChebNK, "one per order");
 
-// orders of a cell's series and log K!; kCellTol bounds 2 (z/2)^K / K! / (1 - ...)
+// orders of a cell's series and log K!; 2.5e-7 bounds 2 (z/2)^K / K! / (1 - ...)
 // there: interpolation at K nodes is within twice that of the function
 constexpr int kCellKs[] = {8, 10, 12, 14, 16};
 constexpr int kCellNK = (int)(sizeof(kCellKs) / sizeof(kCellKs[0])), kCellKMax = 16;
 __device__ constexpr double kCellLogFact[] = {10.604602902745250, 15.104412573075516, 19.987214495661885,
                                               25.191221182738680, 30.671860106080672};
-constexpr double kCellTol = 2.5e-7;
+constexpr double kCellLogTol = -15.201804919084164;   // log 2.5e-7
 
 // log of 2 (z/2)^K / K! / (1 - z/(2K+2)), the truncation bound; +inf when the
 // geometric tail does not converge
@@ -115,20 +115,7 @@ __device__ double cheb_log_bound(int K, double log_fact, double z) {
     const double q = 0.5 * z;
     if (q <= 0.0) return -INFINITY;
     if (q >= (double)(K + 1)) return INFINITY;
-    return (double)K * log(q) - log_fact + log(2.0) - log1p(-q / (double)(K + 1));
-}
-
-// min (or max) over a wave, then over the work-group's waves through sh
-template <bool MAX, class T>
-__device__ __forceinline__ T block_extreme(T v, T* sh, int waves) {
-    auto pick = [](T a, T b) { return MAX ? (a > b ? a : b) : (a < b ? a : b); };
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = pick(v, __shfl_xor(v, o, 64));
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    for (int w = 0; w < waves; ++w) v = pick(v, sh[w]);
-    __syncthreads();
-    return v;
+    return (double)K * log(q) - log_fact + 0.69314718055994531 - log1p(-q / (double)(K + 1));
 }
 
 // The launch's plan, one work-group: the measurement records (transmitters, and
@@ -144,18 +131,28 @@ __global__ __launch_bounds__(kPlanThreads) void k_cheb_plan(const float* __restr
                                                             int n_meas, double Kd, int n_freq,
                                                             MeasCheb* __restrict__ meas, ChebPlan* __restrict__ plan,
                                                             CellGrid* __restrict__ grid, int max_cells) {
-    __shared__ float sf[kPlanThreads / 64];
+    __shared__ float sf[6][kPlanThreads / 64];
     __shared__ double sz[kPlanThreads / 64];
-    const int t = threadIdx.x, waves = kPlanThreads / 64;
+    static_assert(kPlanThreads == 1024, "16 waves");
+    const int t = threadIdx.x;
     float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     if (nb == 0) {
-        for (long j = t; j < n; j += kPlanThreads) {
+        // four points at a time (the last one repeated): one wait on memory per 4096
+        for (long j0 = t; j0 < n; j0 += 4 * kPlanThreads) {
+            float v[4][3];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const float v = xyz[3 * j + c];
-                lo[c] = fminf(lo[c], v);
-                hi[c] = fmaxf(hi[c], v);
+            for (int u = 0; u < 4; ++u) {
+                const long j = min(j0 + u * kPlanThreads, n - 1);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) v[u][c] = xyz[3 * j + c];
             }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    lo[c] = fminf(lo[c], v[u][c]);
+                    hi[c] = fmaxf(hi[c], v[u][c]);
+                }
         }
     } else {
         for (int b = t; b < nb; b += kPlanThreads) {
@@ -166,11 +163,39 @@ __global__ __launch_bounds__(kPlanThreads) void k_cheb_plan(const float* __restr
             }
         }
     }
+    // the six extremes of the work-group, side by side: over the wave, then its 16 waves'
+    // in every 16 lanes
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            lo[c] = fminf(lo[c], __shfl_xor(lo[c], o, 64));
+            hi[c] = fmaxf(hi[c], __shfl_xor(hi[c], o, 64));
+        }
+    if ((t & 63) == 0)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            sf[c][t >> 6] = lo[c];
+            sf[3 + c][t >> 6] = hi[c];
+        }
+    __syncthreads();
     double bl[3], bh[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        bl[c] = (double)block_extreme<false>(lo[c], sf, waves);
-        bh[c] = (double)block_extreme<true>(hi[c], sf, waves);
+        lo[c] = sf[c][t & 15];
+        hi[c] = sf[3 + c][t & 15];
+    }
+#pragma unroll
+    for (int o = 8; o >= 1; o >>= 1)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            lo[c] = fminf(lo[c], __shfl_xor(lo[c], o, 64));
+            hi[c] = fmaxf(hi[c], __shfl_xor(hi[c], o, 64));
+        }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        bl[c] = (double)lo[c];
+        bh[c] = (double)hi[c];
     }
     const bool finite = isfinite(bl[0]) && isfinite(bl[1]) && isfinite(bl[2]) && isfinite(bh[0]) &&
                         isfinite(bh[1]) && isfinite(bh[2]);
@@ -220,11 +245,17 @@ __global__ __launch_bounds__(kPlanThreads) void k_cheb_plan(const float* __restr
         meas[i] = m;
         zl = fmax(zl, 6.283185307179586 * (0.5 * (double)(n_freq - 1)) * Kd * m.h);
     }
-    const double zmax = block_extreme<true>(zl, sz, waves);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) zl = fmax(zl, __shfl_xor(zl, o, 64));
+    if ((t & 63) == 0) sz[t >> 6] = zl;
+    __syncthreads();
+    double zmax = sz[t & 15];
+#pragma unroll
+    for (int o = 8; o >= 1; o >>= 1) zmax = fmax(zmax, __shfl_xor(zmax, o, 64));
     // one lane per candidate order, the smallest that qualifies
     if (t < 64) {
         const int c = t < kChebNK ? t : kChebNK - 1, k = kChebKs[c];
-        const bool ok = t < kChebNK && finite && k < n_freq && cheb_log_bound(k, kChebLogFact[c], zmax) <= log(kChebTol);
+        const bool ok = t < kChebNK && finite && k < n_freq && cheb_log_bound(k, kChebLogFact[c], zmax) <= kChebLogTol;
         const unsigned long long m = __ballot(ok);
         int KC = 0;
         if (grid && m) {
@@ -256,7 +287,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_cheb_plan(const float* __restr
                 KC = 0;
                 if (g.n_cells > 1)
                     for (int q = kCellNK - 1; q >= 0; --q)
-                        if (cheb_log_bound(kCellKs[q], kCellLogFact[q], z) <= log(kCellTol)) KC = kCellKs[q];
+                        if (cheb_log_bound(kCellKs[q], kCellLogFact[q], z) <= kCellLogTol) KC = kCellKs[q];
                 *grid = g;
             }
             KC = __shfl(KC, 63 - __clzll(fit), 64);
