@@ -20,7 +20,8 @@
  * - Outputs are overwritten, except gradient outputs when `flags` contains
  *   RFVR_ACCUMULATE, which then add into the existing contents.
  * - Reductions use a fixed split and a fixed summation order and no floating
- *   point atomics: results are bitwise reproducible for fixed shapes.
+ *   point atomics: results are bitwise reproducible for fixed shapes (and, of
+ *   the filter forward, a fixed workspace size: see there).
  * - NaN/Inf inside arrays propagate; only descriptor scalars are checked.
  *
  * Notation: i = measurement (a transmitter and its receiver: the same antenna
@@ -78,7 +79,9 @@ extern "C" {
  * expansion), cut at the smallest order K in {24, 28, 32, 40, 48, 64} whose
  * truncation bound 2 (z/2)^K / K! / (1 - z/(2K+2)) (z = 2 pi
  * ((n_freq - 1)/2) df 2h/c, h the half-width of the widest interval) is below
- * 1e-6 of the sum of the term magnitudes.  The choice is made on the device
+ * 1e-6 of the sum of the term magnitudes.  Large calls sort their points into
+ * cells of the box and take fewer orders on each cell's own interval, within
+ * another 5e-7.  The choice is made on the device
  * for every call; when no K qualifies (a range spread too wide for the band)
  * or K is not below n_freq, the per-frequency kernels run, which
  * RFVR_TERMS_DIRECT (and RFVR_PHASE_NAIVE32) also select.  Both evaluate the
@@ -195,6 +198,9 @@ int rfvr_render_backward(const rfvr_aperture* ap, const rfvr_samples* sm, const 
  * xyz_q: [n_q][3] query points.  signal2: optional second signal filtered at
  * the same points (e.g. the measured one), with outputs z2/power2.
  * Any of z, power, z2, power2 may be NULL.  flags: 0 or RFVR_PHASE_NAIVE32.
+ * The query includes room for splits of the measurements (few points) or cells
+ * (many); a smaller workspace, down to what the call cannot do without, is
+ * accepted and takes fewer or none, with results that differ by rounding.
  * ------------------------------------------------------------------------ */
 size_t rfvr_mf_forward_ws_bytes(const rfvr_aperture* ap, int64_t n_q, int two_signals);
 int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, uint32_t flags,
@@ -208,9 +214,9 @@ int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, ui
  * errors are those of rfvr_mf_forward, whose kernels it runs; its scratch is a
  * library-owned device array of RFVR_MF_STATIC_SCRATCH_BYTES on each GPU it
  * runs on, looked up on the first call on that device and held until the
- * process ends.  It allocates nothing.  A call whose rfvr_mf_forward_ws_bytes()
- * exceeds RFVR_MF_STATIC_SCRATCH_BYTES returns RFVR_E_INVALID and enqueues
- * nothing (1024 measurements x 128 frequencies need 1.6 MB with one
+ * process ends.  It allocates nothing.  A call whose records, coefficients and
+ * padded signals exceed RFVR_MF_STATIC_SCRATCH_BYTES returns RFVR_E_INVALID and
+ * enqueues nothing (1024 measurements x 128 frequencies need 1.6 MB with one
  * signal, 3.1 MB with two).  Every call on one GPU uses that GPU's one array,
  * which keeps the last call's contents (nothing in it needs clearing between
  * calls): calls that overlap in time on one GPU, on different streams or

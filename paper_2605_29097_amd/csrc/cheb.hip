@@ -947,8 +947,8 @@ __global__ __launch_bounds__(256) void k_cheb_bwd_sum(const ChebPlan* __restrict
 //         b_m = (2 - [m=0]) / KC sum_l f_l T_m(x_l)
 //   up    u_l = sum_m (2 - [m=0]) / KC T_m(x_l) m_m, M_k = sum_l u_l T_k(X_l)
 // i.e. some thousand operations against 512 or more points of 3 (24 - KC) each.
-// Bound: vector issue, 41 (filter) to 66 (render) instructions per pair in place of
-// 96 to 123.  2^20 points in a 20 cm cube, 1024 measurements, 64 frequencies:
+// Bound: vector issue, 47 (filter) to 77 (render adjoint) instructions per pair
+// counted, in place of 96 to 126.  2^20 points in a 20 cm cube, 1024 measurements, 64 frequencies:
 // render 2.73 -> 1.84 ms, its adjoint 3.11 -> 1.90, filter 2.43 -> 1.38, its adjoint
 // 2.45 -> 1.47 (with the polynomials' recurrence instead of powers of x below: 2.27
 // and 1.79 for the two over frequencies).

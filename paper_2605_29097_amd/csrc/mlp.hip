@@ -2,7 +2,7 @@
 // "Signal representation"; App. C) on the MI355X matrix cores.
 //
 // Points are the GEMM's long dimension.  Every dense layer runs as an MFMA
-// GEMM (v_mfma_f32_16x16x4_f32, or one of the 16-bit operand forms below) with
+// GEMM (FP32 on operands split in BF16 parts, or one of the 16-bit forms below) with
 // the elementwise work of its neighbours fused into the operand loads
 // (softplus, its derivative times a tangent or an adjoint, relu) and the bias /
 // relu-mask / accumulate into its epilogue.
@@ -915,7 +915,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_gemm_dual(DualArgs
     epi.finish(g, acc, acd, p0, m0);
 }
 
-// the FP32 dual product, operands split in three (k_gemm_nt32): 64 points x BM
+// the dual product on split operands (k_gemm_nt32): 64 points x BM
 // outputs, 2 x 2 waves
 template <int EPI2, int BM, int N>
 __global__ __launch_bounds__(256, 2) void k_gemm_dual32(DualArgs g) {
@@ -1166,10 +1166,10 @@ __global__ __launch_bounds__(256, 3) void k_gemm_wg(WgArgs g) {
     if (first_n && tid < BM && m0 + tid < g.M) g.bpart[split * (long)g.M + m0 + tid] = bsum;
 }
 
-// The FP32 weight gradient, both operands split in three (k_gemm_nt32).  The
+// The weight gradient on split operands (k_gemm_nt32).  The
 // contraction runs over points, so a fragment holds 8 points of one column: wave
 // w loads points 8 w .. 8 w + 7 of two neighbouring columns per lane (512
-// contiguous bytes per row), splits them where they are, and stores each
+// contiguous bytes per row; in 64 x 64 tiles a wave's halves take 8 points each), splits them where they are, and stores each
 // column's 8 points as one 16-byte vector per part.  Column c of a 16-column
 // tile t lies in slot ((c >> 1) | (c & 1) << 3) ^ (t & 1) << 3: the even and the
 // odd columns that 16 lanes store together, and the 16 columns that they load
