@@ -22,7 +22,9 @@
  * - Reductions use a fixed split and a fixed summation order and no floating
  *   point atomics: results are bitwise reproducible for fixed shapes (and, of
  *   the filter forward, a fixed workspace size: see there).
- * - NaN/Inf inside arrays propagate; only descriptor scalars are checked.
+ * - NaN/Inf inside arrays propagate; only descriptor scalars are checked.  (An
+ *   infinity that a network product meets can come out as NaN: its operands
+ *   are split in parts.)
  *
  * Notation: i = measurement (a transmitter and its receiver: the same antenna
  * for a monostatic aperture, rx = NULL), n = frequency with
