@@ -2,7 +2,8 @@
 // "Signal representation"; App. C) on the MI355X matrix cores.
 //
 // Points are the GEMM's long dimension.  Every dense layer runs as an MFMA
-// GEMM (FP32 on operands split in BF16 parts, or one of the 16-bit forms below) with
+// GEMM (FP32: the FP32 instruction for values, operands split in BF16 parts for
+// derivatives; or one of the 16-bit forms below) with
 // the elementwise work of its neighbours fused into the operand loads
 // (softplus, its derivative times a tangent or an adjoint, relu) and the bias /
 // relu-mask / accumulate into its epilogue.
@@ -150,7 +151,7 @@ __device__ __forceinline__ void st_bf16(float* base, long i, float v) {
 enum { ST_A = 1, ST_B = 2, ST_C2 = 4, ST_Y = 8 };
 
 // operand precision of a network GEMM: FP32 (MM_FP32: operands split in three;
-// MM_MFMA32: the FP32 instruction, see gemm_first), BF16 MFMA, BF16 MFMA on split
+// MM_MFMA32: the FP32 instruction, see gemm and gemm_first), BF16 MFMA, BF16 MFMA on split
 // operands (a b ~ a_big b_big + a_big b_small + a_small b_big), or FP16 MFMA
 // with the weights rounded once and the per-point operand split in two
 // (a b ~ a_big b + a_small b, two products).  The per-point operand's rounding
@@ -209,7 +210,7 @@ __device__ __forceinline__ float sp_d2(float z, float beta) {
 // ----------------------------------------------------------------------------
 // Y[P x M] = pro(A)[P x K] * B[M x K]^T  (+ epilogue).  K multiple of 32; A and
 // B rows hold K valid or zero-padded columns; lda/ldb multiples of 4.
-// Block 128 points x BM outputs, 4 waves, 16x16x4 MFMA tiles, K chunks of 32
+// Block BP (128, or 64: see gemm_launch) points x BM outputs, 4 waves, 16x16x4 MFMA tiles, K chunks of 32
 // staged through LDS with the next chunk's global loads in flight during the
 // current chunk's MFMAs.  The k index of a lane's MFMA operand is permuted so
 // each lane reads 4 consecutive k (one float4) per 16-wide k group.
@@ -391,15 +392,15 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx4 (&acc)[
     }
 }
 
-template <int PRO, int EPI, int BM, int MM, int ST = 0>
+template <int PRO, int EPI, int BM, int MM, int ST = 0, int BP = 128>
 __global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g) {
     // padded LDS rows (BK + 4 floats): the MFMA fragment reads (16 rows, one
     // float4 column) are free of bank conflicts.  Variants measured slower on
     // this shape: an XOR-swizzled unpadded layout, two LDS buffers with one
     // barrier per chunk, 64-deep chunks (all at two waves per SIMD, against
     // three here).
-    constexpr int BP = 128, BK = 32, LW = BK + 4, RPF = BK / 4;
-    constexpr int WP = (BM == 128) ? 2 : 4;
+    constexpr int BK = 32, LW = BK + 4, RPF = BK / 4;
+    constexpr int WP = (BM == 128 || BP == 64) ? 2 : 4;
     constexpr int WM = 4 / WP;
     constexpr int TP = BP / WP / 16;
     constexpr int TM = BM / WM / 16;
@@ -563,9 +564,9 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g) {
 // fragment in one ds_read_b128 and a wave's in one linear kilobyte.  The store
 // side has four lanes on a row (32 bytes of k each, for coalesced global loads);
 // slot kg * 16 + (row ^ 2 kg) of (row, kg) keeps both sides free of bank conflicts.
+// It serves the derivatives; the values stay on the FP32 instruction (gemm).
 // 2^20 x 256 x 256, against the FP32 instruction in the same kernel shape:
-// softplus layer 1.17 -> 0.84 ms, sp'(Z) product 1.21 -> 0.95 ms, weight gradient
-// 1.45 -> 1.0 ms.  The main loop runs at 1.26 PFLOP/s of BF16 products, what a
+// sp'(Z) product 1.21 -> 0.95 ms, weight gradient 1.45 -> 1.0 ms.  The main loop runs at 1.26 PFLOP/s of BF16 products, what a
 // large BF16 product reaches on this card (1.31); the epilogue's HBM traffic
 // (4.7 TB/s) is not hidden behind it.  Tried and slower: persistent work-groups
 // that fetch the next tile's first chunk and their epilogue's operands early
@@ -1775,33 +1776,44 @@ struct PrepList {
     }
 };
 
-size_t weights_bytes(const Layout& l, int precision) {
-    const bool f32 = precision == RFVR_PREC_FP32, image = f32 || precision == RFVR_PREC_BF16X3;
+// Which operands are images.  tangent: the pass multiplies tangents by W_l (the
+// training backward); the others multiply values, on the FP32 instruction in FP32
+// (see gemm).
+struct Images {
+    bool first, layer, head, transposed;       // W_0, W_l, Wh_h, and the transposes (W_0^T always is one)
+};
+Images images(int precision, bool tangent) {
+    const bool f32 = precision == RFVR_PREC_FP32, x3 = precision == RFVR_PREC_BF16X3;
+    return {f32 && tangent, x3 || (f32 && tangent), x3, f32 || x3};
+}
+
+size_t weights_bytes(const Layout& l, int precision, bool tangent) {
+    const Images im = images(precision, tangent);
     size_t b = 0;
     for (int i = 0; i < l.L; ++i) {
         const int fin = i == 0 ? l.in0p : l.W;
-        b += wmat_bytes(l.W, fin, i == 0 ? f32 : image) + wmat_bytes(fin, l.W, image || i == 0);
+        b += wmat_bytes(l.W, fin, i == 0 ? im.first : im.layer) + wmat_bytes(fin, l.W, im.transposed || i == 0);
     }
     for (int h = 0; h < l.HL; ++h) {
         const int fin = h == 0 ? l.W : l.HW;
-        b += wmat_bytes(l.HW, fin, image) + wmat_bytes(fin, l.HW, image);
+        b += wmat_bytes(l.HW, fin, im.head) + wmat_bytes(fin, l.HW, im.transposed);
     }
     return b;
 }
 
-Weights take_weights(WsCursor& cur, const Layout& l, int precision) {
-    const bool f32 = precision == RFVR_PREC_FP32, image = f32 || precision == RFVR_PREC_BF16X3;
-    const int parts = f32 ? 3 : 2;
+Weights take_weights(WsCursor& cur, const Layout& l, int precision, bool tangent) {
+    const Images im = images(precision, tangent);
+    const int parts = precision == RFVR_PREC_FP32 ? 3 : 2;
     Weights w;
     for (int i = 0; i < l.L; ++i) {
         const int fin = i == 0 ? l.in0p : l.W;
-        w.Wp[i] = take_wmat(cur, l.W, fin, i == 0 ? f32 : image, parts);
-        w.WT[i] = take_wmat(cur, fin, l.W, image || i == 0, i == 0 ? 3 : parts);
+        w.Wp[i] = take_wmat(cur, l.W, fin, i == 0 ? im.first : im.layer, parts);
+        w.WT[i] = take_wmat(cur, fin, l.W, im.transposed || i == 0, i == 0 ? 3 : parts);
     }
     for (int h = 0; h < l.HL; ++h) {
         const int fin = h == 0 ? l.W : l.HW;
-        w.Whp[h] = take_wmat(cur, l.HW, fin, image, parts);
-        w.WhT[h] = take_wmat(cur, fin, l.HW, image, parts);
+        w.Whp[h] = take_wmat(cur, l.HW, fin, im.head, parts);
+        w.WhT[h] = take_wmat(cur, fin, l.HW, im.transposed, parts);
     }
     return w;
 }
@@ -1850,7 +1862,7 @@ dim3 gemm_grid(long P, int tp, int M, int bm) {
     return dim3((unsigned)(groups * 8 * ((M + bm - 1) / bm)));
 }
 
-// Tile of the FP32 products: 128 x 128 where they fill the 256 CUs; below that the
+// Tile of the split products: 128 x 128 where they fill the 256 CUs; below that the
 // 64 x 64 ones put four times the work-groups on the chip (a forward of the
 // 8 x 256 network at 5120 points, 80 large tiles: 345 us with them, 213 with
 // the small ones).
@@ -1873,6 +1885,13 @@ void gemm_launch(const GemmArgs& a, hipStream_t st) {
         else
             hipLaunchKernelGGL((k_gemm_nt32<PRO, EPI, 128, 2, N>), g128, dim3(256), 0, st, a);
     } else {
+        if constexpr (MM == MM_MFMA32 && ST == 0) {
+            // the same rule, and the same sums: a tile's k order does not depend on its size
+            if (grid.x < 384) {
+                hipLaunchKernelGGL((k_gemm_nt<PRO, EPI, 64, MM, ST, 64>), gemm_grid(a.P, 64, a.M, 64), dim3(256), 0, st, a);
+                return;
+            }
+        }
         if (bm == 64) hipLaunchKernelGGL((k_gemm_nt<PRO, EPI, 64, MM, ST>), grid, dim3(256), 0, st, a);
         else hipLaunchKernelGGL((k_gemm_nt<PRO, EPI, 128, MM, ST>), grid, dim3(256), 0, st, a);
     }
@@ -1883,12 +1902,19 @@ void gemm(const GemmArgs& a, const Cx& cx) {
     // the FP16 form exists for the forward products' epilogues only (a
     // backward context never carries MM_F16: mm_bwd maps it to BF16)
     constexpr bool FWD_EPI = EPI == EPI_BIAS || EPI == EPI_BIAS_SP || EPI == EPI_DSPMUL;
+    // The values of layers and head stay on the FP32 instruction in FP32: the signs of
+    // the head's pre-activations are its ReLU masks, which the parameter gradient
+    // shows.  2^20 points have some ten units per layer whose sign another rounding
+    // changes, and those alone move it by 3e-7 to 2.9e-6 (six seeds; all the
+    // products of the gradient 3e-7).
+    constexpr bool VALUE = EPI == EPI_BIAS || EPI == EPI_BIAS_SP;
     if (cx.mm == MM_BF16) gemm_launch<PRO, EPI, MM_BF16>(a, cx.st);
     else if (cx.mm == MM_BF16X3) gemm_launch<PRO, EPI, MM_BF16X3>(a, cx.st);
     else if (cx.mm == MM_F16) {
         if constexpr (FWD_EPI) gemm_launch<PRO, EPI, MM_F16>(a, cx.st);
         else gemm_launch<PRO, EPI, MM_BF16>(a, cx.st);
-    } else gemm_launch<PRO, EPI, MM_FP32>(a, cx.st);
+    } else if constexpr (VALUE) gemm_launch<PRO, EPI, MM_MFMA32>(a, cx.st);
+    else gemm_launch<PRO, EPI, MM_FP32>(a, cx.st);
 }
 
 // FP32 GEMM whatever the context (the last sweep product: its result is the
@@ -1899,10 +1925,10 @@ void gemm32(const GemmArgs& a, const Cx& cx) {
 }
 
 // The first layer's products, FP32 in every form (their operand is the
-// encoding).  The 16-bit forms keep the FP32 instruction: a last-bit change of
-// this layer would move the 16-bit roundings of all that follow (6e-5 of the
-// gradient in the FP16 form), and a product over at most 96 k is bound by the
-// activations it writes either way.
+// encoding).  Only the FP32 training backward's tangent comes with an image.  The
+// 16-bit forms keep the FP32 instruction: a last-bit change of this layer would move
+// the 16-bit roundings of all that follow (6e-5 of the gradient in the FP16 form),
+// and a product over at most 96 k is bound by the activations it writes either way.
 template <int EPI, int ST = 0>
 void gemm_first(const GemmArgs& a, const Cx& cx) {
     if constexpr (ST == 0) {
@@ -1923,6 +1949,7 @@ void gemm_b16(const GemmArgs& a, const Cx& cx) {
 #endif
 template <int EPI2>
 void gemm_dual(const DualArgs& a, int mm, hipStream_t st) {
+    if (EPI2 == EPI2_FWD && mm == MM_FP32) mm = MM_MFMA32;       // values: see gemm
     if (is_split(mm)) {
         const int bm = block_rows(a.M);
         const dim3 grid = gemm_grid(a.P, 64, a.M, bm);
@@ -1931,9 +1958,10 @@ void gemm_dual(const DualArgs& a, int mm, hipStream_t st) {
             if (bm == 64) hipLaunchKernelGGL((k_gemm_dual32<EPI2, 64, N>), grid, dim3(256), 0, st, a);
             else hipLaunchKernelGGL((k_gemm_dual32<EPI2, 128, N>), grid, dim3(256), 0, st, a);
         };
-        if (mm == MM_FP32) go(std::integral_constant<int, 3>{});
-        else go(std::integral_constant<int, 2>{});
-        return;
+        if constexpr (EPI2 == EPI2_ADJ) {
+            if (mm == MM_FP32) return go(std::integral_constant<int, 3>{});
+        }
+        return go(std::integral_constant<int, 2>{});
     }
     constexpr int NW = RFVR_DUAL_NW, BP = NW == 8 ? 128 : 64;
     const dim3 grid = gemm_grid(a.P, BP, a.M, 128);
@@ -2033,7 +2061,7 @@ void colsum(const float* X, const float* X2, const float* s, long ldx, long P, i
 // keep: the layers' (Z, H) go to the caller's reserve instead of the workspace
 size_t fwd_bytes(const Layout& l, int prec, long n, bool keep) {
     const long c = n < kChunk ? n : kChunk;
-    return weights_bytes(l, prec) + align256(sizeof(float) * c * l.in0p) +
+    return weights_bytes(l, prec, false) + align256(sizeof(float) * c * l.in0p) +
            (keep ? 0 : (size_t)l.L * align256(sizeof(float) * c * l.W)) + 2 * align256(sizeof(float) * c * l.W) +
            (keep ? 0 : (size_t)l.HL * align256(sizeof(float) * c * l.HW));   // head Y (else in the reserve)
 }
@@ -2046,7 +2074,7 @@ long top_rows(long n, int tile) { return (n + tile - 1) / tile; }
 size_t bwd_bytes(const Layout& l, int prec, long n, bool keep) {
     const long c = n < kChunk ? n : kChunk;
     const long wmax = l.W > l.in0p ? l.W : l.in0p;
-    return weights_bytes(l, prec) + 2 * align256(sizeof(float) * c * l.in0p) +
+    return weights_bytes(l, prec, keep) + 2 * align256(sizeof(float) * c * l.in0p) +
            (keep ? 1 : 3) * (size_t)l.L * align256(sizeof(float) * c * l.W) +  // Hdot (and Z, H)
            4 * align256(sizeof(float) * c * l.W) +                  // Hbar, Hdotbar, Zbar, Zdotbar
            (keep ? 1 : 2) * (size_t)l.HL * align256(sizeof(float) * c * l.HW) +  // head Ybar (and Y)
@@ -2104,7 +2132,7 @@ int mlp_forward(const rfvr_mlp* net, const float* xyz, long n, float* sdf, float
     const float beta = net->softplus_beta, half = net->half_size, inv_half = 1.0f / net->half_size;
     const long chunk = n < kChunk ? n : kChunk;
     WsCursor cur{reinterpret_cast<char*>(ws), 0};
-    const Weights w = take_weights(cur, l, net->precision);
+    const Weights w = take_weights(cur, l, net->precision, false);
     float* X0 = cur.take<float>((size_t)chunk * l.in0p);
     float* Hw[16];
     for (int i = 0; i < l.L && !keep; ++i) Hw[i] = cur.take<float>((size_t)chunk * l.W);
@@ -2256,7 +2284,7 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
     const long chunk = n < kChunk ? n : kChunk;
     const long wmax = l.W > l.in0p ? l.W : l.in0p;
     WsCursor cur{reinterpret_cast<char*>(ws), 0};
-    const Weights w = take_weights(cur, l, net->precision);
+    const Weights w = take_weights(cur, l, net->precision, keep);
     float* X0 = cur.take<float>((size_t)chunk * l.in0p);
     float* X0d = cur.take<float>((size_t)chunk * l.in0p);
     float *Zw[16], *Hw[16], *Hd[16];
@@ -2305,7 +2333,7 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
         } else {
             // one dual GEMM per layer: (Z_i, H_i) and Hdot_i share W_i
             gemm_dual<EPI2_FWD>(da(X0, X0d, l.in0p, w.Wp[0], l.in0p, P + l.ob[0], nullptr, nullptr, Z[0], H[0], Hd[0],
-                                   l.W, m, l.W, l.in0p, beta), w.Wp[0].f ? MM_MFMA32 : MM_FP32, st);
+                                   l.W, m, l.W, l.in0p, beta), MM_MFMA32, st);
             for (int i = 1; i < l.L; ++i)
                 gemm_dual<EPI2_FWD>(da(H[i - 1], Hd[i - 1], l.W, w.Wp[i], l.W, P + l.ob[i], nullptr, nullptr, Z[i],
                                        H[i], Hd[i], l.W, m, l.W, l.W, beta), cxf.mm, st);
