@@ -53,8 +53,8 @@ namespace rfvr {
 constexpr int kChebKs[] = {24, 28, 32, 40, 48, 64};
 constexpr int kChebKMax = kChebMaxOrder;
 // truncation bound, relative to the sum of the term magnitudes: of the order of
-// the FP32 rounding of the sums themselves (a lane's moments accumulate a
-// point split of ~2k points in FP32)
+// the FP32 rounding of the sums themselves (a lane's moments accumulate a point
+// split in FP32, 2048 points at 2^20 x 1024; with cells runs of 64)
 constexpr double kChebLogTol = -13.815510557964274;   // log 1e-6
 
 // ---------------------------------------------------------------------------
@@ -1192,19 +1192,24 @@ __device__ __forceinline__ void cell_interval(const CellGrid& g, int c, const An
     h = 0.5 * (b - a);
 }
 
-// the cell's nodes in the box's normalised range, X_l
+// the cell's nodes in the box's normalised range, X_l = x_l + d_l: a node's rounding is
+// shared by all of the cell's points, so its remainder goes into the recurrences too
 template <int K>
-__device__ __forceinline__ void node_args(double rc, double h, const MeasCheb& box, float (&x)[K]) {
+__device__ __forceinline__ void node_args(double rc, double h, const MeasCheb& box, float (&x)[K], float (&d)[K]) {
 #pragma unroll
-    for (int l = 0; l < K; ++l) x[l] = (float)((rc + h * (double)kNodeCos<K>.c[l][1] - box.rc) * box.inv_h);
+    for (int l = 0; l < K; ++l) {
+        const double X = (rc + h * (double)kNodeCos<K>.c[l][1] - box.rc) * box.inv_h;
+        x[l] = (float)X;
+        d[l] = (float)(X - (double)x[l]);
+    }
 }
 
 // a cell's series coefficients b from the box's, B[0 .. KP)
 template <int K>
 __device__ __forceinline__ void cell_down(const float2* __restrict__ B, int KP, double rc, double h, const MeasCheb& box,
                                           float2* __restrict__ b) {
-    float x[K], tm[K], tk[K], fr[K], fi[K];
-    node_args<K>(rc, h, box, x);
+    float x[K], d[K], tm[K], tk[K], fr[K], fi[K];
+    node_args<K>(rc, h, box, x, d);
     // two orders per step (all KP are even), the next two on the way meanwhile
     const float4* B4 = reinterpret_cast<const float4*>(B);
     float4 v = B4[0], w = B4[1];
@@ -1220,9 +1225,9 @@ __device__ __forceinline__ void cell_down(const float2* __restrict__ B, int KP, 
         w = B4[min(k / 2 + 1, KP / 2 - 1)];
 #pragma unroll
         for (int l = 0; l < K; ++l) {
-            const float x2 = x[l] + x[l];
-            tm[l] = __builtin_fmaf(x2, tk[l], -tm[l]);
-            tk[l] = __builtin_fmaf(x2, tm[l], -tk[l]);
+            const float x2 = x[l] + x[l], d2 = d[l] + d[l];
+            tm[l] = __builtin_fmaf(x2, tk[l], __builtin_fmaf(d2, tk[l], -tm[l]));
+            tk[l] = __builtin_fmaf(x2, tm[l], __builtin_fmaf(d2, tm[l], -tk[l]));
             fr[l] = __builtin_fmaf(v.z, tk[l], __builtin_fmaf(v.x, tm[l], fr[l]));
             fi[l] = __builtin_fmaf(v.w, tk[l], __builtin_fmaf(v.y, tm[l], fi[l]));
         }
@@ -1276,8 +1281,8 @@ __device__ __forceinline__ void cell_series(const float2 (&b)[K], float x, float
 template <int K>
 __device__ __forceinline__ void cell_up(const float (&mr)[K], const float (&mi)[K], int KP, double rc, double h,
                                         const MeasCheb& box, float2* __restrict__ M) {
-    float x[K], tm[K], tk[K], ur[K], ui[K];
-    node_args<K>(rc, h, box, x);
+    float x[K], d[K], tm[K], tk[K], ur[K], ui[K];
+    node_args<K>(rc, h, box, x, d);
     float m0r = 0.0f, m0i = 0.0f, m1r = 0.0f, m1i = 0.0f;
 #pragma unroll
     for (int l = 0; l < K; ++l) {
@@ -1302,9 +1307,9 @@ __device__ __forceinline__ void cell_up(const float (&mr)[K], const float (&mi)[
         float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
         for (int l = 0; l < K; ++l) {
-            const float x2 = x[l] + x[l];
-            tm[l] = __builtin_fmaf(x2, tk[l], -tm[l]);
-            tk[l] = __builtin_fmaf(x2, tm[l], -tk[l]);
+            const float x2 = x[l] + x[l], d2 = d[l] + d[l];
+            tm[l] = __builtin_fmaf(x2, tk[l], __builtin_fmaf(d2, tk[l], -tm[l]));
+            tk[l] = __builtin_fmaf(x2, tm[l], __builtin_fmaf(d2, tm[l], -tk[l]));
             v.x = __builtin_fmaf(ur[l], tm[l], v.x);
             v.y = __builtin_fmaf(ui[l], tm[l], v.y);
             v.z = __builtin_fmaf(ur[l], tk[l], v.z);
@@ -1359,8 +1364,26 @@ __global__ __launch_bounds__(256) void k_cell_points(const ChebPlan* __restrict_
     float mr[K], mi[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) mr[k] = mi[k] = 0.0f;
-    cheb_moments<K, KIND, SPEC, BI>(A, Rx, rc, 1.0 / h, Kc, reinterpret_cast<const Rec*>(recs_v), (long)first,
-                                    (long)first + count, mr, mi);
+    // Runs of kCellRun points summed by themselves: the FP32 sums of a whole unit (4096
+    // points at 2^20 points x 1024 measurements) round twice as long as those of a split
+    // without cells, which was 16 to 33 % of the outputs' error (against 64 bits: 2^19 points
+    // in a 25 cm cube 5.8e-7, 4.3e-7 without cells, 3.1e-7 in runs of 64; 128: 3.3e-7,
+    // 256: 3.7e-7, all within 1 % of the time).
+    constexpr int kCellRun = 64;
+    const double inv_h = 1.0 / h;
+    const long end = (long)first + count;
+    for (long j = first; j < end; j += kCellRun) {
+        float br[K], bi[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) br[k] = bi[k] = 0.0f;
+        cheb_moments<K, KIND, SPEC, BI>(A, Rx, rc, inv_h, Kc, reinterpret_cast<const Rec*>(recs_v), j, min(j + kCellRun, end),
+                                        br, bi);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            mr[k] += br[k];
+            mi[k] += bi[k];
+        }
+    }
     if (i < n_meas)
         cell_up<K>(mr, mi, plan->K, rc, h, meas[ic], partial + ((size_t)unit * n_meas + i) * kChebKMax);
 }
