@@ -83,7 +83,7 @@ extern "C" {
  * ((n_freq - 1)/2) df 2h/c, h the half-width of the widest interval) is below
  * 1e-6 of the sum of the term magnitudes.  Large calls sort their points into
  * cells of the box and take fewer orders on each cell's own interval, within
- * another 5e-7.  The choice is made on the device
+ * the same 1e-6 in all.  The choice is made on the device
  * for every call; when no K qualifies (a range spread too wide for the band)
  * or K is not below n_freq, the per-frequency kernels run, which
  * RFVR_TERMS_DIRECT (and RFVR_PHASE_NAIVE32) also select.  Both evaluate the

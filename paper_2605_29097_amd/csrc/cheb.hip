@@ -56,6 +56,9 @@ constexpr int kChebKMax = kChebMaxOrder;
 // the FP32 rounding of the sums themselves (a lane's moments accumulate a point
 // split in FP32, 2048 points at 2^20 x 1024; with cells runs of 64)
 constexpr double kChebLogTol = -13.815510557964274;   // log 1e-6
+// ... and of the box's series where cells add their own cut to it, so that both
+// together stay within the same 1e-6 (orders of the box cost nothing per pair there)
+constexpr double kChebCellsLogTol = -14.508657738524219;   // log 5e-7
 
 // ---------------------------------------------------------------------------
 // bounding box of a launch's points: per-block min / max, then the plan
@@ -104,7 +107,8 @@ static_assert(sizeof(kChebLogFact) / sizeof(double) == kChebNK, "one per order")
 // orders of a cell's series and log K!; 2.5e-7 bounds 2 (z/2)^K / K! / (1 - ...)
 // there: interpolation at K nodes is within twice that of the function
 constexpr int kCellKs[] = {8, 10, 12, 14, 16};
-constexpr int kCellNK = (int)(sizeof(kCellKs) / sizeof(kCellKs[0])), kCellKMax = 16;
+constexpr int kCellNK = (int)(sizeof(kCellKs) / sizeof(kCellKs[0]));
+static_assert(kCellKs[kCellNK - 1] < kChebKs[0], "cells take fewer orders than any box");
 __device__ constexpr double kCellLogFact[] = {10.604602902745250, 15.104412573075516, 19.987214495661885,
                                               25.191221182738680, 30.671860106080672};
 constexpr double kCellLogTol = -15.201804919084164;   // log 2.5e-7
@@ -255,10 +259,11 @@ __global__ __launch_bounds__(kPlanThreads) void k_cheb_plan(const float* __restr
     // one lane per candidate order, the smallest that qualifies
     if (t < 64) {
         const int c = t < kChebNK ? t : kChebNK - 1, k = kChebKs[c];
-        const bool ok = t < kChebNK && finite && k < n_freq && cheb_log_bound(k, kChebLogFact[c], zmax) <= kChebLogTol;
-        const unsigned long long m = __ballot(ok);
+        const bool fits = t < kChebNK && finite && k < n_freq;
+        const double bound = cheb_log_bound(k, kChebLogFact[c], zmax);
+        const unsigned long long m = __ballot(fits && bound <= kChebLogTol), mc = __ballot(fits && bound <= kChebCellsLogTol);
         int KC = 0;
-        if (grid && m) {
+        if (grid && mc) {
             // the finest of 1 .. 64 divisions of the box's longest edge, the others
             // cut alike, that gives at most max_cells cells
             const double e[3] = {bh[0] - bl[0], bh[1] - bl[1], bh[2] - bl[2]};
@@ -294,8 +299,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_cheb_plan(const float* __restr
         }
         if (t == 0) {
             ChebPlan p;
-            p.K = m ? kChebKs[__ffsll(m) - 1] : 0;
-            p.KC = p.K > KC ? KC : 0;
+            p.K = m ? kChebKs[__ffsll(KC ? mc : m) - 1] : 0;
+            p.KC = KC;                           // below every order of the box
             p.zmax = zmax;
             *plan = p;
         }
