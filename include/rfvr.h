@@ -20,8 +20,7 @@
  * - Outputs are overwritten, except gradient outputs when `flags` contains
  *   RFVR_ACCUMULATE, which then add into the existing contents.
  * - Reductions use a fixed split and a fixed summation order and no floating
- *   point atomics: results are bitwise reproducible for fixed shapes (and, of
- *   the filter forward, a fixed workspace size: see there).
+ *   point atomics: results are bitwise reproducible for fixed shapes.
  * - NaN/Inf inside arrays propagate; only descriptor scalars are checked.  (An
  *   infinity that a network product meets can come out as NaN: its operands
  *   are split in parts.)
@@ -200,9 +199,6 @@ int rfvr_render_backward(const rfvr_aperture* ap, const rfvr_samples* sm, const 
  * xyz_q: [n_q][3] query points.  signal2: optional second signal filtered at
  * the same points (e.g. the measured one), with outputs z2/power2.
  * Any of z, power, z2, power2 may be NULL.  flags: 0 or RFVR_PHASE_NAIVE32.
- * The query includes room for splits of the measurements (few points) or cells
- * (many); a smaller workspace, down to what the call cannot do without, is
- * accepted and takes fewer or none, with results that differ by rounding.
  * ------------------------------------------------------------------------ */
 size_t rfvr_mf_forward_ws_bytes(const rfvr_aperture* ap, int64_t n_q, int two_signals);
 int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, uint32_t flags,
@@ -219,7 +215,10 @@ int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, ui
  * process ends.  It allocates nothing.  A call whose records, coefficients and
  * padded signals exceed RFVR_MF_STATIC_SCRATCH_BYTES returns RFVR_E_INVALID and
  * enqueues nothing (1024 measurements x 128 frequencies need 1.6 MB with one
- * signal, 3.1 MB with two).  Every call on one GPU uses that GPU's one array,
+ * signal, 3.1 MB with two).  Where the array does not hold all that
+ * rfvr_mf_forward_ws_bytes() asks for, the call splits its measurements less or
+ * sorts its points into no cells, by its shape alone, and differs from
+ * rfvr_mf_forward by rounding.  Every call on one GPU uses that GPU's one array,
  * which keeps the last call's contents (nothing in it needs clearing between
  * calls): calls that overlap in time on one GPU, on different streams or
  * from several host threads, race and give wrong results, so the caller

@@ -239,7 +239,7 @@ static size_t ws_render_backward(const RenderGeom& g) {
 }
 
 // what the filter forward cannot do without; its query adds the cells, and the
-// sums of the measurement splits: a call uses what its workspace has room for
+// sums of the measurement splits (the static scratch may hold less of these)
 static size_t ws_mf_forward(const rfvr_aperture* ap, long n_q, int two) {
     const size_t np = padded_freq(ap->n_freq);
     return ant_bytes(ap->n_meas, ap->rx != nullptr) +
@@ -463,9 +463,11 @@ size_t rfvr_mf_forward_ws_bytes(const rfvr_aperture* ap, int64_t n_q, int two_si
     return ws_mf_forward_full(ap, (long)n_q, two_signals);
 }
 
-int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, uint32_t flags,
-                    const float* signal, float* z, float* power, const float* signal2, float* z2,
-                    float* power2, void* ws, size_t ws_bytes, void* stream) {
+// part: the workspace may hold a part of the query only; the call then takes as many
+// splits as fit, and no cells if those do not
+static int mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, uint32_t flags, const float* signal, float* z,
+                      float* power, const float* signal2, float* z2, float* power2, void* ws, size_t ws_bytes, bool part,
+                      void* stream) {
     int rc;
     if ((rc = check_aperture(ap))) return rc;
     if (flags & ~(uint32_t)(RFVR_PHASE_NAIVE32 | RFVR_TERMS_DIRECT)) {
@@ -475,7 +477,7 @@ int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, ui
     if (!xyz_q || !signal) { set_error("xyz_q and signal are required"); return RFVR_E_INVALID; }
     if ((rc = check_count("n_q", n_q))) return rc;
     const int two = signal2 ? 1 : 0;
-    if ((rc = check_ws(ws, ws_bytes, ws_mf_forward(ap, (long)n_q, two)))) return rc;
+    if ((rc = check_ws(ws, ws_bytes, part ? ws_mf_forward(ap, (long)n_q, two) : ws_mf_forward_full(ap, (long)n_q, two)))) return rc;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     RenderGeom g = make_geom(ap, 1, 1);
     const int np = padded_freq(ap->n_freq);
@@ -525,6 +527,12 @@ int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, ui
                       "mf forward");
 }
 
+int rfvr_mf_forward(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, uint32_t flags,
+                    const float* signal, float* z, float* power, const float* signal2, float* z2,
+                    float* power2, void* ws, size_t ws_bytes, void* stream) {
+    return mf_forward(ap, xyz_q, n_q, flags, signal, z, power, signal2, z2, power2, ws, ws_bytes, false, stream);
+}
+
 int rfvr_mf_forward_static(const rfvr_aperture* ap, const float* xyz_q, int64_t n_q, uint32_t flags,
                            const float* signal, float* z, float* power, const float* signal2, float* z2,
                            float* power2, void* stream) {
@@ -540,8 +548,8 @@ int rfvr_mf_forward_static(const rfvr_aperture* ap, const float* xyz_q, int64_t 
     }
     void* ws = nullptr;
     if ((rc = static_scratch(&ws))) return rc;
-    return rfvr_mf_forward(ap, xyz_q, n_q, flags, signal, z, power, signal2, z2, power2, ws,
-                           (size_t)RFVR_MF_STATIC_SCRATCH_BYTES, stream);
+    return mf_forward(ap, xyz_q, n_q, flags, signal, z, power, signal2, z2, power2, ws,
+                      (size_t)RFVR_MF_STATIC_SCRATCH_BYTES, true, stream);
 }
 
 size_t rfvr_mf_backward_ws_bytes(const rfvr_aperture* ap, int64_t n_q) {
