@@ -21,9 +21,7 @@
  *   RFVR_ACCUMULATE, which then add into the existing contents.
  * - Reductions use a fixed split and a fixed summation order and no floating
  *   point atomics: results are bitwise reproducible for fixed shapes.
- * - NaN/Inf inside arrays propagate; only descriptor scalars are checked.  (An
- *   infinity that a network product meets can come out as NaN: its operands
- *   are split in parts.)
+ * - NaN/Inf inside arrays propagate; only descriptor scalars are checked.
  *
  * Notation: i = measurement (a transmitter and its receiver: the same antenna
  * for a monostatic aperture, rx = NULL), n = frequency with

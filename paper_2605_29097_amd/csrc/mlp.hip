@@ -602,6 +602,74 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g) {
 // ----------------------------------------------------------------------------
 __device__ __forceinline__ int frag_slot(int row, int kg) { return kg * 16 + (row ^ (kg * 2)); }
 
+// An infinite operand has no parts (its remainders are NaN), nor has a number that
+// rounds to infinity in BF16 (beyond 3.39e38).  Either makes every sum that it enters
+// NaN, so a wave that finds one among its sums forms its tiles again on the FP32
+// instruction and takes its sums in place of those: infinities propagate as in plain
+// FP32, and other points and outputs keep theirs.
+template <int TP, int TM>
+__device__ __forceinline__ bool any_nan(const floatx4 (&acc)[TP][TM]) {
+    float t[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};          // eight chains side by side
+#pragma unroll
+    for (int a = 0; a < TP; ++a)
+#pragma unroll
+        for (int b = 0; b < TM; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) t[(b & 1) * 4 + v] = __builtin_fmaf(acc[a][b][v], 0.0f, t[(b & 1) * 4 + v]);
+    const float s = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+    return __ballot(s != s) != 0;
+}
+
+// four weights of one row from a three-part image (k a multiple of 4)
+__device__ __forceinline__ floatx4 image_row4(const uint16_t* img, int bm, int nk, int m, int k) {
+    const uint16_t* t = img + ((long)(m / bm) * nk + k / 32) * 3 * bm * 32 + (m % bm / 16) * 512 +
+                        ((k % 32 / 8) * 16 + m % 16) * 8 + k % 8;
+    floatx4 w = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int q = 2; q >= 0; --q) {               // exact from the smallest part on
+        const uint2 r = *reinterpret_cast<const uint2*>(t + (long)q * bm * 32);
+        const float4 p = widen_bf16x4(r);
+        const float pv[4] = {p.x, p.y, p.z, p.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = (q == 0 && fabsf(pv[e]) == INFINITY) ? pv[e] : w[e] + pv[e];
+    }
+    return w;
+}
+
+// t where acc is no number
+__device__ __forceinline__ void take_where_nan(floatx4& acc, const floatx4& t) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = __builtin_fmaf(acc[v], 0.0f, 0.0f) == 0.0f ? acc[v] : t[v];
+}
+
+// the sums that are no numbers of pro(A) W^T, for the wave's TP x TM tiles from point
+// row p and weight row m on (a tile at a time: no second set of accumulators)
+template <int PRO, int TP, int TM, bool POINTS_FIRST>
+__device__ __forceinline__ void fp32_tiles(floatx4 (&acc)[TP][TM], const float* A, long lda, long P, long p, const uint16_t* img,
+                                           int bm, int nk, int m, float beta, const float* colv) {
+    const int li = threadIdx.x & 15, lg = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int a = 0; a < TP; ++a)
+#pragma unroll
+        for (int b = 0; b < TM; ++b) {
+            const float* row = A + min(p + a * 16 + li, P - 1) * lda;
+            floatx4 t = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+            for (int k = 4 * lg; k < nk * 32; k += 16) {
+                floatx4 x = *reinterpret_cast<const floatx4*>(row + k);
+                const floatx4 w = image_row4(img, bm, nk, m + b * 16 + li, k);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (PRO == PRO_RELU) x[e] = fmaxf(x[e], 0.0f);
+                    if constexpr (PRO == PRO_SEED) x[e] = sp_d1_h(x[e], beta) * colv[k + e];
+                    t = POINTS_FIRST ? __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], w[e], t, 0, 0, 0)
+                                     : __builtin_amdgcn_mfma_f32_16x16x4f32(w[e], x[e], t, 0, 0, 0);
+                }
+            }
+            take_where_nan(acc[a][b], t);
+        }
+}
+
 // T x T tiles; HB output tiles of a wave are multiplied at a time: with two,
 // three waves fit on a SIMD (all four, at two waves, read less LDS: better
 // where no third work-group would come to the CU anyway).
@@ -701,6 +769,11 @@ __global__ __launch_bounds__(256, T != 128 ? 4 : (HB == 4 || EPI == EPI_TOPADJ) 
             }
         }
         __syncthreads();
+    }
+    if constexpr (N == 3) {
+        if (any_nan(acc))
+            fp32_tiles<PRO, TP, TM, false>(acc, g.A, g.lda, g.P, p0 + wp * (BP / WP), g.Bx, bm, nk, m0 + wm * (BM / WM), g.beta,
+                                           g.colv);
     }
     gemm_epilogue<EPI, BP, BM, WP, 0>(g, acc, reinterpret_cast<float*>(sA), p0, m0);
 }
@@ -1022,6 +1095,12 @@ __global__ __launch_bounds__(256, 2) void k_gemm_dual32(DualArgs g) {
         }
         __syncthreads();
     }
+    if constexpr (N == 3) {
+        const long pw = p0 + wp * (BP / WP);
+        const int mw = m0 + wm * (BM / 2);
+        if (any_nan(acc)) fp32_tiles<PRO_ID, TP, TM, true>(acc, g.A, g.lda, g.P, pw, g.Bx, BM, nk, mw, g.beta, nullptr);
+        if (any_nan(acd)) fp32_tiles<PRO_ID, TP, TM, true>(acd, g.A2, g.lda, g.P, pw, g.Bx, BM, nk, mw, g.beta, nullptr);
+    }
     epi.finish(g, acc, acd, p0, m0);
 }
 
@@ -1337,6 +1416,31 @@ __global__ __launch_bounds__(256, T == 128 ? 2 : 3) void k_gemm_wg32(WgArgs g) {
             for (int b = 0; b < TW; ++b) acc[a][b] *= g.scale2;
     }
     pass(std::integral_constant<int, ST>{}, std::true_type{}, g.A, g.B);
+    if constexpr (N == 3) {
+        if (any_nan(acc)) {                      // on the FP32 instruction: see any_nan
+            const auto add = [&](auto st_c, const float* A, const float* B, int m, int k, floatx4 t) {
+                constexpr int S = decltype(st_c)::value;
+#pragma unroll 1
+                for (long q = pb; q < pe; q += 4) {
+                    const bool in = q + lg < pe;
+                    float x = 0.0f, y = in && k < g.Kout ? B[(q + lg) * g.ldb + k] : 0.0f;
+                    if (in && m < g.M) x = (S & ST_A) ? ld_bf16(A, (q + lg) * g.lda + m) : A[(q + lg) * g.lda + m];
+                    if constexpr (PRO == PRO_RELU) y = fmaxf(y, 0.0f);
+                    t = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, t, 0, 0, 0);
+                }
+                return t;
+            };
+#pragma unroll
+            for (int a = 0; a < TW; ++a)
+#pragma unroll
+                for (int b = 0; b < TW; ++b) {
+                    const int m = m0 + (wp * TW + a) * 16 + li, k = n0 + (wn * TW + b) * 16 + li;
+                    floatx4 t = {0.0f, 0.0f, 0.0f, 0.0f};
+                    if constexpr (ST2 >= 0) t = add(std::integral_constant<int, ST2 < 0 ? 0 : ST2>{}, g.A2, g.B2, m, k, t) * g.scale2;
+                    take_where_nan(acc[a][b], add(std::integral_constant<int, ST>{}, g.A, g.B, m, k, t));
+                }
+        }
+    }
     float* out = g.part + split * (long)g.M * g.Kout;
 #pragma unroll
     for (int a = 0; a < TW; ++a)
@@ -1676,6 +1780,16 @@ __global__ void k_prep_weights(PrepTable t) {
             }
             bf16x8 part[3];
             split_bf16x8(lo, hi, part);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {        // beyond BF16's range: from its largest number on
+                const float x = e < 4 ? lo[e] : hi[e - 4];
+                if (fabsf((float)part[0][e]) != INFINITY) continue;
+                part[1][e] = part[2][e] = (__bf16)0.0f;
+                if (fabsf(x) == INFINITY) continue;
+                part[0][e] = (__bf16)copysignf(3.3895313892515355e38f, x);
+                part[1][e] = (__bf16)(x - (float)part[0][e]);
+                part[2][e] = (__bf16)(x - (float)part[0][e] - (float)part[1][e]);
+            }
             uint16_t* out = reinterpret_cast<uint16_t*>(j.out) + (long)blk * 3 * tiles * 512;
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<bf16x8*>(&out[((long)q * tiles + tile) * 512 + slot * 8]) = part[q];
