@@ -62,13 +62,16 @@ def network_digest() -> str:
 
 def cell_order(K, xyz, ap) -> int:
     """Order of the cells' series in the render of these points (the rule of the
-    library's plan kernel): 0 where the launch has no cells."""
+    library's plan kernel, held to its source by tests/test_term_plan_rules.py): 0
+    where the launch has no cells."""
     import torch
     n = xyz.numel() // 3
     if K == 0 or n * ap.n_meas < 1 << 27 or ap.n_meas < 512 or n < 1 << 16 or n > 1 << 24:
         return 0
     x = xyz.reshape(-1, 3)
     e = (x.amax(0).double() - x.amin(0).double()).tolist()
+    if max(e) == 0.0:
+        return 0
     most = min(512, n // 256, (1 << 21) // ap.n_meas)
     cut = lambda t: [max(1, math.ceil(v * t / max(e) - 1e-6)) for v in e]
     d = cut(max(t for t in range(1, 65) if math.prod(cut(t)) <= most))
