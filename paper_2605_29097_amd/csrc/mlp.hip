@@ -1126,7 +1126,6 @@ struct WgArgs {
     float* bpart;                              // [n_split][M]
     long P; int M; int Kout; long per_split;
     int n_split;
-    float beta;
 };
 
 // Three waves per SIMD but for a pair in FP32 storage (the plain backward), whose two
@@ -2139,7 +2138,6 @@ GemmArgs ga(const float* A, long lda, const WMat& B, long ldb, const float* bias
     return g;
 }
 
-// ST != 0 (BF16 storage of operands): the FP32 and single-rounded BF16 forms
 // 64 x 64 tiles where they cover at most half of what 128 x 128 ones do: the matrix
 // cores then bound the padded product (262144 points, 64 x 64 and 64 x 32: 70 and
 // 68 -> 33 and 32 us; a trunk's first layer, 256 x 64 at 150001 points: 148 -> 111)
@@ -2408,7 +2406,7 @@ int mlp_backward(const rfvr_mlp* net, const float* xyz, long n, const float* g_s
         return rc;
     // cxf: the plain backward's recompute of the forward products, in the
     // forward's operand form; cx: the backward's own products
-    const Cx cx{st, mm_bwd(net->precision)}, cxf{st, mm_fwd(net->precision)}, cx32{st, MM_FP32};
+    const Cx cx{st, mm_bwd(net->precision)}, cxf{st, mm_fwd(net->precision)};
     // the training pair's weight gradients run on the side stream when the
     // products are bound by the matrix cores (FP32); the BF16 forms are bound by
     // HBM and gain nothing measurable from it
