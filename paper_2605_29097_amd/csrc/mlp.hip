@@ -2008,9 +2008,11 @@ dim3 gemm_grid(long P, int tp, int M, int bm) {
 }
 
 // Tile of the split products: 128 x 128 where they fill the 256 CUs; below that the
-// 64 x 64 ones put four times the work-groups on the chip (a forward of the
-// 8 x 256 network at 5120 points, 80 large tiles: 345 us with them, 213 with
-// the small ones).
+// 64 x 64 ones put four times the work-groups on the chip.  Training backward of the
+// 8 x 256 network with 64 | 128, in us: 4096 points (64 large tiles) 637 | 764, 12000
+// (192) 838 | 933, 16384 (256) 879 | 858, 20000 (320) 1063 | 1052, 24000 (384) 1127 |
+// 1160, 28000 (448) 1231 | 1277, 32768 (512) 1326 | 1274, 131072 4610 | 4365: from
+// one tile a CU on either side wins by a few per cent as the last round is full or not.
 int split_tile(long P, int M) { return M <= 64 || gemm_grid(P, 128, M, 128).x < 384 ? 64 : 128; }
 
 template <int PRO, int EPI, int MM, int ST = 0>
@@ -2020,8 +2022,11 @@ void gemm_launch(const GemmArgs& a, hipStream_t st) {
     if constexpr (MM == MM_FP32 || MM == MM_BF16X3) {
         static_assert(ST == 0, "the split kernel has no BF16 storage");
         constexpr int N = split_parts(MM);
-        // up to two large tiles a CU take all their outputs at a time (training
-        // pair at 32768 points, 512 tiles: 3.21 ms in halves, 3.12)
+        // Up to two large tiles a CU (512) take all their outputs at a time: two waves per
+        // SIMD are all that come then, and LDS is read less; above, three fit in halves.
+        // Training backward of the 8 x 256 network, all | halves, in us: 24000 points
+        // (384 tiles) 1157 | 1184, 32768 (512) 1266 | 1282, 36000 (576) 1610 | 1577,
+        // 65536 2321 | 2379, 2^20 31537 | 31456 (its forward with the sweep 17722 | 17089).
         const dim3 g128 = gemm_grid(a.P, 128, a.M, 128);
         if (split_tile(a.P, a.M) == 64)
             hipLaunchKernelGGL((k_gemm_nt32<PRO, EPI, 64, 2, N>), gemm_grid(a.P, 64, a.M, 64), dim3(256), 0, st, a);
@@ -2031,8 +2036,11 @@ void gemm_launch(const GemmArgs& a, hipStream_t st) {
             hipLaunchKernelGGL((k_gemm_nt32<PRO, EPI, 128, 2, N>), g128, dim3(256), 0, st, a);
     } else {
         if constexpr (MM == MM_MFMA32 && ST == 0) {
-            // the same rule, and the same sums: a tile's k order does not depend on its size
-            if (grid.x < 384) {
+            // 64 x 64 tiles below two large ones a CU; the sums are the same, a tile's k order
+            // does not depend on its size.  Training forward of the 8 x 256 network, 64 |
+            // 128, in us: 4096 points 185 | 296, 28000 (448 large tiles) 657 | 748, 32768
+            // (512) 668 | 642, 49152 (768) 943 | 936, 65536 1231 | 1311, 98304 1786 | 1740.
+            if (grid.x < 512) {
                 hipLaunchKernelGGL((k_gemm_nt<PRO, EPI, 64, MM, ST, 64>), gemm_grid(a.P, 64, a.M, 64), dim3(256), 0, st, a);
                 return;
             }

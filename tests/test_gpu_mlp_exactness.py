@@ -53,7 +53,7 @@ def _chain(h, w, b):
 
 
 @pytest.mark.parametrize("n,width,head,layers", [(65, 64, 64, 2), (129, 192, 128, 3), (4133, 256, 64, 2),
-                                                 (24001, 256, 192, 2), (49157, 128, 64, 1)])
+                                                 (24001, 256, 192, 2), (49157, 128, 64, 1), (70001, 256, 192, 2)])
 def test_values_are_fp32_multiply_add_chains(n, width, head, layers):
     """With a softplus so sharp that it is a relu beyond |z| = 2e-4, H shows the trunk's pre-activations too.  Sizes on
     both sides of the rule for 64- and 128-point tiles; the first and the last rows are compared."""
