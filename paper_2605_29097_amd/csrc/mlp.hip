@@ -606,7 +606,10 @@ __device__ __forceinline__ int frag_slot(int row, int kg) { return kg * 16 + (ro
 // rounds to infinity in BF16 (beyond 3.39e38).  Either makes every sum that it enters
 // NaN, so a wave that finds one among its sums forms its tiles again on the FP32
 // instruction and takes its sums in place of those: infinities propagate as in plain
-// FP32, and other points and outputs keep theirs.
+// FP32, and other points and outputs keep theirs.  Sums with a NaN among their operands
+// are NaN either way: one look at the operands leaves them out (without it the backward
+// with a NaN point in a thousand took 41 ms at 262144 points, with it 10.5; 8.2 without
+// NaN).
 template <int TP, int TM>
 __device__ __forceinline__ bool any_nan(const floatx4 (&acc)[TP][TM]) {
     float t[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};          // eight chains side by side
@@ -637,9 +640,25 @@ __device__ __forceinline__ floatx4 image_row4(const uint16_t* img, int bm, int n
 }
 
 // t where acc is no number
+__device__ __forceinline__ bool no_number(float x) { return __builtin_fmaf(x, 0.0f, 0.0f) != 0.0f; }
 __device__ __forceinline__ void take_where_nan(floatx4& acc, const floatx4& t) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] = __builtin_fmaf(acc[v], 0.0f, 0.0f) == 0.0f ? acc[v] : t[v];
+    for (int v = 0; v < 4; ++v) acc[v] = no_number(acc[v]) ? t[v] : acc[v];
+}
+
+// of 16 rows, one per lane modulo 16, those for which a lane has f
+__device__ __forceinline__ uint32_t rows_with(bool f) {
+    const unsigned long long m = __ballot(f);
+    return (uint32_t)((m | m >> 16 | m >> 32 | m >> 48) & 0xffff);
+}
+// whether a tile has a sum that is no number although its row (4 lg + v, of `rows`) and
+// its column (li, of `cols`) are without NaN
+__device__ __forceinline__ bool wants_fp32(const floatx4& acc, uint32_t rows, uint32_t cols) {
+    const int li = threadIdx.x & 15, lg = (threadIdx.x & 63) >> 4;
+    bool w = false;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) w |= no_number(acc[v]) && !(rows >> (4 * lg + v) & 1) && !(cols >> li & 1);
+    return __ballot(w) != 0;
 }
 
 // the sums that are no numbers of pro(A) W^T, for the wave's TP x TM tiles from point
@@ -648,23 +667,44 @@ template <int PRO, int TP, int TM, bool POINTS_FIRST>
 __device__ __forceinline__ void fp32_tiles(floatx4 (&acc)[TP][TM], const float* A, long lda, long P, long p, const uint16_t* img,
                                            int bm, int nk, int m, float beta, const float* colv) {
     const int li = threadIdx.x & 15, lg = (threadIdx.x & 63) >> 4;
+    const auto point4 = [&](int a, int k) {
+        floatx4 x = *reinterpret_cast<const floatx4*>(A + min(p + a * 16 + li, P - 1) * lda + k);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (PRO == PRO_RELU) x[e] = fmaxf(x[e], 0.0f);
+            if constexpr (PRO == PRO_SEED) x[e] = sp_d1_h(x[e], beta) * colv[k + e];
+        }
+        return x;
+    };
+    const auto nan4 = [](const floatx4& x) { return x[0] != x[0] || x[1] != x[1] || x[2] != x[2] || x[3] != x[3]; };
+    uint32_t np[TP], nw[TM];                     // points and weight rows with a NaN
+#pragma unroll
+    for (int a = 0; a < TP; ++a) {
+        bool f = false;
+#pragma unroll 4
+        for (int k = 4 * lg; k < nk * 32; k += 16) f |= nan4(point4(a, k));
+        np[a] = rows_with(f);
+    }
+#pragma unroll
+    for (int b = 0; b < TM; ++b) {
+        bool f = false;
+#pragma unroll 4
+        for (int k = 4 * lg; k < nk * 32; k += 16) f |= nan4(image_row4(img, bm, nk, m + b * 16 + li, k));
+        nw[b] = rows_with(f);
+    }
 #pragma unroll
     for (int a = 0; a < TP; ++a)
 #pragma unroll
         for (int b = 0; b < TM; ++b) {
-            const float* row = A + min(p + a * 16 + li, P - 1) * lda;
+            if (!wants_fp32(acc[a][b], POINTS_FIRST ? np[a] : nw[b], POINTS_FIRST ? nw[b] : np[a])) continue;
             floatx4 t = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll 1
             for (int k = 4 * lg; k < nk * 32; k += 16) {
-                floatx4 x = *reinterpret_cast<const floatx4*>(row + k);
-                const floatx4 w = image_row4(img, bm, nk, m + b * 16 + li, k);
+                const floatx4 x = point4(a, k), w = image_row4(img, bm, nk, m + b * 16 + li, k);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if constexpr (PRO == PRO_RELU) x[e] = fmaxf(x[e], 0.0f);
-                    if constexpr (PRO == PRO_SEED) x[e] = sp_d1_h(x[e], beta) * colv[k + e];
+                for (int e = 0; e < 4; ++e)
                     t = POINTS_FIRST ? __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], w[e], t, 0, 0, 0)
                                      : __builtin_amdgcn_mfma_f32_16x16x4f32(w[e], x[e], t, 0, 0, 0);
-                }
             }
             take_where_nan(acc[a][b], t);
         }
@@ -1417,26 +1457,51 @@ __global__ __launch_bounds__(256, T == 128 ? 2 : 3) void k_gemm_wg32(WgArgs g) {
     pass(std::integral_constant<int, ST>{}, std::true_type{}, g.A, g.B);
     if constexpr (N == 3) {
         if (any_nan(acc)) {                      // on the FP32 instruction: see any_nan
-            const auto add = [&](auto st_c, const float* A, const float* B, int m, int k, floatx4 t) {
-                constexpr int S = decltype(st_c)::value;
-#pragma unroll 1
+            // operands of point q + lg (zero beyond the split): column m of A, k of B
+            const auto left = [&](auto st_c, const float* A, int m, long q) {
+                if (q + lg >= pe || m >= g.M) return 0.0f;
+                return (decltype(st_c)::value & ST_A) ? ld_bf16(A, (q + lg) * g.lda + m) : A[(q + lg) * g.lda + m];
+            };
+            const auto right = [&](const float* B, int k, long q) {
+                const float y = q + lg < pe && k < g.Kout ? B[(q + lg) * g.ldb + k] : 0.0f;
+                return PRO == PRO_RELU ? fmaxf(y, 0.0f) : y;
+            };
+            const auto st1 = std::integral_constant<int, ST>{};
+            const auto st2 = std::integral_constant<int, ST2 < 0 ? 0 : ST2>{};
+            uint32_t nm[TW], nk[TW];             // columns with a NaN
+#pragma unroll
+            for (int a = 0; a < TW; ++a) {
+                const int m = m0 + (wp * TW + a) * 16 + li, k = n0 + (wn * TW + a) * 16 + li;
+                bool fm = false, fk = false;
+#pragma unroll 8
                 for (long q = pb; q < pe; q += 4) {
-                    const bool in = q + lg < pe;
-                    float x = 0.0f, y = in && k < g.Kout ? B[(q + lg) * g.ldb + k] : 0.0f;
-                    if (in && m < g.M) x = (S & ST_A) ? ld_bf16(A, (q + lg) * g.lda + m) : A[(q + lg) * g.lda + m];
-                    if constexpr (PRO == PRO_RELU) y = fmaxf(y, 0.0f);
-                    t = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, t, 0, 0, 0);
+                    float x = left(st1, g.A, m, q), y = right(g.B, k, q);
+                    if constexpr (ST2 >= 0) {
+                        const float x2 = left(st2, g.A2, m, q), y2 = right(g.B2, k, q);
+                        fm |= x2 != x2;
+                        fk |= y2 != y2;
+                    }
+                    fm |= x != x;
+                    fk |= y != y;
                 }
+                nm[a] = rows_with(fm);
+                nk[a] = rows_with(fk);
+            }
+            const auto add = [&](auto st_c, const float* A, const float* B, int m, int k, floatx4 t) {
+#pragma unroll 1
+                for (long q = pb; q < pe; q += 4)
+                    t = __builtin_amdgcn_mfma_f32_16x16x4f32(left(st_c, A, m, q), right(B, k, q), t, 0, 0, 0);
                 return t;
             };
 #pragma unroll
             for (int a = 0; a < TW; ++a)
 #pragma unroll
                 for (int b = 0; b < TW; ++b) {
+                    if (!wants_fp32(acc[a][b], nm[a], nk[b])) continue;
                     const int m = m0 + (wp * TW + a) * 16 + li, k = n0 + (wn * TW + b) * 16 + li;
                     floatx4 t = {0.0f, 0.0f, 0.0f, 0.0f};
-                    if constexpr (ST2 >= 0) t = add(std::integral_constant<int, ST2 < 0 ? 0 : ST2>{}, g.A2, g.B2, m, k, t) * g.scale2;
-                    take_where_nan(acc[a][b], add(std::integral_constant<int, ST>{}, g.A, g.B, m, k, t));
+                    if constexpr (ST2 >= 0) t = add(st2, g.A2, g.B2, m, k, t) * g.scale2;
+                    take_where_nan(acc[a][b], add(st1, g.A, g.B, m, k, t));
                 }
         }
     }
