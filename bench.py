@@ -66,7 +66,8 @@ def cell_order(K, xyz, ap) -> int:
     where the launch has no cells."""
     import torch
     n = xyz.numel() // 3
-    if K == 0 or n * ap.n_meas < 1 << 27 or ap.n_meas < 512 or n < 1 << 16 or n > 1 << 24:
+    least = 1 << (28 if ap.n_meas < 1024 else 27)
+    if K == 0 or n * ap.n_meas < least or ap.n_meas < 512 or n < 1 << 16 or n > 1 << 24:
         return 0
     x = xyz.reshape(-1, 3)
     e = (x.amax(0).double() - x.amin(0).double()).tolist()

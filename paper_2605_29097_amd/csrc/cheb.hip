@@ -1677,6 +1677,7 @@ int cheb_point_splits(long n_pts, int n_meas) {
 //   over points (render, filter adjoint)   2^10 meas 2^16 pts 234 | 274, 215 | 245
 //     2^10 x 2^17  392 | 381, 360 | 326    2^8 x 2^20   773 | 845, 654 | 695
 //     2^10 x 2^19 1368 | 1152, 1204 | 935  2^12 x 2^15  402 | 417, 364 | 415
+//     2^9 x 2^18   445 | 459, 411 | 392: fewer than 2^10 measurements from 2^28 pairs on
 //   over frequencies (render adjoint, filter), whose work-groups take the points
 //   of one cell and are too few below 2^19 points
 //     2^10 x 2^18  925 | 985, 697 | 663    2^8 x 2^20  1138 | 1087, 597 | 552
@@ -1685,7 +1686,7 @@ int cheb_point_splits(long n_pts, int n_meas) {
 // and of 2^21 cell-measurement pairs, whose moments take 1 GiB.  Positions are 32-bit.
 int cell_count(long n_pts, int n_meas, bool over_points) {
     const double pairs = (double)n_pts * n_meas;
-    const bool pays = over_points ? pairs >= 134217728.0 && n_meas >= 512 && n_pts >= (1L << 16)
+    const bool pays = over_points ? pairs >= (n_meas < 1024 ? 268435456.0 : 134217728.0) && n_meas >= 512 && n_pts >= (1L << 16)
                                   : pairs >= 268435456.0 && n_pts >= (1L << 19);
     if (!pays || n_pts > (1L << 24)) return 0;
     return (int)std::min({(long)kMaxCells, n_pts / 256, (1L << 21) / n_meas});

@@ -31,7 +31,8 @@ def test_cuts_add_up_to_the_stated_bound():
 
 
 @pytest.mark.parametrize("n_pts,n_meas,n_freq,side", [(1 << 20, 1024, 128, 0.2), (1 << 19, 1024, 64, 0.35), (1 << 19, 576, 100, 0.5),
-                                                      (1 << 16, 2049, 64, 0.25), (1 << 20, 700, 101, 0.05)])
+                                                      (1 << 16, 2049, 64, 0.25), (1 << 20, 700, 101, 0.05),
+                                                      (1 << 18, 1023, 64, 0.2), ((1 << 17) - 1, 1024, 64, 0.2), (1 << 20, 511, 64, 0.2)])
 def test_benchmark_counts_the_plan_s_cells(n_pts, n_meas, n_freq, side):
     """bench.cell_order against the rule of k_cheb_plan and cell_count, with their constants as the source has them."""
     import bench
@@ -40,8 +41,11 @@ def test_benchmark_counts_the_plan_s_cells(n_pts, n_meas, n_freq, side):
     xyz[:8] = corners
     df = 4e9 / (n_freq - 1)
     got = bench.cell_order(24, xyz, SimpleNamespace(n_meas=n_meas, n_freq=n_freq, df=df))
-    pays = re.search(r"over_points \? pairs >= ([\d.]+) && n_meas >= (\d+) && n_pts >= \(1L << (\d+)\)", SRC)
-    assert n_pts * n_meas >= float(pays.group(1)) and n_meas >= int(pays.group(2)) and n_pts >= 1 << int(pays.group(3))
+    pays = re.search(r"over_points \? pairs >= \(n_meas < (\d+) \? ([\d.]+) : ([\d.]+)\) && n_meas >= (\d+) && n_pts >= \(1L << (\d+)\)", SRC)
+    few, least_few, least, meas, pts = (float(v) for v in pays.groups())
+    if n_pts * n_meas < (least_few if n_meas < few else least) or n_meas < meas or n_pts < 1 << int(pts):
+        assert got == 0
+        return
     most = min(int(re.search(r"kMaxCells = (\d+);", open(os.path.join(ROOT, "paper_2605_29097_amd", "csrc", "rfvr_impl.hpp")).read()).group(1)),
                n_pts // 256, (1 << 21) // n_meas)
     edge = max(t for t in range(1, 65) if t ** 3 <= most)
