@@ -334,7 +334,12 @@ int rfvr_sample_points(const rfvr_sample_desc* d, float* xyz, float* u, float* r
  * params: flat float32 vector, row-major [out][in] matrices in the order
  *   W_0,b_0,...,W_{L-1},b_{L-1}, w_out,b_out, Wh_0,bh_0,...,wh_out,bh_out.
  * ------------------------------------------------------------------------ */
-#define RFVR_PREC_FP32 0
+#define RFVR_PREC_FP32 0         /* FP32 operands and accumulation: values (trunk layers,
+                                    head) on the FP32 matrix instruction, derivatives (the
+                                    grad_x f sweep, tangents, adjoints, weight gradients) on
+                                    operands split in three BF16 parts, which hold all 24
+                                    bits down to 1e-33 (15 at 1e-36: upstream gradients of
+                                    that size lose precision) */
 #define RFVR_PREC_BF16 1         /* BF16 matrix operands, FP32 accumulation */
 #define RFVR_PREC_BF16X3 2       /* BF16 MFMA on split operands, x = big + small with
                                     big = bf16(x), small = bf16(x - big); products
