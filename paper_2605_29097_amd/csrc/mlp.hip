@@ -1168,12 +1168,13 @@ struct WgArgs {
     int n_split;
 };
 
-// Three waves per SIMD but for a pair in FP32 storage (the plain backward), whose two
-// prefetches then spill inside the loop (backward of 2^20 points, 8 layers of 256: 36.2 ms
-// in BF16 and 38.4 in FP16 with three, 31.0 and 33.4 with two; 300000 points 11.4 and
-// 11.9, 9.7 and 10.3).  The pair in BF16 storage stays at three (2^20 points 17.97 | 18.13 ms).
+// Three waves per SIMD in BF16 storage; in FP32 storage (the plain backward, the head)
+// three spill inside the loop (plain backward of 2^20 points, 8 layers of 256: 36.2 ms in
+// BF16 and 38.4 in FP16 with three, 31.0 and 33.4 with two; the head alone makes no
+// difference of 1 %).  The pair in BF16 storage stays at three (training backward 18.0 |
+// 18.2 ms).
 template <int PRO, int ST = 0, int ST2 = -1>
-__global__ __launch_bounds__(256, ST == 0 && ST2 == 0 ? 2 : 3) void k_gemm_wg(WgArgs g) {
+__global__ __launch_bounds__(256, ST == 0 ? 2 : 3) void k_gemm_wg(WgArgs g) {
     constexpr int BM = 128, BN = 128, BK = 32, LW = 128 + 4;
     __shared__ float sA[BK * LW];
     __shared__ float sB[BK * LW];
